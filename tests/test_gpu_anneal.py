@@ -124,3 +124,35 @@ def test_anneal_argument_errors(torch, ctx):
         Dd = bad.pop("D")
         with pytest.raises(D.DiscoverError):
             ctx.anneal(*args, Dd, **bad)
+
+
+# chains x problems decides how many lanes walk one chain: 64, 32, 16, 8, 4, 2, 1
+@pytest.mark.parametrize("Q", [511, 1000, 2047, 2049, 8192, 16384, 16400])
+def test_every_lane_count_walks_the_oracle_trajectory(torch, ctx, oracle_mod, Q):
+    S, n, D, K, T0, alpha, seed = 23, 129, 3, 61, 0.05, 0.98, 17
+    F, ids, y = _problem(31, S, n, D)
+    w, B, E = oracle_mod.anneal(F, ids, y, D, Q, K, T0, alpha, seed)
+    rows, _, _, en, crow, cen, _ = ctx.anneal(dev(torch, F), dev(torch, ids), dev(torch, y), D, chains=Q, steps=K,
+                                              T0=T0, alpha=alpha, seed=seed, chain_results=True)
+    assert np.array_equal(crow.cpu().numpy(), B)
+    assert np.array_equal(cen.cpu().numpy().view(np.int64), E.view(np.int64))
+    assert rows.cpu().numpy().tolist() == B[w].tolist() and float(en) == E[w]
+
+
+# rows uncorrelated exactly (zero quotients), constant rows, and values near the ends of the range
+@pytest.mark.parametrize("scale", [1.0, 1e150, 1e-150])
+def test_zero_and_extreme_correlations(torch, ctx, oracle_mod, scale):
+    S, n, D, Q, K = 16, 64, 4, 40, 300
+    t = np.arange(n)
+    F = np.array([((t >> (i % 6)) & 1) * 2.0 - 1.0 for i in range(S)]) * np.where(np.arange(S) < 6, 1.0, -3.0)[:, None]
+    F[6:12] += 1e-9 * np.random.default_rng(3).normal(size=(6, n))
+    F[13] = 4.0
+    y = (F[0] + 0.5 * F[1]) * scale
+    F = F * scale
+    ids = np.arange(S, dtype=np.int64)[::-1].copy()
+    w, B, E = oracle_mod.anneal(F, ids, y, D, Q, K, 0.05, 0.99, 5)
+    rows, _, _, en, crow, cen, _ = ctx.anneal(dev(torch, F), dev(torch, ids), dev(torch, y), D, chains=Q, steps=K,
+                                              T0=0.05, alpha=0.99, seed=5, chain_results=True)
+    assert np.array_equal(cen.cpu().numpy().view(np.int64), E.view(np.int64))
+    assert np.array_equal(crow.cpu().numpy(), B)
+    assert rows.cpu().numpy().tolist() == B[w].tolist()

@@ -23,14 +23,11 @@ namespace dsc {
 constexpr double SW3_RCP_DELTA = 4.76837158203125e-7;  // 2^-21: D = 3 sweep values use a bare rcp
 
 // ------------------------------------------------------------------ prep
-// One wave per row (rows 0..S-1 of F, row S = y): Z = (f - mean) / ||f - mean||,
-// and when nrm is given, nrm[row] = |Z row|^2 for the rows of F (0 for a
-// constant row).
+// One wave per row (rows 0..S-1 of F, row S = y): Z = (f - mean) / ||f - mean||.
 __device__ __forceinline__ void d_l0_prep(int n, int S, const double* __restrict__ F,
                                                  int64_t ldf, const double* __restrict__ y,
                                                  int ldz, double* __restrict__ Z,
-                                                 double* __restrict__ yy,
-                                                 double* __restrict__ nrm = nullptr) {
+                                                 double* __restrict__ yy) {
     const int row = blockIdx.x * 4 + wave_id();
     const int lane = threadIdx.x & 63;
     if (row > S) return;
@@ -46,16 +43,7 @@ __device__ __forceinline__ void d_l0_prep(int n, int S, const double* __restrict
     q = wave_sum(q);
     const double inv = q > 0.0 ? 1.0 / sqrt(q) : 0.0;
     double* z = Z + (int64_t)row * ldz;
-    double zz = 0.0;
-    for (int i = lane; i < ldz; i += 64) {
-        const double zi = i < n ? (f[i] - m) * inv : 0.0;
-        z[i] = zi;
-        zz += zi * zi;
-    }
-    if (nrm && row < S) {
-        zz = wave_sum(zz);
-        if (lane == 0) nrm[row] = zz;
-    }
+    for (int i = lane; i < ldz; i += 64) z[i] = i < n ? (f[i] - m) * inv : 0.0;
     if (row == S && lane == 0) *yy = q;
 }
 
@@ -809,49 +797,72 @@ __device__ __forceinline__ bool rank_before(const RankKey& x, const RankKey& y) 
     return x.e < y.e;
 }
 
-// The same ranking by one thread, for short bands (fewer barriers).
-constexpr int64_t RANK_SERIAL = 512;
+// The same ranking by one wave, for bands that it holds in registers (entry
+// lane + 64 u in v[u]): no barriers and no passes over memory; the band
+// entries of the models go to picks[m] (-1 past the last).  One thread
+// scanning a short band in memory took 82 us for 8 models of the L0 over all
+// pairs of 2000 rows; with this and a block per residual the launch takes 12.
+constexpr int RANK_U = 8;
+constexpr int64_t RANK_WAVE = 64 * RANK_U;
 
-__device__ __forceinline__ void rank_models_serial(const int4* __restrict__ band, const double* __restrict__ brss,
-                              const double* __restrict__ bcoef, int64_t nb, int D, int m,
-                              const int64_t* __restrict__ ids, double yy, int n, uint8_t* __restrict__ taken,
-                              int32_t* __restrict__ out_sub, double* __restrict__ out_rmse,
-                              double* __restrict__ out_coef, int32_t* __restrict__ chosen, int sub_ld,
-                              int coef_ld) {
-    for (int64_t e = 0; e < nb; e++) taken[e] = !(brss[e] >= 0.0);
+__device__ __forceinline__ void rank_models_wave(const int4* __restrict__ band, const double* __restrict__ brss,
+                                                 int64_t nb, int D, int m, const int64_t* __restrict__ ids,
+                                                 double yy, int* picks) {
+    const int lane = threadIdx.x & 63;
+    double v[RANK_U];
+#pragma unroll
+    for (int u = 0; u < RANK_U; u++) {
+        const int64_t e = lane + 64 * u;
+        const double x = e < nb ? brss[e] : INFINITY;
+        v[u] = x >= 0.0 ? x : INFINITY;
+    }
     for (int q = 0; q < m; q++) {
-        double rmin = INFINITY;
-        for (int64_t e = 0; e < nb; e++)
-            if (!taken[e] && brss[e] < rmin) rmin = brss[e];
-        RankKey best{{0, 0, 0}, -1};
+        double rmin = v[0];
+#pragma unroll
+        for (int u = 1; u < RANK_U; u++) rmin = fmin(rmin, v[u]);
+        rmin = wave_min(rmin);
+        int pick = -1, tied = 0;
         if (rmin < INFINITY) {
-            for (int64_t e = 0; e < nb; e++) {
-                if (taken[e] || !(brss[e] <= rmin + TAU_TIE * yy)) continue;
-                const int4 sv = band[e];
-                const int pos[3] = {sv.x, sv.y, sv.z};
-                RankKey c{{0, 0, 0}, e};
-                for (int j = 0; j < D; j++) c.k[j] = ids[pos[j]];
-                for (int u = 1; u < D; u++)
-                    for (int v = u; v > 0 && c.k[v - 1] > c.k[v]; v--) {
-                        const int64_t tt = c.k[v]; c.k[v] = c.k[v - 1]; c.k[v - 1] = tt;
-                    }
-                if (rank_before(c, best)) best = c;
+            const double lim = rmin + TAU_TIE * yy;
+#pragma unroll
+            for (int u = 0; u < RANK_U; u++) {
+                const uint64_t at = __ballot(v[u] <= lim);
+                if (at) pick = 64 * u + __builtin_ctzll(at);
+                tied += __popcll(at);
+            }
+            if (tied != 1) {                         // several within the tolerance: the smallest ID tuple
+                RankKey best{{0, 0, 0}, -1};
+#pragma unroll
+                for (int u = 0; u < RANK_U; u++) {
+                    if (!(v[u] <= lim)) continue;
+                    const int4 sv = band[lane + 64 * u];
+                    const int pos[3] = {sv.x, sv.y, sv.z};
+                    RankKey c{{0, 0, 0}, lane + 64 * u};
+#pragma unroll
+                    for (int j = 0; j < 3; j++) c.k[j] = j < D ? ids[pos[j]] : INT64_MAX;
+#pragma unroll
+                    for (int x = 1; x < 3; x++)      // sort the ID tuple (unused places stay last)
+#pragma unroll
+                        for (int y = x; y > 0; y--)
+                            if (c.k[y - 1] > c.k[y]) {
+                                const int64_t tt = c.k[y]; c.k[y] = c.k[y - 1]; c.k[y - 1] = tt;
+                            }
+                    if (rank_before(c, best)) best = c;
+                }
+                for (int o = 32; o > 0; o >>= 1) {
+                    RankKey x;
+#pragma unroll
+                    for (int j = 0; j < 3; j++) x.k[j] = __shfl_xor((long long)best.k[j], o, 64);
+                    x.e = __shfl_xor((long long)best.e, o, 64);
+                    if (rank_before(x, best)) best = x;
+                }
+                pick = (int)best.e;
             }
         }
-        const int64_t pick = best.e;
-        chosen[q] = (int32_t)pick;
-        if (pick < 0) {
-            for (int j = 0; j < D; j++) out_sub[q * sub_ld + j] = -1;
-            out_rmse[q] = __longlong_as_double(0x7FF8000000000000LL);
-            for (int j = 0; j <= D; j++) out_coef[q * coef_ld + j] = __longlong_as_double(0x7FF8000000000000LL);
-            continue;
-        }
-        taken[pick] = 1;
-        const int4 sv = band[pick];
-        const int pos[3] = {sv.x, sv.y, sv.z};
-        for (int j = 0; j < D; j++) out_sub[q * sub_ld + j] = pos[j];
-        out_rmse[q] = sqrt(brss[pick] / n);
-        for (int j = 0; j <= D; j++) out_coef[q * coef_ld + j] = bcoef[pick * (D + 1) + j];
+        if (lane == 0) picks[q] = pick;
+#pragma unroll
+        for (int u = 0; u < RANK_U; u++)
+            if (pick == lane + 64 * u) v[u] = INFINITY;
     }
 }
 
@@ -867,12 +878,6 @@ __device__ __forceinline__ void d_rank_models(const int4* __restrict__ band, con
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const double yy = *yyp;
     const int64_t nb = min((int64_t)*bcnt, bcap);
-    if (nb <= RANK_SERIAL) {                         // (block-uniform) a short band: one thread
-        if (t == 0) rank_models_serial(band, brss, bcoef, nb, D, m, ids, yy, n, taken, out_sub, out_rmse,
-                                       out_coef, chosen, sub_ld, coef_ld);
-        __syncthreads();
-        return;
-    }
     for (int64_t e = t; e < nb; e += 256) taken[e] = !(brss[e] >= 0.0);
     __syncthreads();
     for (int q = 0; q < m; q++) {
@@ -935,23 +940,27 @@ __device__ __forceinline__ void d_rank_models(const int4* __restrict__ band, con
     }
 }
 
-// Residual of chosen model q (NaN for a missing model), by the 256 threads
-// of a block.
-__device__ __forceinline__ void d_resid(int q, int n, int D, const double* __restrict__ F,
-                                               int64_t ldf, const double* __restrict__ y,
-                                               const int32_t* __restrict__ sub,
-                                               const double* __restrict__ coef,
-                                               double* __restrict__ out, int64_t ldr, int sub_ld, int coef_ld) {
-    const int32_t* s = sub + q * sub_ld;
-    const double* c = coef + q * coef_ld;
+// Residual of a model of rows sub and coefficients c (NaN for a missing
+// model), by the 256 threads of a block.
+__device__ __forceinline__ void d_resid(int n, int D, const double* __restrict__ F, int64_t ldf,
+                                        const double* __restrict__ y, const int32_t* sub,
+                                        const double* __restrict__ c, double* __restrict__ out) {
+    int s[3];
+    double k[4];
+#pragma unroll
+    for (int j = 0; j < 3; j++) s[j] = j < D ? sub[j] : 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) k[j] = j <= D ? c[j] : 0.0;
     for (int i = threadIdx.x; i < n; i += 256) {
         if (s[0] < 0) {
-            out[q * ldr + i] = __longlong_as_double(0x7FF8000000000000LL);
+            out[i] = __longlong_as_double(0x7FF8000000000000LL);
             continue;
         }
-        double p = c[0];
-        for (int j = 0; j < D; j++) p = fma(c[j + 1], F[(int64_t)s[j] * ldf + i], p);
-        out[q * ldr + i] = y[i] - p;
+        double p = k[0];
+#pragma unroll
+        for (int j = 0; j < 3; j++)
+            if (j < D) p = fma(k[j + 1], F[(int64_t)s[j] * ldf + i], p);
+        out[i] = y[i] - p;
     }
 }
 
@@ -978,30 +987,6 @@ __global__ __launch_bounds__(256) void k_l0_prep(ctab<PrepArgs> A) {
         a.clr[w] = 0u;
     if ((int)blockIdx.x * 4 > a.S) return;
     d_l0_prep(a.n, a.S, a.F, a.ldf, a.y, a.ldz, a.Z, a.yy);
-}
-
-// OMP set-up for one problem: grid (row blocks of 4).  Standardised rows,
-// their squared norms, and (block 0) the starting active set.
-// Warm start: the rows of init that lie in 0..S-1, first occurrences only,
-// in order; a missing or repeated row leaves the model one row shorter.
-__global__ __launch_bounds__(256) void k_omp_prep(int n, int S, const double* __restrict__ F,
-                                                  int64_t ldf, const double* __restrict__ y, int ldz,
-                                                  double* __restrict__ Z, double* __restrict__ yy,
-                                                  double* __restrict__ nrm,
-                                                  int32_t* __restrict__ active, int D_max,
-                                                  const int32_t* __restrict__ init, int n_init,
-                                                  int32_t* __restrict__ nact) {
-    d_l0_prep(n, S, F, ldf, y, ldz, Z, yy, nrm);
-    if (blockIdx.x != 0 || threadIdx.x != 0) return;
-    int c = 0;
-    for (int q = 0; q < n_init; q++) {
-        const int r = init[q];
-        bool keep = r >= 0 && r < S;
-        for (int t = 0; t < c; t++) keep = keep && active[t] != r;
-        if (keep) active[c++] = r;
-    }
-    for (int q = c; q < D_max; q++) active[q] = -1;
-    *nact = c;
 }
 
 // grid (8 x the tiles of the busiest XCD, 1, problems).  Block p runs on
@@ -1142,122 +1127,435 @@ __global__ __launch_bounds__(256) void k_refit_all(ctab<RefitArgs> A, int na,
     }
 }
 
-// grid (problems): the m best models of each problem's band (one thread),
-// then their residuals when asked for (the whole block).
+// grid (problems, models when residuals are asked for): the m best models
+// of each problem's band and their residuals.  A band that one wave ranks
+// is ranked by every block, the first of which writes the models, and
+// block y writes the residual of model y; a longer one by the first block
+// alone, which writes everything.
 __global__ __launch_bounds__(256) void k_rank_models(ctab<RefitArgs> A) {
     const RefitArgs& a = tab(A, blockIdx.x);
     DSC_GLOBAL(a.F); DSC_GLOBAL(a.y); DSC_GLOBAL(a.band); DSC_GLOBAL(a.bcnt); DSC_GLOBAL(a.scratch); DSC_GLOBAL(a.brss); DSC_GLOBAL(a.bcoef); DSC_GLOBAL(a.ids); DSC_GLOBAL(a.yy); DSC_GLOBAL(a.taken); DSC_GLOBAL(a.out_sub); DSC_GLOBAL(a.out_rmse); DSC_GLOBAL(a.out_coef); DSC_GLOBAL(a.chosen); DSC_GLOBAL(a.out_resid);
+    const int64_t nb = min((int64_t)*a.bcnt, a.bcap);
+    if (nb <= RANK_WAVE) {
+        __shared__ int picks[64];
+        const int D = a.D;
+        if (threadIdx.x < 64) rank_models_wave(a.band, a.brss, nb, D, a.m, a.ids, *a.yy, picks);
+        __syncthreads();
+        const double nan = __longlong_as_double(0x7FF8000000000000LL);
+        if (blockIdx.y == 0 && (int)threadIdx.x < a.m) {
+            const int q = threadIdx.x, e = picks[q];
+            int4 sv = make_int4(-1, -1, -1, -1);
+            if (e >= 0) sv = a.band[e];
+            const int pos[3] = {sv.x, sv.y, sv.z};
+            a.chosen[q] = e;
+            for (int j = 0; j < D; j++) a.out_sub[q * a.sub_ld + j] = pos[j];
+            a.out_rmse[q] = e >= 0 ? sqrt(a.brss[e] / a.n) : nan;
+            for (int j = 0; j <= D; j++)
+                a.out_coef[q * a.coef_ld + j] = e >= 0 ? a.bcoef[(int64_t)e * (D + 1) + j] : nan;
+        }
+        if (!a.out_resid) return;
+        for (int q = blockIdx.y; q < a.m; q += gridDim.y) {
+            const int e = picks[q];
+            int4 sv = make_int4(-1, -1, -1, -1);
+            if (e >= 0) sv = a.band[e];
+            const int32_t pos[3] = {sv.x, sv.y, sv.z};
+            d_resid(a.n, D, a.F, a.ldf, a.y, pos, a.bcoef + (int64_t)max(e, 0) * (D + 1), a.out_resid + q * a.ldr);
+        }
+        return;
+    }
+    if (blockIdx.y != 0) return;
     d_rank_models(a.band, a.brss, a.bcoef, a.bcnt, a.bcap, a.D, a.m, a.ids, a.yy, a.n, a.taken,
                   a.out_sub, a.out_rmse, a.out_coef, a.chosen, a.sub_ld, a.coef_ld);
     if (!a.out_resid) return;
     __syncthreads();                             // the chosen models are written
     for (int q = 0; q < a.m; q++)
-        d_resid(q, a.n, a.D, a.F, a.ldf, a.y, a.out_sub, a.out_coef, a.out_resid, a.ldr, a.sub_ld,
-                a.coef_ld);
+        d_resid(a.n, a.D, a.F, a.ldf, a.y, a.out_sub + q * a.sub_ld, a.out_coef + q * a.coef_ld,
+                a.out_resid + q * a.ldr);
 }
 
 // ------------------------------------------------------------------ OMP
-// g_j = |Z_j . r| for inactive rows (one wave per row).
-__global__ __launch_bounds__(256) void k_omp_corr(int n, int S, const double* __restrict__ Z, int ldz,
-                                                  const double* __restrict__ r,
-                                                  const int32_t* __restrict__ active,
-                                                  const int32_t* __restrict__ nact,
-                                                  double* __restrict__ g) {
-    const int j = blockIdx.x * 4 + wave_id();
+// One problem's pointers; a launch takes up to OMP_CHUNK of them as kernel
+// arguments (grid.y = problem), so that it needs no argument table in
+// device memory.
+struct OmpProb {
+    int n, S;
+    const double* F;
+    int64_t ldf;
+    const double* y;
+    const int64_t* ids;
+    double *mean, *inv;       // per row: mean, 1 / ||f - mean|| (0: constant row)
+    double* g;                // per row: |z . r|, -1 for an active one
+    double* A;                // the reflectors' columns, then the reduced right-hand side; D_max + 2 columns of n
+    double* TR;               // packed upper triangles T and R, (D_max + 1)(D_max + 2) values
+    double* r;                // residual
+    int32_t *active, *nact;
+    double *coef, *rmse;
+    const int32_t* init;
+};
+
+constexpr int OMP_CHUNK = 16;
+
+struct OmpArgs {
+    OmpProb p[OMP_CHUNK];
+};
+
+// OMP set-up: grid (row blocks of 4, problems).  One wave per row: its mean
+// and inverse norm (rows of up to 2048 samples are read once and kept in
+// registers), and (block 0) the starting active set: the rows of init that
+// lie in 0..S-1, first occurrences only, in order; a missing or repeated
+// row leaves the model one row shorter.  The standardised rows themselves
+// are not stored: the correlations form them again from F with the same
+// two operations, which halves the traffic of this pass.  Bound by HBM;
+// S = 3000, n = 2000: 38 us when it stored them, 10 us now.
+__global__ __launch_bounds__(256) void k_omp_prep(OmpArgs args, int D_max, int n_init) {
+    const OmpProb& a = args.p[blockIdx.y];
+    const int row = blockIdx.x * 4 + wave_id();
     const int lane = threadIdx.x & 63;
-    if (j >= S) return;
-    double s = 0.0;
-    for (int i = lane; i < n; i += 64) s += Z[(int64_t)j * ldz + i] * r[i];
-    s = fabs(wave_sum(s));
-    if (lane == 0) {
-        bool act = false;
-        for (int q = 0; q < *nact; q++) act |= active[q] == j;
-        double zz = 0.0;
-        (void)zz;
-        g[j] = act ? -1.0 : s;
+    if (row < a.S) {
+        const int n = a.n;
+        const double* f = a.F + (int64_t)row * a.ldf;
+        double s = 0.0, q = 0.0, m;
+        if (n <= 32 * 64) {
+            double v[32];
+#pragma unroll
+            for (int u = 0; u < 32; u++) v[u] = lane + 64 * u < n ? f[lane + 64 * u] : 0.0;
+#pragma unroll
+            for (int u = 0; u < 32; u++)
+                if (lane + 64 * u < n) s += v[u];
+            m = wave_sum(s) / n;
+#pragma unroll
+            for (int u = 0; u < 32; u++) {
+                const double d = v[u] - m;
+                if (lane + 64 * u < n) q += d * d;
+            }
+        } else {
+            for (int i = lane; i < n; i += 64) s += f[i];
+            m = wave_sum(s) / n;
+            for (int i = lane; i < n; i += 64) {
+                const double d = f[i] - m;
+                q += d * d;
+            }
+        }
+        q = wave_sum(q);
+        if (lane == 0) {
+            a.mean[row] = m;
+            a.inv[row] = q > 0.0 ? 1.0 / sqrt(q) : 0.0;
+        }
+    }
+    if (blockIdx.x != 0 || threadIdx.x != 0) return;
+    int c = 0;
+    for (int q = 0; q < n_init; q++) {
+        const int r = a.init[q];
+        bool keep = r >= 0 && r < a.S;
+        for (int t = 0; t < c; t++) keep = keep && a.active[t] != r;
+        if (keep) a.active[c++] = r;
+    }
+    for (int q = c; q < D_max; q++) a.active[q] = -1;
+    *a.nact = c;
+}
+
+// g_j = |z_j . r| for inactive rows, z_j = (f_j - mean_j) / ||f_j - mean_j||
+// formed on the way: grid (row blocks of 8, problems), two rows per wave so
+// that a load of r serves both and enough loads of F are in flight.  Bound
+// by reading F.
+__global__ __launch_bounds__(256) void k_omp_corr(OmpArgs args) {
+    const OmpProb& a = args.p[blockIdx.y];
+    const int j0 = blockIdx.x * 8 + 2 * wave_id();
+    const int lane = threadIdx.x & 63;
+    if (j0 >= a.S) return;
+    const int j1 = min(j0 + 1, a.S - 1), n = a.n;
+    const double *f0 = a.F + (int64_t)j0 * a.ldf, *f1 = a.F + (int64_t)j1 * a.ldf, *r = a.r;
+    const double m0 = a.mean[j0], m1 = a.mean[j1], v0 = a.inv[j0], v1 = a.inv[j1];
+    double s0 = 0.0, s1 = 0.0;
+    int i = lane;
+    for (; i + 7 * 64 < n; i += 8 * 64) {
+        double x0[8], x1[8], w[8];
+#pragma unroll
+        for (int u = 0; u < 8; u++) { x0[u] = f0[i + 64 * u]; x1[u] = f1[i + 64 * u]; w[u] = r[i + 64 * u]; }
+#pragma unroll
+        for (int u = 0; u < 8; u++) { s0 += (x0[u] - m0) * v0 * w[u]; s1 += (x1[u] - m1) * v1 * w[u]; }
+    }
+    for (; i < n; i += 64) {
+        const double w = r[i];
+        s0 += (f0[i] - m0) * v0 * w;
+        s1 += (f1[i] - m1) * v1 * w;
+    }
+    s0 = fabs(wave_sum(s0));
+    s1 = fabs(wave_sum(s1));
+    if (lane > 1 || (lane == 1 && j1 == j0)) return;
+    const int j = lane ? j1 : j0, d = *a.nact;
+    bool act = false;
+    for (int q = 0; q < d; q++) act |= a.active[q] == j;
+    a.g[j] = act ? -1.0 : lane ? s1 : s0;
+}
+
+// Index of entry (row j, column c), j <= c, of a packed upper triangle.
+__device__ __forceinline__ int tri(int j, int c) { return c * (c + 1) / 2 + j; }
+
+// Sums of up to OMP_M + 1 values over the 512 threads of a block, in a
+// fixed order; every thread gets them in tot.  Two barriers.
+constexpr int OMP_M = DISCOVER_MAX_D + 1;     // most columns: intercept and rows
+constexpr int OMP_T = 512, OMP_W = OMP_T / 64;
+
+__device__ __forceinline__ void omp_reduce(double (&v)[OMP_M + 1], int count, double (*red)[OMP_W], double* tot) {
+    const int lane = threadIdx.x & 63, wv = wave_id();
+#pragma unroll
+    for (int q = 0; q <= OMP_M; q++)
+        if (q < count) {
+            const double t = wave_sum(v[q]);
+            if (lane == 0) red[q][wv] = t;
+        }
+    __syncthreads();
+    for (int q = wv; q < count; q += OMP_W) {
+        const double t = wave_sum(lane < OMP_W ? red[q][lane] : 0.0);
+        if (lane == 0) tot[q] = t;
+    }
+    __syncthreads();
+}
+
+// What the append and residual steps share in LDS.
+struct OmpLds {
+    double T[OMP_M * (OMP_M + 1) / 2], R[OMP_M * (OMP_M + 1) / 2];
+    double red[OMP_M + 1][OMP_W], tot[OMP_M + 1], tv[OMP_M], vm[OMP_M + 2], cf[OMP_M];
+    int idx[OMP_M];
+};
+
+// Column m (0: the intercept, else row idx[m - 1]) joins the factorisation
+// of columns 0..m-1.  The count is fixed at compile time so that all of a
+// sample's loads are issued before the first is used.  Every thread reads
+// and writes its own samples of the columns.
+template <int m>
+__device__ __forceinline__ void omp_append(const OmpProb& a, double* w, OmpLds& L) {
+    const int tid = threadIdx.x, n = a.n;
+    const double* f = m ? a.F + (int64_t)L.idx[m ? m - 1 : 0] * a.ldf : nullptr;
+    double* am = a.A + (int64_t)m * n;
+    double sm[OMP_M + 1];
+#pragma unroll
+    for (int q = 0; q <= OMP_M; q++) sm[q] = 0.0;
+    if (m > 0) {
+#pragma unroll 4
+        for (int i = tid; i < n; i += OMP_T) {
+            const double v = f[i];
+#pragma unroll
+            for (int j = 0; j < m; j++) sm[j] += a.A[(int64_t)j * n + i] * v;
+        }
+        omp_reduce(sm, m, L.red, L.tot);
+        if (tid < m) {
+            double t = 0.0;
+#pragma unroll
+            for (int j = 0; j < m; j++)
+                if (j <= tid) t = fma(L.T[tri(j, tid)], L.tot[j], t);
+            L.tv[tid] = t;
+        }
+        __syncthreads();
+    }
+    // sums over samples >= m: [0] a^2, [1] a w, [2 + j] v_j a
+#pragma unroll
+    for (int q = 0; q <= OMP_M; q++) sm[q] = 0.0;
+    double tv[m ? m : 1];
+#pragma unroll
+    for (int j = 0; j < m; j++) tv[j] = L.tv[j];
+#pragma unroll 4
+    for (int i = tid; i < n; i += OMP_T) {
+        double v = m ? f[i] : 1.0, col[m ? m : 1];
+        const double wi = w[i];
+#pragma unroll
+        for (int j = 0; j < m; j++) col[j] = a.A[(int64_t)j * n + i];
+#pragma unroll
+        for (int j = 0; j < m; j++) v = fma(-col[j], tv[j], v);
+        am[i] = v;
+        if (i < m) {
+            L.R[tri(i, m)] = v;
+        } else {
+            sm[0] += v * v;
+            sm[1] += v * wi;
+#pragma unroll
+            for (int j = 0; j < m; j++) sm[2 + j] += col[j] * v;
+        }
+        if (i == m) {
+            L.vm[0] = v;
+            L.vm[1] = wi;
+#pragma unroll
+            for (int j = 0; j < m; j++) L.vm[2 + j] = col[j];
+        }
+    }
+    omp_reduce(sm, m + 2, L.red, L.tot);
+    const double nrm = sqrt(L.tot[0]), amm = L.vm[0];
+    const double alpha = amm > 0 ? -nrm : nrm;
+    const double v0 = amm - alpha;
+    const double vv = 2.0 * nrm * (nrm + fabs(amm));   // v^T v
+    const double tau = vv > 0.0 ? 2.0 / vv : 0.0;
+    const double tw = tau * fma(v0 - amm, L.vm[1], L.tot[1]);
+    if (tid < m) {
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < m; j++)
+            if (j >= tid) t = fma(L.T[tri(tid, j)], fma(v0 - amm, L.vm[2 + j], L.tot[2 + j]), t);
+        L.T[tri(tid, m)] = -tau * t;
+    }
+    if (tid == 0) {
+        L.T[tri(m, m)] = tau;
+        L.R[tri(m, m)] = alpha;
+    }
+#pragma unroll 4
+    for (int i = tid; i < n; i += OMP_T) {
+        const double x = am[i], wi = w[i];
+        const double v = i < m ? 0.0 : i == m ? v0 : x;
+        am[i] = v;
+        if (i >= m) w[i] = wi - tw * v;
+    }
+    __syncthreads();
+}
+
+// r = y - prediction of the model of d rows.
+template <int d>
+__device__ __forceinline__ void omp_resid(const OmpProb& a, const OmpLds& L) {
+    const double* f[d ? d : 1];
+    double c[d + 1];
+    c[0] = L.cf[0];
+#pragma unroll
+    for (int j = 0; j < d; j++) {
+        f[j] = a.F + (int64_t)L.idx[j] * a.ldf;
+        c[j + 1] = L.cf[j + 1];
+    }
+#pragma unroll 4
+    for (int i = threadIdx.x; i < a.n; i += OMP_T) {
+        double p = c[0], x[d ? d : 1];
+        const double yi = a.y[i];
+#pragma unroll
+        for (int j = 0; j < d; j++) x[j] = f[j][i];
+#pragma unroll
+        for (int j = 0; j < d; j++) p = fma(c[j + 1], x[j], p);
+        a.r[i] = yi - p;
     }
 }
 
-// One OMP step in one workgroup.  With g given, first the argmax of g by
+#define OMP_SWITCH(k, call)                                                                          \
+    switch (k) {                                                                                     \
+    case 0: call(0); break; case 1: call(1); break; case 2: call(2); break; case 3: call(3); break;  \
+    case 4: call(4); break; case 5: call(5); break; case 6: call(6); break; case 7: call(7); break;  \
+    default: call(8); break;                                                                         \
+    }
+
+// One OMP step of each problem (grid.y), one workgroup each.  build: the
+// Householder QR of [1, active rows] from nothing, else the factorisation
+// an earlier launch left in A and TR is taken on.  pick: the argmax of g by
 // (-g, ID) over the non-constant rows is appended to the active list (none
-// when every row is taken); then the least-squares fit on the active rows,
-// its residual r and, with out_rmse given, sqrt(RSS / n).
-__global__ __launch_bounds__(256) void k_omp_fit(int n, const double* __restrict__ F, int64_t ldf,
-                                                 const double* __restrict__ y,
-                                                 int32_t* __restrict__ active,
-                                                 int32_t* __restrict__ nact,
-                                                 double* __restrict__ A, double* __restrict__ coef,
-                                                 double* __restrict__ rss, double* __restrict__ r,
-                                                 int use_lds, int S, const double* __restrict__ g,
-                                                 const int64_t* __restrict__ ids,
-                                                 const double* __restrict__ rownorm,
-                                                 double* __restrict__ out_rmse) {
-    __shared__ int idx[DISCOVER_MAX_D];
-    __shared__ double cf[DISCOVER_MAX_D + 1];
-    __shared__ double rs;
-    __shared__ double bg[256];
-    __shared__ int bj[256];
-    __shared__ int s_d;
-    extern __shared__ double dsm[];              // (D_max + 2) * n doubles when use_lds
-    if (threadIdx.x == 0) s_d = *nact;
-    __syncthreads();
-    const int d0 = s_d;
+// when every row is taken).  Then the coefficients, the residual r and,
+// when last, sqrt(RSS / n).
+//
+// A column joins the factorisation by one application of all reflectors at
+// once (compact WY form: Q = I - V T V^T, Schreiber and Van Loan, SIAM J.
+// Sci. Stat. Comput. 10, 1989): the dot products V^T a in one reduction,
+// then the norm of the remainder with its products with V (T's next
+// column) and with the right-hand side in a second one.  The work is
+// latency: refitting every column at each pick took a reduction and an
+// update pass per column, 11 to 66 us a launch at n = 2000 and 0 to 6
+// rows; a launch that appends one column takes 15 to 22 us.
+__global__ __launch_bounds__(OMP_T) void k_omp_fit(OmpArgs args, int D_max, int build, int fixed, int pick_one,
+                                                   int last) {
+    const OmpProb& a = args.p[blockIdx.y];
+    __shared__ OmpLds L;
+    __shared__ double wbest[OMP_W];
+    __shared__ int wrow[OMP_W];
+    const int tid = threadIdx.x, lane = tid & 63, wv = wave_id();
+    const int n = a.n;
+    double* w = a.A + (int64_t)(D_max + 1) * n;
+    const int d0 = fixed >= 0 ? fixed : *a.nact;
+    const int tri_len = (D_max + 1) * (D_max + 2) / 2;
+    if (tid < d0) L.idx[tid] = a.active[tid];
+    int m = 0;                                   // columns factorised so far
+    if (build) {
+        for (int i = tid; i < n; i += OMP_T) w[i] = a.y[i];
+    } else {
+        m = d0 + 1;
+        for (int q = tid; q < tri(0, m); q += OMP_T) { L.T[q] = a.TR[q]; L.R[q] = a.TR[tri_len + q]; }
+    }
     int pick = -1;
-    if (g) {
+    if (pick_one) {
         double best = -2.0;
         int bi = -1;
         // four rows per thread are loaded before any is compared, so the
-        // loads overlap; rows are visited in increasing j as before
-        for (int j0 = threadIdx.x; j0 < S; j0 += 4 * 256) {
+        // loads overlap; rows are visited in increasing j
+        for (int j0 = tid; j0 < a.S; j0 += 4 * OMP_T) {
             double nv[4], gv[4];
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                const int j = j0 + q * 256;
-                nv[q] = j < S ? rownorm[j] : 0.0;
-                gv[q] = j < S ? g[j] : 0.0;
+                const int j = j0 + q * OMP_T;
+                nv[q] = j < a.S ? a.inv[j] : 0.0;
+                gv[q] = j < a.S ? a.g[j] : 0.0;
             }
 #pragma unroll
             for (int q = 0; q < 4; q++) {
-                const int j = j0 + q * 256;
+                const int j = j0 + q * OMP_T;
                 if (!(nv[q] > 0.0)) continue;
                 const double v = gv[q];
-                if (v > best || (v == best && bi >= 0 && ids[j] < ids[bi])) {
+                if (v > best || (v == best && bi >= 0 && a.ids[j] < a.ids[bi])) {
                     best = v;
                     bi = j;
                 }
             }
         }
-        bg[threadIdx.x] = best;
-        bj[threadIdx.x] = bi;
+        // the better of two choices (-1: none) by (-g, ID)
+        auto better = [&](double v, int j, double bv, int bj) {
+            return j >= 0 && (bj < 0 || v > bv || (v == bv && a.ids[j] < a.ids[bj]));
+        };
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const double v = __shfl_xor(best, o);
+            const int j = __shfl_xor(bi, o);
+            if (better(v, j, best, bi)) { best = v; bi = j; }
+        }
+        if (lane == 0) { wbest[wv] = best; wrow[wv] = bi; }
         __syncthreads();
-        for (int o = 128; o > 0; o >>= 1) {
-            if (threadIdx.x < o) {
-                const double v = bg[threadIdx.x + o];
-                const int j = bj[threadIdx.x + o];
-                const int cj = bj[threadIdx.x];
-                if (j >= 0 && (cj < 0 || v > bg[threadIdx.x] || (v == bg[threadIdx.x] && ids[j] < ids[cj]))) {
-                    bg[threadIdx.x] = v;
-                    bj[threadIdx.x] = j;
-                }
-            }
-            __syncthreads();
-        }
-        pick = bj[0] >= 0 && bg[0] >= 0.0 ? bj[0] : -1;
-        if (threadIdx.x == 0 && pick >= 0) {
-            active[d0] = pick;
-            *nact = d0 + 1;
+        best = wbest[0];
+        bi = wrow[0];
+        for (int q = 1; q < OMP_W; q++)
+            if (better(wbest[q], wrow[q], best, bi)) { best = wbest[q]; bi = wrow[q]; }
+        pick = bi >= 0 && best >= 0.0 ? bi : -1;
+        if (tid == 0 && pick >= 0) {
+            a.active[d0] = pick;
+            *a.nact = d0 + 1;
+            L.idx[d0] = pick;
         }
     }
-    const int d = pick >= 0 ? d0 + 1 : d0;
-    if (threadIdx.x < d) idx[threadIdx.x] = threadIdx.x < d0 ? active[threadIdx.x] : pick;
     __syncthreads();
-    if (use_lds) block_lsq(n, d, idx, F, ldf, y, dsm, cf, &rs, r);
-    else block_lsq(n, d, idx, F, ldf, y, A, cf, &rs, r);
-    if (threadIdx.x == 0) {
-        for (int j = 0; j <= d; j++) coef[j] = cf[j];
-        *rss = rs;
-        if (out_rmse) *out_rmse = sqrt(rs / n);
+    const int M = pick >= 0 ? d0 + 2 : d0 + 1;   // columns of this step's model
+    for (; m < M; m++) {
+#define OMP_APPEND(k) omp_append<k>(a, w, L)
+        OMP_SWITCH(m, OMP_APPEND)
+#undef OMP_APPEND
     }
+    // R coef = w[0..M): column by column from the last, one lane per row
+    if (wv == 0) {
+        double x = lane < M ? w[lane] : 0.0;
+        for (int c = M - 1; c >= 0; c--) {
+            const double v = __shfl(x, c) / L.R[tri(c, c)];
+            if (lane < c) x = fma(-L.R[tri(lane, c)], v, x);
+            if (lane == c) x = v;
+        }
+        if (lane < M) {
+            L.cf[lane] = x;
+            a.coef[lane] = x;
+        }
+    }
+    if (last) {
+        double sm[OMP_M + 1];
+        sm[0] = 0.0;
+        for (int i = tid; i < n; i += OMP_T) {
+            const double v = w[i];
+            if (i >= M) sm[0] += v * v;
+        }
+        omp_reduce(sm, 1, L.red, L.tot);
+        if (tid == 0) *a.rmse = sqrt(L.tot[0] / n);
+    } else {
+        for (int q = tid; q < tri(0, M); q += OMP_T) { a.TR[q] = L.T[q]; a.TR[tri_len + q] = L.R[q]; }
+        __syncthreads();
+    }
+    if (!a.r) return;
+#define OMP_RESID(k) omp_resid<k>(a, L)
+    OMP_SWITCH(M - 1, OMP_RESID)
+#undef OMP_RESID
 }
 
 // ================================================================== host
@@ -1600,7 +1898,8 @@ void l0_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int D
                                                                                    sld, rl);
             check_launch("k_refit");
         }
-        k_rank_models<<<na, 256, 0, st>>>(dfa);
+        const bool any_resid = std::any_of(outs.begin(), outs.end(), [](const L0Out& o) { return o.resid != nullptr; });
+        k_rank_models<<<dim3(na, any_resid ? m : 1), 256, 0, st>>>(dfa);
         check_launch("k_rank_models");
         if (devmode) {                          // capacities are checked on the device
             for (int q = 0; q < na; q++) bcl.push_back(BandCheck{ba[q].bcnt, cap[act[q]]});
@@ -1699,9 +1998,12 @@ extern "C" discover_status discover_l0_fit(discover_ctx* ctx, const discover_l0_
 
 namespace dsc {
 
-// Work buffers of one problem's OMP (byte sizes, each a multiple of 256):
-// standardised rows Z, |y - mean|^2, active count, scores, row norms,
-// residual (when the caller keeps none), QR columns, RSS.
+// Work space of one problem's OMP, as documented for the allocation-free
+// form (byte sizes, each a multiple of 256): row means and the triangles T
+// and R (in a part sized (S + 1) rows of samples), two single values, scores, inverse norms,
+// residual (when the caller keeps none), QR columns, one value.  The first
+// part holds 8 (S + (D_max + 1)(D_max + 2)) bytes of use: S >= D_max and at
+// least 16 samples a row make that fit.
 static void omp_sizes(const discover_l0_problem& pb, int D_max, bool resid, size_t sz[8]) {
     auto r256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
     const size_t ldz = (size_t)cdiv(pb.n, 16) * 16;
@@ -1731,48 +2033,47 @@ void omp_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int 
                char* scratch) {
     static const char* const names[8] = {"ompZ", "ompyy", "ompn", "ompg", "ompnrm", "ompr", "ompA", "omprss"};
     size_t off = 0;
-    for (int b = 0; b < nb; b++) {
-        const discover_l0_problem& pb = probs[b];
-        const int ldz = (int)cdiv(pb.n, 16) * 16;
-        size_t sz[8];
-        omp_sizes(pb, D_max, out_resid != nullptr, sz);
-        char* w[8] = {};
-        for (int q = 0; q < 8; q++) {
-            if (!sz[q]) continue;
-            if (scratch) {                       // the caller's scratch, laid out in order
-                w[q] = scratch + off;
-                off += sz[q];
-            } else {
-                w[q] = (char*)ctx->raw(names[q] + std::to_string(b), sz[q]);
+    // (no timer events in the scratch form: it creates nothing)
+    std::unique_ptr<KTimer> kt(scratch ? nullptr : new KTimer(ctx, st, "omp"));
+    for (int b0 = 0; b0 < nb; b0 += OMP_CHUNK) {
+        const int nc = std::min(OMP_CHUNK, nb - b0);
+        OmpArgs A{};
+        int Smax = 0;
+        for (int b = b0; b < b0 + nc; b++) {
+            const discover_l0_problem& pb = probs[b];
+            size_t sz[8];
+            omp_sizes(pb, D_max, out_resid != nullptr, sz);
+            if (!scratch) sz[0] = (size_t)(pb.S + (D_max + 1) * (D_max + 2)) * 8;
+            char* w[8] = {};
+            for (int q = 0; q < 8; q++) {
+                if (!sz[q]) continue;
+                if (scratch) {                   // the caller's scratch, laid out in order
+                    w[q] = scratch + off;
+                    off += sz[q];
+                } else {
+                    w[q] = (char*)ctx->raw(names[q] + std::to_string(b), sz[q]);
+                }
             }
+            OmpProb& p = A.p[b - b0];
+            p.n = pb.n; p.S = pb.S; p.F = pb.F; p.ldf = pb.ldf; p.y = pb.y; p.ids = pb.ids;
+            p.TR = (double*)w[0];
+            p.mean = p.TR + (D_max + 1) * (D_max + 2);
+            p.nact = (int32_t*)w[2];
+            p.g = (double*)w[3];
+            p.inv = (double*)w[4];
+            p.r = out_resid ? out_resid + (int64_t)b * ldr : (double*)w[5];
+            p.A = (double*)w[6];
+            p.active = out_active + (int64_t)b * D_max;
+            p.coef = out_coef + (int64_t)b * (D_max + 1);
+            p.rmse = out_rmse + b;
+            p.init = n_init ? init_active + (int64_t)b * init_ld : nullptr;
+            Smax = std::max(Smax, pb.S);
         }
-        double* Z = (double*)w[0];
-        double* yy = (double*)w[1];
-        int32_t* active = out_active + (int64_t)b * D_max;
-        int32_t* nact = (int32_t*)w[2];
-        double* g = (double*)w[3];
-        double* nrm = (double*)w[4];
-        double* r = out_resid ? out_resid + (int64_t)b * ldr : (double*)w[5];
-        double* A = (double*)w[6];
-        double* rss = (double*)w[7];
-        double* coef = out_coef + (int64_t)b * (D_max + 1);
-        // (no timer events in the scratch form: it creates nothing)
-        std::unique_ptr<KTimer> kt(scratch ? nullptr : new KTimer(ctx, st, "omp"));
-        k_omp_prep<<<(unsigned)cdiv(pb.S + 1, 4), 256, 0, st>>>(
-            pb.n, pb.S, pb.F, pb.ldf, pb.y, ldz, Z, yy, nrm, active, D_max,
-            n_init ? init_active + (int64_t)b * init_ld : nullptr, n_init, nact);
-        // the QR's columns in LDS when they fit in 64 KB
-        const size_t qr_bytes = (size_t)(D_max + 2) * pb.n * sizeof(double);
-        const int qr_lds = qr_bytes <= 65536 ? 1 : 0;
-        const size_t dyn = qr_lds ? qr_bytes : 0;
-        k_omp_fit<<<1, 256, dyn, st>>>(pb.n, pb.F, pb.ldf, pb.y, active, nact, A, coef, rss, r, qr_lds,
-                                       pb.S, nullptr, pb.ids, nrm, n_init < D_max ? nullptr : out_rmse + b);
+        k_omp_prep<<<dim3((unsigned)cdiv(Smax, 4), nc), 256, 0, st>>>(A, D_max, n_init);
+        k_omp_fit<<<dim3(1, nc), OMP_T, 0, st>>>(A, D_max, 1, -1, 0, n_init < D_max ? 0 : 1);
         for (int step = n_init; step < D_max; step++) {
-            k_omp_corr<<<(unsigned)cdiv(pb.S, 4), 256, 0, st>>>(pb.n, pb.S, Z, ldz, r, active,
-                                                                nact, g);
-            k_omp_fit<<<1, 256, dyn, st>>>(pb.n, pb.F, pb.ldf, pb.y, active, nact, A, coef, rss, r,
-                                           qr_lds, pb.S, g, pb.ids, nrm,
-                                           step + 1 == D_max ? out_rmse + b : nullptr);
+            k_omp_corr<<<dim3((unsigned)cdiv(Smax, 8), nc), 256, 0, st>>>(A);
+            k_omp_fit<<<dim3(1, nc), OMP_T, 0, st>>>(A, D_max, 0, -1, 1, step + 1 == D_max ? 1 : 0);
         }
         check_launch("omp");
     }
@@ -1784,22 +2085,22 @@ void omp_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int 
 void fit_rows(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int D, const int32_t* rows,
               int64_t rows_ld, double* coef, int64_t coef_ld, double* rmse, double* resid, int64_t ldr,
               hipStream_t st) {
-    int32_t* cnt = ctx->buf<int32_t>("fit_rows_d" + ctx->tag, 1);
-    fill_all(ctx, "fit_rows_fill", {fill_seg(cnt, 4, (uint32_t)D)}, st);
-    for (int b = 0; b < nb; b++) {
-        const discover_l0_problem& pb = probs[b];
-        double* A = ctx->buf<double>("fit_rows_A" + std::to_string(b) + ctx->tag, (size_t)(D + 2) * pb.n);
-        double* rs = ctx->buf<double>("fit_rows_rss" + std::to_string(b) + ctx->tag, 1);
-        double* r = resid ? resid + (int64_t)b * ldr
-                          : ctx->buf<double>("fit_rows_r" + std::to_string(b) + ctx->tag, pb.n);
-        const size_t qr_bytes = (size_t)(D + 2) * pb.n * sizeof(double);
-        const int qr_lds = qr_bytes <= 65536 ? 1 : 0;
-        // the rows are not modified: the kernel only appends when it picks
-        k_omp_fit<<<1, 256, qr_lds ? qr_bytes : 0, st>>>(pb.n, pb.F, pb.ldf, pb.y, (int32_t*)rows + b * rows_ld,
-                                                       cnt, A, coef + b * coef_ld, rs, r, qr_lds, pb.S, nullptr,
-                                                       pb.ids, nullptr, rmse + b);
+    for (int b0 = 0; b0 < nb; b0 += OMP_CHUNK) {
+        const int nc = std::min(OMP_CHUNK, nb - b0);
+        OmpArgs A{};
+        for (int b = b0; b < b0 + nc; b++) {
+            const discover_l0_problem& pb = probs[b];
+            OmpProb& p = A.p[b - b0];
+            p.n = pb.n; p.S = pb.S; p.F = pb.F; p.ldf = pb.ldf; p.y = pb.y; p.ids = pb.ids;
+            p.A = ctx->buf<double>("fit_rows_A" + std::to_string(b) + ctx->tag, (size_t)(D + 2) * pb.n);
+            p.r = resid ? resid + (int64_t)b * ldr : nullptr;
+            p.active = (int32_t*)rows + b * rows_ld;   // not modified: the kernel only appends when it picks
+            p.coef = coef + b * coef_ld;
+            p.rmse = rmse + b;
+        }
+        k_omp_fit<<<dim3(1, nc), OMP_T, 0, st>>>(A, D, 1, D, 0, 1);
+        check_launch("k_omp_fit (rows)");
     }
-    check_launch("k_omp_fit (rows)");
 }
 
 GramOut l0_gram_one(discover_ctx* ctx, const discover_l0_problem& pb, const std::string& name,

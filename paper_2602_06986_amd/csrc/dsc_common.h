@@ -91,6 +91,12 @@ struct discover_ctx {
         pinned[name] = p;
         return p;
     }
+    // One of at least `bytes` bytes, in sizes of powers of two.
+    void* pinned_least(const std::string& name, size_t bytes) {
+        size_t b = 256;
+        while (b < bytes) b *= 2;
+        return pinned_buf(name + ":" + std::to_string(b), b);
+    }
     bool timing = false;
     std::map<std::string, std::pair<int64_t, double>> times;
     struct Pending {

@@ -1043,6 +1043,7 @@ struct RefitArgs {
     double* out_resid;
     int64_t ldr;
     int sub_ld, coef_ld;      // row strides of out_sub and out_coef
+    unsigned long long* host; // pinned host memory for the band and pair counts, or NULL
 };
 
 // Offsets of every problem's band in one merged work list: boff[p] =
@@ -1136,6 +1137,7 @@ __global__ __launch_bounds__(256) void k_rank_models(ctab<RefitArgs> A) {
     const RefitArgs& a = tab(A, blockIdx.x);
     DSC_GLOBAL(a.F); DSC_GLOBAL(a.y); DSC_GLOBAL(a.band); DSC_GLOBAL(a.bcnt); DSC_GLOBAL(a.scratch); DSC_GLOBAL(a.brss); DSC_GLOBAL(a.bcoef); DSC_GLOBAL(a.ids); DSC_GLOBAL(a.yy); DSC_GLOBAL(a.taken); DSC_GLOBAL(a.out_sub); DSC_GLOBAL(a.out_rmse); DSC_GLOBAL(a.out_coef); DSC_GLOBAL(a.chosen); DSC_GLOBAL(a.out_resid);
     const int64_t nb = min((int64_t)*a.bcnt, a.bcap);
+    if (a.host && blockIdx.y == 0 && threadIdx.x < 2) a.host[threadIdx.x] = a.bcnt[threadIdx.x];
     if (nb <= RANK_WAVE) {
         __shared__ int picks[64];
         const int D = a.D;
@@ -1832,6 +1834,8 @@ void l0_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int D
     double* rscratch = ctx->buf<double>("l0_refit_scratch", (size_t)NREFIT * sld);
     int64_t* boff = ctx->buf<int64_t>("l0_boff" + ctx->tag, (size_t)nb + 1);
     bool prefilled = true;                      // the first round's counters: cleared by k_l0_prep
+    // band and pair counts of a waiting call, written by k_rank_models
+    unsigned long long* cnt = devmode ? nullptr : (unsigned long long*)ctx->pinned_least("l0_host", (size_t)nb * 16);
     std::vector<BandCheck> bcl;
     while (!act.empty()) {
         const int na = (int)act.size();
@@ -1873,6 +1877,7 @@ void l0_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int D
             f.out_coef = outs[b].coef; f.coef_ld = outs[b].coef_ld; f.chosen = (int32_t*)(bb + v[5]);
             f.out_resid = outs[b].resid;
             f.ldr = outs[b].ldr;
+            f.host = devmode ? nullptr : cnt + 2 * q;
         }
         if (!prefilled) fill_all(ctx, "l0_fills", fills, st);
         prefilled = false;
@@ -1906,9 +1911,6 @@ void l0_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int D
             if (checks) checks->insert(checks->end(), bcl.begin(), bcl.end());
             break;
         }
-        std::vector<unsigned long long> cnt(2 * (size_t)na);
-        for (int q = 0; q < na; q++)
-            DSC_HIP(hipMemcpyAsync(&cnt[2 * q], ba[q].bcnt, 16, hipMemcpyDeviceToHost, st));
         DSC_HIP(hipStreamSynchronize(st));
         std::vector<int> next;
         for (int q = 0; q < na; q++) {

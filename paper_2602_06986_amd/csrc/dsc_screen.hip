@@ -2624,7 +2624,23 @@ struct SelArgs {
     PoolVals pvs;             // stored values of the first pvs.cap pool entries
     int64_t* vrow;            // per selected rank: address of its stored value row, 0 for none
     const RuleTab* rules;     // selection rules, or NULL
+    const unsigned long long* ctr;   // the problem's counters
+    int64_t* host;            // pinned host memory for the list's outcome (HOST_RES words), or NULL
 };
+
+// What a waiting call reads of a list after its round, written by k_groups
+// into pinned host memory: res[0..4], the largest screening error (bits),
+// the problem's four counters.  (A device-to-host copy of each piece cost
+// 25 to 30 us apiece: 100 us of a call with one list, 450 us with 16.)
+constexpr int HOST_RES = 16;
+
+__device__ __forceinline__ void report_list(const SelArgs& a) {
+    int64_t* h = a.host;
+    if (!h) return;
+    for (int i = 0; i < 5; i++) h[i] = a.res[i];
+    h[5] = (int64_t)*a.maxerr;
+    for (int i = 0; i < 4; i++) h[8 + i] = (int64_t)a.ctr[i];
+}
 
 // grid (blocks, lists) for the streaming kernels, (lists) for the one-block ones
 __global__ __launch_bounds__(256) void k_compact(ctab<SelArgs> A) {
@@ -2732,12 +2748,16 @@ __global__ __launch_bounds__(GRP_THREADS) void k_groups(ctab<SelArgs> A) {
     if (Pd <= GRP_LDS) {
         d_groups_lds(a.pool, a.ps, a.pex, a.order, a.parent, Pd, tail, a.k, a.sel, a.st, a.margin,
                      a.th1d, a.headpos, a.out_ids, a.out_sc, a.res, a.pvs, a.vrow);
-        if (threadIdx.x == 0) a.res[4] = (int64_t)*a.cnt;     // pool size (capacity check)
+        if (threadIdx.x == 0) {
+            a.res[4] = (int64_t)*a.cnt;                       // pool size (capacity check)
+            report_list(a);
+        }
         return;
     }
     for (int64_t i = threadIdx.x; i < a.k; i += GRP_THREADS) a.vrow[i] = 0;   // rows are evaluated
     d_groups(a.pool, a.ps, a.pex, a.order, a.cnt, a.cap, tail, a.k, a.sel, a.st, a.margin, a.th1d, a.parent, a.blk,
              a.repid, a.reppos, a.headpos, a.out_ids, a.out_sc, a.res);
+    if (threadIdx.x == 0) report_list(a);
 }
 
 // Values of the selected features of one list.
@@ -2750,13 +2770,14 @@ struct ValArgs {
     double* out;
     int64_t ldv;
     const int64_t* vrow;      // or NULL: per row, the address of its stored values (0: evaluate)
+    const unsigned long long* ctr;   // the problem's counters: nothing is written for an unusable target
 };
 
 // grid (row blocks of 4, lists)
 __global__ __launch_bounds__(256) void k_values(ctab<ValArgs> A) {
     const ValArgs& a = tab(A, blockIdx.y);
     DSC_GLOBAL(a.ids); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.out);
-    if ((int64_t)blockIdx.x * 4 >= a.m) return;
+    if ((int64_t)blockIdx.x * 4 >= a.m || (a.ctr[0] & 0xFFFFFFFFull)) return;
     d_values(a.ids, a.m, a.ev, a.o, a.n, a.out, a.ldv, a.vrow);
 }
 
@@ -3640,7 +3661,7 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
                          const discover_screen_params& prm, std::vector<Problem>& PS,
                          const std::vector<ListState>& LS, const std::vector<int>& act,
                          const std::vector<double>& margin, const std::vector<ScreenOut>& outs,
-                         hipStream_t st, std::vector<SelArgs>& sa, bool prefilled = false) {
+                         hipStream_t st, std::vector<SelArgs>& sa, int64_t* host, bool prefilled = false) {
     const int nl = (int)act.size();
     const int k = prm.k;
     std::vector<std::vector<size_t>> o;
@@ -3692,6 +3713,8 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         a.out_ids = outs[L.b].ids + (int64_t)L.t * k;
         a.out_sc = outs[L.b].sc + (int64_t)L.t * k;
         a.vrow = vrow + vbase[L.b] + (int64_t)L.t * k;
+        a.ctr = P.ctr;
+        a.host = host ? host + (int64_t)HOST_RES * q : nullptr;
         ra[q] = RadixArgs{a.sc, P.N, L.K, hist, sel, stv, nullptr};
         fills.push_back(fill_seg(misc, 64, 0u));            // pool count, maximum error, st, sel, clusters, prefix
         fills.push_back(fill_seg(hist, 8192 * 4, 0u));
@@ -3931,15 +3954,40 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
             margin[b] = std::max(margin[b], s.guard_band);
         }
     }
+    // values of the selected features; with vrow, rows whose values the
+    // round stored are copied
+    auto write_values = [&](const int64_t* vrow) {
+        std::vector<ValArgs> va;
+        int64_t mmax = 0, voff = 0;
+        for (int b = 0; b < nb; b++) {
+            const Problem& P = PS[b];
+            ValArgs a{};
+            a.ids = outs[b].ids; a.m = (int64_t)P.Tl * prm.k; a.ev = P.ev(); a.o = P.ops();
+            a.n = P.n; a.out = outs[b].vals; a.ldv = outs[b].ldv;
+            a.vrow = vrow ? vrow + voff : nullptr;
+            a.ctr = P.ctr;
+            voff += a.m;
+            va.push_back(a);
+            mmax = std::max(mmax, a.m);
+        }
+        KTimer kt(ctx, st, "values");
+        k_values<<<dim3((unsigned)cdiv(mmax, 4), nb), 256, 0, st>>>(ct(ctx->upload("scr_values", va, st)));
+        check_launch("k_values");
+    };
     std::vector<SelArgs> sa;
     std::vector<ListCheck> lc;
     bool checked_bad = false;
     bool prefilled = true;
     int rounds = 0;
+    int64_t* host = devmode ? nullptr : (int64_t*)ctx->pinned_least("sel_host", LS.size() * HOST_RES * 8);
     while (!act.empty()) {
-        select_round(ctx, probs, prm, PS, LS, act, margin, outs, st, sa, prefilled);
+        select_round(ctx, probs, prm, PS, LS, act, margin, outs, st, sa, host, prefilled);
         prefilled = false;
         rounds++;
+        // after the first round every list's stored pool values are in place
+        // (a later one lays the arena out anew); the values are written
+        // without waiting for its outcome, and again should it not be the last
+        if (rounds == 1 && outs[0].vals) write_values(ctx->buf<int64_t>("scr_vrow" + ctx->tag, 0));
         if (devmode) {                          // results are checked on the device
             for (size_t q = 0; q < act.size(); q++) {
                 const ListState& L = LS[act[q]];
@@ -3951,24 +3999,16 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         }
         // one synchronisation per round: outcome of every active list
         const int nl = (int)act.size();
-        std::vector<int64_t> h_res(8 * (size_t)nl);
-        std::vector<unsigned long long> h_err(nl);
-        for (int q = 0; q < nl; q++) {
-            DSC_HIP(hipMemcpyAsync(&h_res[8 * q], sa[q].res, 64, hipMemcpyDeviceToHost, st));
-            DSC_HIP(hipMemcpyAsync(&h_err[q], sa[q].maxerr, 8, hipMemcpyDeviceToHost, st));
-        }
-        std::vector<unsigned long long> h_ctr(4 * (size_t)nb);
-        if (!checked_bad)
-            for (int b = 0; b < nb; b++)
-                DSC_HIP(hipMemcpyAsync(&h_ctr[4 * b], PS[b].ctr, 32, hipMemcpyDeviceToHost, st));
         DSC_HIP(hipStreamSynchronize(st));
         if (!checked_bad) {
             int64_t need = 0;
-            for (int b = 0; b < nb; b++) {
-                if ((int)(h_ctr[4 * b] & 0xFFFFFFFFull))
+            for (int q = 0; q < nl; q++) {
+                const int b = LS[act[q]].b;
+                const int64_t* c = host + HOST_RES * q + 8;
+                if ((int)(c[0] & 0xFFFFFFFFll))
                     DSC_FAIL(DISCOVER_E_NUMERIC, "problem %d: a target column is constant or not finite", b);
-                stats[b].n_scored = (int64_t)h_ctr[4 * b + 2];
-                const int64_t nf = (int64_t)std::max(h_ctr[4 * b + 1], h_ctr[4 * b + 3]);
+                stats[b].n_scored = c[2];
+                const int64_t nf = std::max(c[1], c[3]);
                 if (nf > PS[b].fix_cap) need = std::max(need, nf);
             }
             // a fix-up list overflowed: candidates past its end were neither
@@ -3981,7 +4021,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         for (int q = 0; q < nl; q++) {
             ListState& L = LS[act[q]];
             discover_screen_stats& s = stats[L.b];
-            const int64_t* r = &h_res[8 * q];
+            const int64_t* r = host + HOST_RES * q;
             const int64_t N = PS[L.b].N;
             if (r[4] > L.cap) {                       // pool overflow: enlarge and redo
                 L.cap = r[4] + 1024;
@@ -3998,7 +4038,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
             }
             s.pool_size += r[4];
             double e;
-            std::memcpy(&e, &h_err[q], 8);
+            std::memcpy(&e, &r[5], 8);
             s.max_lowprec_err = std::max(s.max_lowprec_err, e);
             if (r[1] || L.K >= N) {
                 s.n_selected += r[0];
@@ -4014,7 +4054,6 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         }
         act.swap(next);
     }
-    const auto gen0 = ctx->generation;
     if (!devmode) {
         // size the result arena for a one-round run of every list at the final
         // capacities, as a captured run does
@@ -4023,28 +4062,6 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         for (const ListState& L : LS) { m->K.push_back(L.K); m->cap.push_back(L.cap); m->fcap.push_back(L.fcap); }
         if (ctx->batches.size() >= 256) ctx->batches.clear();
         ctx->batches["sel" + ck] = m;
-    }
-    if (outs[0].vals) {
-        std::vector<ValArgs> va;
-        int64_t mmax = 0;
-        // after one selection round every list's stored pool values are still
-        // in place (a later round lays the arena out anew, a regrown arena
-        // is a new allocation)
-        const int64_t* vrow = rounds == 1 && ctx->generation == gen0 ? ctx->buf<int64_t>("scr_vrow" + ctx->tag, 0) : nullptr;
-        int64_t voff = 0;
-        for (int b = 0; b < nb; b++) {
-            const Problem& P = PS[b];
-            ValArgs a{};
-            a.ids = outs[b].ids; a.m = (int64_t)P.Tl * prm.k; a.ev = P.ev(); a.o = P.ops();
-            a.n = P.n; a.out = outs[b].vals; a.ldv = outs[b].ldv;
-            a.vrow = vrow ? vrow + voff : nullptr;
-            voff += a.m;
-            va.push_back(a);
-            mmax = std::max(mmax, a.m);
-        }
-        KTimer kt(ctx, st, "values");
-        k_values<<<dim3((unsigned)cdiv(mmax, 4), nb), 256, 0, st>>>(ct(ctx->upload("scr_values", va, st)));
-        check_launch("k_values");
     }
     if (devmode) {
         if (dev_stats) {
@@ -4064,7 +4081,10 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         }
         return;
     }
-    DSC_HIP(hipStreamSynchronize(st));
+    if (rounds > 1 && outs[0].vals) {
+        write_values(nullptr);
+        DSC_HIP(hipStreamSynchronize(st));
+    }
     ctx->resolve_timing();
     if (out_stats)
         for (int b = 0; b < nb; b++) out_stats[b] = stats[b];

@@ -148,19 +148,21 @@ typedef struct {
     int32_t score_mode;       /* DISCOVER_SCORE_PER_TARGET or DISCOVER_SCORE_MAX */
     int32_t precision;        /* DISCOVER_FP64, DISCOVER_BF16_GUARD or DISCOVER_FP16_GUARD */
     int32_t dedup;            /* 1: duplicate groups are merged (default); 0: off */
-    int32_t tile_j;           /* FP64 dense pair kernel tile width: 0 = autotuned
-                                 (default), or 1, 2, 4 operand features per wave
-                                 (capped by what the target count allows); the
-                                 scores do not depend on it */
+    int32_t tile_j;           /* FP64 dense pair tiles: 0 = the matrix form, or the
+                                 vector form for data outside its range (default);
+                                 1, 2, 4: the vector form with that many operand
+                                 features per wave (capped by what the target count
+                                 allows).  The selection does not depend on it */
     int32_t lp_pairs;         /* precision forms, pair candidates of rungs <= 2: 0 = the
                                  MFMA form or the FP64 tiles, whichever the autotuner
                                  times faster for the shape (default); 1 = always the
                                  MFMA form; -1 = always FP64.  The selection does not
                                  depend on it */
-    int32_t sched;            /* FP64 dense pair tiles: 0 = autotuned (default), 1 = one
-                                 persistent launch whose blocks take tiles from a device
-                                 work queue (heaviest first), -1 = one block per tile.
-                                 The scores do not depend on it */
+    int32_t sched;            /* FP64 dense pair tiles: 0 = default, 1 = the vector form as
+                                 one persistent launch whose blocks take tiles from a
+                                 device work queue (heaviest first), -1 = the vector form
+                                 with one block per tile.  The selection does not depend
+                                 on it */
 } discover_screen_params;
 
 /* Per-problem counters of one screening call (host memory). */
@@ -177,9 +179,10 @@ typedef struct {
     int64_t n_selected;       /* selected features (summed over lists) */
     double  max_lowprec_err;  /* precision forms: max |s_lowprec - s_fp64| over the pool */
     double  guard_band;       /* precision forms: the guard half-width used */
-    int32_t tile_j;           /* FP64 dense pair kernel: operand features per wave,
-                                 chosen by timing 1/2/4 on the first call for a
-                                 search space (0 when that kernel did not run) */
+    int32_t tile_j;           /* FP64 dense pairs: operand features per wave of the
+                                 vector form, should the data take it (0: no dense
+                                 pairs in FP64); where only sched is given, chosen by
+                                 timing 1/2/4 on the first call for a search space */
     int32_t status;           /* DISCOVER_OK, or (device stats) E_CAPACITY / E_NUMERIC:
                                  this problem's outputs are not valid */
 } discover_screen_stats;

@@ -25,6 +25,7 @@
 #include "dsc_select.h"
 #include "dsc_space.h"
 #include "dsc_r3.h"
+#include "dsc_pairs.h"
 
 #include <memory>
 #include <type_traits>
@@ -142,23 +143,31 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
                                                    double* __restrict__ Vf, double* __restrict__ Rf,
                                                    double* __restrict__ Cf, double* __restrict__ mu,
                                                    double* __restrict__ mur, double* __restrict__ msq,
-                                                   uint8_t* __restrict__ valid) {
+                                                   uint8_t* __restrict__ valid, uint8_t* __restrict__ cls) {
     const int c = c0 + blockIdx.x * 4 + wave_id();
     const int lane = threadIdx.x & 63;
     if (c >= c1) return;
     const double* v = Vf + (int64_t)c * ldn;
-    double s = 0.0, sr = 0.0;
-    int bad = 0;
+    double s = 0.0, sr = 0.0, vmax = 0.0, rmax = 0.0;
+    int bad = 0, zero = 0;
     for (int i = lane; i < n; i += 64) {
         const double x = v[i];
         const double r = 1.0 / x;
         Rf[(int64_t)c * ldn + i] = r;
         bad |= !isfinite(x);
+        zero |= x == 0.0;
         s += x;
         sr += r;
+        vmax = fmax(vmax, fabs(x));
+        rmax = fmax(rmax, fabs(r));
     }
+    // padding to whole chunks of the matrix form
+    for (int i = n + lane; i < ldn; i += 64) Vf[(int64_t)c * ldn + i] = Rf[(int64_t)c * ldn + i] = 0.0;
     s = wave_sum(s);
     sr = wave_sum(sr);
+    vmax = wave_max(vmax);
+    rmax = wave_max(rmax);
+    const int anyzero = __any(zero);
     const int anybad = __any(bad);
     const double m = s / n;
     double q = 0.0;
@@ -192,6 +201,9 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
         mu[c] = m;
         mur[c] = sr / n;
         msq[c] = q / n + m * m;
+        cls[c] = (uint8_t)((q / n < (q / n + m * m) * (1.0 / 2048.0) ? PC_NARROW : 0) |
+                           (vmax >= PC_MIN && vmax <= PC_MAX ? 0 : PC_VAL) |
+                           (rmax >= PC_MIN && rmax <= PC_MAX ? 0 : PC_RCP) | (anyzero ? PC_ZERO : 0));
     }
 }
 
@@ -206,6 +218,8 @@ struct MatArgs {
     const int64_t* raw;
     double *Vf, *Rf, *Cf, *mu, *mur, *msq;
     uint8_t* valid;
+    uint8_t* cls;             // range classes
+    int* route;               // form of the dense pairs
 };
 
 // grid (sample blocks, features of the level, problems)
@@ -222,7 +236,37 @@ __global__ __launch_bounds__(256) void k_mat_stats(ctab<MatArgs> A, int level) {
     DSC_GLOBAL(a.op); DSC_GLOBAL(a.ca); DSC_GLOBAL(a.cb); DSC_GLOBAL(a.Vf); DSC_GLOBAL(a.Rf); DSC_GLOBAL(a.Cf); DSC_GLOBAL(a.mu); DSC_GLOBAL(a.mur); DSC_GLOBAL(a.msq); DSC_GLOBAL(a.valid);
     if (level >= a.nlev) return;
     d_mat_stats(a.n, a.ldn, a.rs[level], a.rs[level + 1], a.op, a.ca, a.cb, a.Vf, a.Rf, a.Cf, a.mu,
-                a.mur, a.msq, a.valid);
+                a.mur, a.msq, a.valid, a.cls);
+}
+
+// Form of each problem's dense pairs (one block per problem): the matrix
+// form when at most 1/256 of them are expected in the exact fix-up through
+// the operands' ranges: two narrow operands (an unshifted product then has
+// a conditioning of about 1000 or more), or one outside the safe range.
+// The fix-up decides about 2 candidates a microsecond at n = 2000, so that
+// share costs less than the matrix form saves; data beyond it (every
+// column with a spread of 1 % of its mean, say) keeps the shifted vector
+// form.  The choice is made on the device: it depends on the data and must
+// hold for a captured call.
+__global__ __launch_bounds__(256) void k_pair_route(ctab<MatArgs> A) {
+    const MatArgs& a = tab(A, blockIdx.x);
+    __shared__ int nn, nr;
+    if (threadIdx.x == 0) nn = nr = 0;
+    __syncthreads();
+    const int M = a.rs[a.nlev];
+    int narrow = 0, range = 0;
+    for (int c = threadIdx.x; c < M; c += 256) {
+        if (!a.valid[c]) continue;
+        narrow += (a.cls[c] & PC_NARROW) != 0;
+        range += (a.cls[c] & (PC_VAL | PC_RCP)) != 0 && !(a.cls[c] & PC_ZERO);
+    }
+    if (narrow) atomicAdd(&nn, narrow);
+    if (range) atomicAdd(&nr, range);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const double m = (double)M;
+        *a.route = (nn / m) * (nn / m) + 2.0 * (nr / m) <= 1.0 / 256.0 ? 1 : 0;
+    }
 }
 
 // Feature-major [M][ldn] -> sample-major [n][ldm] (padding left as is).
@@ -245,6 +289,7 @@ struct TrArgs {
     int n, M, ldn, ldm;
     const double* src[3];
     double* dst[3];
+    const int* route;         // skipped when *route is 1 (no vector-form kernel reads the copies); NULL: never
 };
 
 // grid (sample tiles, feature tiles, 3 x problems)
@@ -252,7 +297,7 @@ __global__ void k_transpose(ctab<TrArgs> A) {
     const TrArgs& a = tab(A, blockIdx.z / 3);
     const int w = blockIdx.z % 3;
     DSC_GLOBAL(a.src[w]); DSC_GLOBAL(a.dst[w]);
-    if ((int)blockIdx.x * 32 >= a.n || (int)blockIdx.y * 32 >= a.M) return;
+    if ((int)blockIdx.x * 32 >= a.n || (int)blockIdx.y * 32 >= a.M || (a.route && *a.route)) return;
     d_transpose(a.n, a.M, a.ldn, a.ldm, a.src[w], a.dst[w]);
 }
 
@@ -327,19 +372,6 @@ __device__ __forceinline__ bool cand_of_id(const EvalCtx& e, int64_t id, Cand& c
     return c.ca >= 0 && c.cb >= 0 && e.valid[c.ca] && e.valid[c.cb];
 }
 
-// One slot of a counter-indexed list for every active lane of the wave
-// (lane order), with a single atomic: for appends made inside divergent
-// code, where the active lanes are exactly those that append.
-__device__ __forceinline__ unsigned long long wave_slot(unsigned long long* ctr) {
-    const uint64_t m = __builtin_amdgcn_ballot_w64(true);
-    const int lane = threadIdx.x & 63;
-    const int leader = __ffsll((long long)m) - 1;
-    unsigned long long base = 0;
-    if (lane == leader) base = atomicAdd(ctr, (unsigned long long)__popcll(m));
-    base = __shfl(base, leader, 64);
-    return base + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull));
-}
-
 // Exact two-pass Pearson of one candidate against T centered targets by one
 // wave.  Returns false when the candidate is not finite or is constant.
 template <int TMAX>
@@ -409,7 +441,8 @@ __device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uin
                                              const double* __restrict__ syy, int64_t N,
                                              double* __restrict__ scores, unsigned* nok,
                                              uint8_t* __restrict__ r2v, double* __restrict__ r2m,
-                                             double* __restrict__ r2q, int64_t off2, int64_t off3);
+                                             double* __restrict__ r2q, int64_t off2, int64_t off3,
+                                             double* __restrict__ fy, int TP);
 
 // One wave per listed candidate (exact two-pass score).
 __device__ __forceinline__ void d_score_list(const ListItem* __restrict__ items, int64_t m,
@@ -420,14 +453,15 @@ __device__ __forceinline__ void d_score_list(const ListItem* __restrict__ items,
                                                     double* __restrict__ scores,
                                                     unsigned long long* __restrict__ nscored,
                                                     uint8_t* __restrict__ r2v, double* __restrict__ r2m,
-                                                    double* __restrict__ r2q, int64_t off2, int64_t off3) {
+                                                    double* __restrict__ r2q, int64_t off2, int64_t off3,
+                                                    double* __restrict__ fy, int TP) {
     // the block's valid candidates are counted in LDS and added once
     __shared__ unsigned nok;
     if (threadIdx.x == 0) nok = 0u;
     __syncthreads();
     const int64_t w = (int64_t)blockIdx.x * 4 + wave_id();
     if (w < m) d_score_item(items[w], o, valid, n, T, mode, Yc, syy, N, scores, &nok, r2v, r2m, r2q,
-                            off2, off3);
+                            off2, off3, fy, TP);
     __syncthreads();
     if (threadIdx.x == 0 && nok) atomicAdd(nscored, (unsigned long long)nok);
 }
@@ -437,13 +471,17 @@ __device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uin
                                              const double* __restrict__ syy, int64_t N,
                                              double* __restrict__ scores, unsigned* nok,
                                              uint8_t* __restrict__ r2v, double* __restrict__ r2m,
-                                             double* __restrict__ r2q, int64_t off2, int64_t off3) {
+                                             double* __restrict__ r2q, int64_t off2, int64_t off3,
+                                             double* __restrict__ fy, int TP) {
     Cand c{it.kind, it.op, it.ca, it.cb, OP_NONE, -1, -1};
     bool ok = valid[c.ca] && (c.kind < 2 || valid[c.cb]);
     if (c.kind == 0) ok = valid[c.ca];
-    double r[DISCOVER_MAX_TARGETS], mean = 0.0, msq = 0.0;
-    ok = ok && wave_exact_r<DISCOVER_MAX_TARGETS>(c, o, n, T, Yc, syy, r, &mean, &msq);
+    double r[DISCOVER_MAX_TARGETS], mean = 0.0, msq = 0.0, sxx = 0.0;
+    ok = ok && wave_exact_r<DISCOVER_MAX_TARGETS>(c, o, n, T, Yc, syy, r, &mean, &msq, nullptr, &sxx);
     if ((threadIdx.x & 63) == 0) {
+        // an operand feature's sums (f - mean) y_t, for the matrix form's sums and differences
+        if (fy && ok && it.kind == 0)
+            for (int t = 0; t < TP; t++) fy[(int64_t)it.ca * TP + t] = t < T ? r[t] * sqrt(sxx) : 0.0;
         if (!ok) {
             for (int t = 0; t < (mode ? 1 : T); t++) scores[(int64_t)t * N + it.id] = __longlong_as_double(-1LL);
             return;
@@ -477,6 +515,8 @@ struct ListArgs {
     uint8_t* r2v;
     double *r2m, *r2q;
     int64_t off2, off3;
+    double* fy;               // or NULL
+    int TP;
 };
 
 // grid (item blocks of 4, problems)
@@ -485,7 +525,7 @@ __global__ __launch_bounds__(256) void k_score_list(ctab<ListArgs> A) {
     DSC_GLOBAL(a.items); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.valid); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.scores); DSC_GLOBAL(a.nscored);
     if ((int64_t)blockIdx.x * 4 >= a.m) return;
     d_score_list(a.items, a.m, a.o, a.valid, a.n, a.T, a.mode, a.Yc, a.syy, a.N, a.scores, a.nscored,
-                 a.r2v, a.r2m, a.r2q, a.off2, a.off3);
+                 a.r2v, a.r2m, a.r2q, a.off2, a.off3, a.fy, a.TP);
 }
 
 // --------------------------------------------------- streamed pair screen
@@ -497,31 +537,6 @@ __global__ __launch_bounds__(256) void k_score_list(ctab<ListArgs> A) {
 // with the unit-norm targets.
 //
 // OPS bits: 0 add, 1 sub, 2 mul, 3 div, 4 rdiv.
-struct PairArgs {
-    const int2* tiles;        // precision form: (jc, ic0) per wave
-    const int32_t* ilist;     // explicit partner lists (list mode) or NULL
-    int64_t n_tiles;
-    int n, ldm, ldn, Mc, jc_end, i_end;   // i_end: end of the partner pool
-    const double *Vs, *Rs, *Cs, *Vf, *Rf, *Cf, *mu, *mur;
-    const uint8_t* valid;
-    const int64_t* mat_raw;
-    const double* Yn;
-    const double* ysum;
-    int T, mode, r;
-    uint32_t opmask;          // runtime enabled subset of OPS (bits as above)
-    SpaceDev sd;
-    int64_t N;
-    double* scores;
-    unsigned long long* nscored;
-    int64_t* fix_ids;         // candidates whose shifted moments are ill-conditioned
-    unsigned long long* fix_cnt;
-    int64_t fix_cap;
-    uint8_t* r2v;             // rung-2 operand statistics for a streamed rung 3 (or NULL)
-    double* r2m;
-    double* r2q;
-    const double* msq;        // mean square of every operand feature
-};
-
 // One block = one tile; its waves take consecutive parts of the samples and
 // their partial moments are summed in LDS in a fixed order (wave 0 + wave 1
 // + ...), so results do not depend on scheduling.  Dense tiles use 4 waves
@@ -544,6 +559,7 @@ __device__ __forceinline__ void pair_tile(ctab<PairArgs> A, const int4 tile) {
     constexpr int PAIR_SPLIT = pair_split<LIST>();
     __shared__ double red[PAIR_SPLIT - 1][SL][64];
     const PairArgs& g = tab(A, tile.x);
+    if (!LIST && g.route && *g.route) return;    // (block-uniform) the matrix form has this problem
     DSC_GLOBAL(g.ilist); DSC_GLOBAL(g.Vs); DSC_GLOBAL(g.Rs); DSC_GLOBAL(g.Cs); DSC_GLOBAL(g.Vf); DSC_GLOBAL(g.Rf); DSC_GLOBAL(g.Cf); DSC_GLOBAL(g.mu); DSC_GLOBAL(g.mur); DSC_GLOBAL(g.valid);
     DSC_GLOBAL(g.mat_raw); DSC_GLOBAL(g.Yn); DSC_GLOBAL(g.ysum); DSC_GLOBAL(g.scores); DSC_GLOBAL(g.nscored); DSC_GLOBAL(g.fix_ids); DSC_GLOBAL(g.fix_cnt); DSC_GLOBAL(g.msq);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar loop
@@ -739,7 +755,13 @@ __device__ __forceinline__ void pair_tile(ctab<PairArgs> A, const int4 tile) {
 template <int OPS, int J, int TP, bool LIST, bool QUEUE>
 __global__ __launch_bounds__(64 * pair_split<LIST>()) void k_screen_pairs(ctab<PairArgs> A,
                                                       const int4* __restrict__ tiles, int64_t n_tiles,
-                                                      unsigned long long* __restrict__ queue) {
+                                                      unsigned long long* __restrict__ queue,
+                                                      const int* __restrict__ routes, int n_routes) {
+    if (routes) {                                // nothing to do when every problem takes the matrix form
+        int vec = 0;
+        for (int b = threadIdx.x; b < n_routes; b += 64 * pair_split<LIST>()) vec |= routes[b] == 0;
+        if (!__syncthreads_or(vec)) return;
+    }
     if (!QUEUE) {
         pair_tile<OPS, J, TP, LIST>(A, tiles[blockIdx.x]);
         return;
@@ -2793,45 +2815,47 @@ static int max_J(int TP) { return TP == 1 ? 4 : TP == 2 ? 2 : 1; }
 
 template <int OPS, int J, int TP>
 static void launch_pairs_t(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list,
-                           unsigned long long* queue, hipStream_t st) {
+                           unsigned long long* queue, const int* routes, int n_routes, hipStream_t st) {
     if (n == 0) return;
     if (list) {
-        k_screen_pairs<OPS, 1, TP, true, false><<<(unsigned)n, 64 * pair_split<true>(), 0, st>>>(A, tiles, n, nullptr);
+        k_screen_pairs<OPS, 1, TP, true, false><<<(unsigned)n, 64 * pair_split<true>(), 0, st>>>(A, tiles, n, nullptr, nullptr, 0);
     } else if (queue) {                        // persistent: 8 blocks per CU at most
         const unsigned g = (unsigned)std::min<int64_t>(n, 8 * 256);
-        k_screen_pairs<OPS, J, TP, false, true><<<g, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, queue);
+        k_screen_pairs<OPS, J, TP, false, true><<<g, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, queue, routes, n_routes);
     } else {                                   // one block per tile
-        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr);
+        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr, routes, n_routes);
     }
 }
 
 template <int OPS>
 static void launch_pairs_ops(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
-                             int J, unsigned long long* q, hipStream_t st) {
+                             int J, unsigned long long* q, const int* routes, int n_routes, hipStream_t st) {
     switch (TP) {
     case 1:
-        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, st);
-        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, st);
-        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, st);
+        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, routes, n_routes, st);
+        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, routes, n_routes, st);
+        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, routes, n_routes, st);
         break;
     case 2:
-        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, st);
-        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, st);
+        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, routes, n_routes, st);
+        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, routes, n_routes, st);
         break;
-    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, st); break;
-    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, st); break;
-    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, st); break;
+    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, routes, n_routes, st); break;
+    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, routes, n_routes, st); break;
+    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, routes, n_routes, st); break;
     }
 }
 
 // queue: a zeroed device counter to run the dense tiles as one persistent
-// launch over a work queue, or NULL for one block per tile.
+// launch over a work queue, or NULL for one block per tile.  routes: the
+// forms of the call's problems, where the matrix form may have taken some.
 static void launch_pairs(int OPS, ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
-                         int J, hipStream_t st, unsigned long long* queue = nullptr) {
+                         int J, hipStream_t st, unsigned long long* queue = nullptr, const int* routes = nullptr,
+                         int n_routes = 0) {
     switch (OPS) {
-    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, st); break;
-    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, st); break;
-    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, st); break;
+    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
+    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
+    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
     default: DSC_FAIL(DISCOVER_E_UNSUPPORTED, "operator class %d", OPS);
     }
 }
@@ -2889,7 +2913,7 @@ struct Plan {
     ListItem* items = nullptr;
     int64_t n_items = 0;
     std::vector<int2> dtilesJ[3];             // dense (jc0, ic0) tiles for J = 1, 2, 4
-    int tuned_J = 0;                          // 0: not tuned yet (single-problem calls)
+    std::vector<int2> mmtiles[2];             // matrix form: (i0, j0) of 16 x 16 and of big tiles
     uint32_t dense_ops = 0;
     int dense_cls = 0;
     int2* ptiles = nullptr;                   // (j, i0) tiles of one j for the precision form
@@ -2988,6 +3012,14 @@ static std::shared_ptr<Plan> get_plan(discover_ctx* ctx, const discover_problem&
                 for (int32_t i0 = 0; i0 < ilim; i0 += 64) tiles.push_back(make_int2(j, i0));
             }
         }
+        for (int big = 0; big < 2; big++) {
+            int rows, cols;
+            pairs_mm_tile(P->TP, big ? 2 : 0, rows, cols);
+            for (int32_t j0 = jc0; j0 < jc1; j0 += cols) {
+                const int32_t ilim = std::min<int32_t>(i_end, std::min<int32_t>(j0 + cols, jc1) - 1);
+                for (int32_t i0 = 0; i0 < ilim; i0 += rows) P->mmtiles[big].push_back(make_int2(i0, j0));
+            }
+        }
         std::vector<int2> pt;
         for (int32_t j = jc0; j < jc1; j++) {
             const int32_t ilim = std::min<int32_t>(i_end, j);
@@ -3056,6 +3088,9 @@ struct Problem {
     unsigned long long* queues = nullptr;   // the call's work-queue counters (zeroed by its fills)
     double *Vf, *Rf, *Cf, *Vs, *Rs, *Cs, *mu, *mur, *msq, *Yc, *Yn, *syy, *ysum, *scores;
     uint8_t* valid;
+    uint8_t* cls;                             // operand range classes
+    int* route;                               // form of the dense pairs
+    double* fy;                               // operand features' sums with the targets
     unsigned long long* ctr;                  // [0] bad target (int), [1] fix count, [2] scored, [3] rung-3 fix count
     int64_t *fix_ids, *fix_ids3;
     uint8_t* r2v = nullptr;                   // rung-2 operand statistics (streamed rung 3)
@@ -3125,6 +3160,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         for (int k = 0; k < 3; k++) u.push_back(ao.add(Mc * ldn * 8));          // Vf Rf Cf
         for (int k = 0; k < 3; k++) u.push_back(ao.add(Mc * 8));                // mu mur msq
         u.push_back(ao.add(Mc));                                               // valid
+        u.push_back(ao.add(Mc));                                               // cls
         for (int k = 0; k < 3; k++) u.push_back(ao.add(P.pairs ? n * ldm * 8 : 8));  // Vs Rs Cs
         v.push_back(ar.add((size_t)P.T * ldn * 8));                            // Yc
         v.push_back(ar.add((size_t)P.TP * ldn * 8));                           // Yn
@@ -3142,7 +3178,9 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         const R3Plan* r3 = pl.r3.get();
         v.push_back(ar.add(r3 ? r3_bmat_bytes(*r3, P.TP, P.n) : 8));              // rung-3 operands
         v.push_back(ar.add(r3 ? r3_pstat_bytes(*r3, P.TP) : 8));                  // partner ranges, sums
+        v.push_back(ar.add(P.pairs ? Mc * P.TP * 8 : 8));                         // fy
     }
+    const size_t routes = ao.add((size_t)nb * sizeof(int));
     char* base = (char*)ctx->raw("scr_arena", ar.total);
     char* obase = (char*)ctx->raw("scr_ops" + ctx->ops_tag, ao.total);
     // counters stay apart from the shared arena: a captured run checks the
@@ -3159,6 +3197,8 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         P.Vf = (double*)ato(); P.Rf = (double*)ato(); P.Cf = (double*)ato();
         P.mu = (double*)ato(); P.mur = (double*)ato(); P.msq = (double*)ato();
         P.valid = (uint8_t*)ato();
+        P.cls = (uint8_t*)ato();
+        P.route = (int*)(obase + routes) + b;
         P.Vs = (double*)ato(); P.Rs = (double*)ato(); P.Cs = (double*)ato();
         P.Yc = (double*)at(); P.Yn = (double*)at(); P.syy = (double*)at(); P.ysum = (double*)at();
         P.scores = (double*)at();
@@ -3170,6 +3210,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         P.ylp = at();
         P.r3b = (double*)at();
         P.r3p = (double*)at();
+        P.fy = (double*)at();
     }
 }
 
@@ -3251,26 +3292,23 @@ static int log2_bucket(int64_t v) {
 }
 
 // Autotuned choice of the precision form for one problem's dense pair
-// tiles: the MFMA kernel and the FP64 tiles (one operand feature per wave)
-// are each timed once for this shape, their counter bumps undone, and the
+// tiles: the BF16/FP16 kernel and the FP64 kernels are each timed once for this shape, their counter bumps undone, and the
 // faster is remembered.  (Both give the same selection: the FP64 scores lie
 // within the guard band of their own exact values.)
 static bool tune_precision(discover_ctx* ctx, const std::string& key, Problem& P,
-                           const std::function<void()>& run_lp, ctab<PairArgs> dA, int b, hipStream_t st) {
+                           const std::function<void()>& run_lp, const std::function<void()>& run_f64,
+                           hipStream_t st) {
     auto it = ctx->tuned.find(key);
     if (it != ctx->tuned.end()) return it->second != 0;
     if (ctx->capturing) DSC_FAIL(DISCOVER_E_CAPACITY, "precision-form tuning during graph capture");
     unsigned long long* sv = ctx->buf<unsigned long long>("tune_lp_ctr", 4);
     DSC_HIP(hipMemcpyAsync(sv, P.ctr, 32, hipMemcpyDeviceToDevice, st));
-    std::vector<int4> tiles;
-    for (const int2& t : P.plan->dtilesJ[0]) tiles.push_back(make_int4(b, t.x, t.y, 0));
-    const int4* dt = ctx->upload("tune_lp_tiles", tiles, st);
     float ms[2] = {0.f, 0.f};
     for (int v = 0; v < 2; v++) {
         hipEvent_t e0 = ctx->event(), e1 = ctx->event();
         DSC_HIP(hipEventRecord(e0, st));
         if (v == 0) run_lp();
-        else launch_pairs(P.plan->dense_cls, dA, dt, (int64_t)tiles.size(), false, P.TP, 1, st);
+        else run_f64();
         DSC_HIP(hipEventRecord(e1, st));
         DSC_HIP(hipMemcpyAsync(P.ctr, sv, 32, hipMemcpyDeviceToDevice, st));
         DSC_HIP(hipEventSynchronize(e1));
@@ -3328,6 +3366,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.op = pl.mat_op; a.ca = pl.mat_a; a.cb = pl.mat_b; a.raw = pl.mat_raw;
         a.Vf = P.Vf; a.Rf = P.Rf; a.Cf = P.Cf; a.mu = P.mu; a.mur = P.mur; a.msq = P.msq;
         a.valid = P.valid;
+        a.cls = P.cls;
+        a.route = P.route;
         nlev = std::max(nlev, a.nlev);
         nmax = std::max(nmax, P.n);
         for (int r = 0; r < a.nlev; r++) wmax[r] = std::max(wmax[r], a.rs[r + 1] - a.rs[r]);
@@ -3353,6 +3393,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             k_mat_values<<<dim3((unsigned)cdiv(nmax, 256), (unsigned)wmax[r], nb), 256, 0, st>>>(dma, r);
             k_mat_stats<<<dim3((unsigned)cdiv(wmax[r], 4), nb), 256, 0, st>>>(dma, r);
         }
+        if (std::any_of(PS.begin(), PS.end(), [](const Problem& P) { return P.pairs && P.plan->dense_ops; }))
+            k_pair_route<<<nb, 256, 0, st>>>(dma);
         check_launch("k_mat");
     }
     // 4. exact list: operand features and unary candidates of the streamed rung
@@ -3370,6 +3412,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.r2v = P.r2v; a.r2m = P.r2m; a.r2q = P.r2q;
         a.off2 = pl.sp.stream3 ? sd.off[2] : 0;
         a.off3 = pl.sp.stream3 ? sd.off[3] : 0;
+        a.fy = P.pairs ? P.fy : nullptr; a.TP = P.TP;
         mmax = std::max(mmax, a.m);
     }
     {
@@ -3384,7 +3427,9 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
     for (int b = 0; b < nb; b++) {
         const Problem& P = PS[b];
         if (!P.pairs) continue;
-        tr.push_back(TrArgs{P.n, P.Mc, P.ldn, P.ldm, {P.Vf, P.Rf, P.Cf}, {P.Vs, P.Rs, P.Cs}});
+        // (list tiles, the precision form and forced vector tiles always read the copies)
+        const bool mm_only = prm.precision == DISCOVER_FP64 && prm.tile_j == 0 && prm.sched == 0 && !P.plan->list_ops;
+        tr.push_back(TrArgs{P.n, P.Mc, P.ldn, P.ldm, {P.Vf, P.Rf, P.Cf}, {P.Vs, P.Rs, P.Cs}, mm_only ? P.route : nullptr});
         tn = std::max(tn, P.n);
         tm = std::max(tm, P.Mc);
     }
@@ -3393,7 +3438,10 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                       dim3(32, 8), 0, st>>>(ct(ctx->upload("scr_tr", tr, st)));
         check_launch("k_transpose");
     }
-    // 6. pair kernels
+    // 6. pair kernels.  The vector form's tile width and schedule can be
+    // forced; else each problem takes the matrix form or, where its data
+    // need it, the vector form (decided on the device).
+    const bool forced = prm.tile_j > 0 || prm.sched != 0;
     std::vector<PairArgs> pa(nb);
     for (int b = 0; b < nb; b++) {
         const Problem& P = PS[b];
@@ -3414,55 +3462,54 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.r2v = P.r2v; a.r2m = P.r2m; a.r2q = P.r2q; a.msq = P.msq;
         a.ilist = pl.ilist;
         a.opmask = pl.dense_ops;
+        a.cls = P.cls; a.fy = P.fy;
+        a.route = forced ? nullptr : P.route;
     }
     const ctab<PairArgs> dpa = ct(ctx->upload("scr_pairs", pa, st));
     const std::vector<int> order = by_weight(PS);
-    // 6a. precision form: per problem, MFMA screening with FP64 guard-band
-    // rescore, where the autotuner found it faster than the FP64 tiles for
-    // this problem's shape (either gives the same selection)
-    std::vector<char> lp_used(nb, 0);
-    for (int b = 0; b < nb; b++) {
-        Problem& P = PS[b];
-        const Plan& pl = *P.plan;
-        if (!P.pairs || !pl.dense_ops || prm.precision == DISCOVER_FP64) continue;
-        const bool fp16 = prm.precision == DISCOVER_FP16_GUARD;
-        dim3 gy((unsigned)cdiv(P.ldl, 256), 16);
-        if (fp16) k_targets_lp<true><<<gy, 256, 0, st>>>(P.n, P.T, P.ldn, P.ldl, P.Yn, (_Float16*)P.ylp);
-        else k_targets_lp<false><<<gy, 256, 0, st>>>(P.n, P.T, P.ldn, P.ldl, P.Yn, (__bf16*)P.ylp);
-        PairArgs a = pa[b];
-        a.tiles = pl.ptiles; a.n_tiles = pl.n_ptiles;
-        const double dl = lowprec_delta(prm.precision, P.n);
-        auto run_lp = [&] {
-            if (fp16) launch_lp<true>(pl.dense_cls, a, P.ylp, P.ldl, dl, st);
-            else launch_lp<false>(pl.dense_cls, a, P.ylp, P.ldl, dl, st);
-            check_launch("k_screen_lp");
-        };
-        if (prm.lp_pairs < 0 ||
-            (prm.lp_pairs == 0 &&
-             !tune_precision(ctx, "lp" + pl.key + std::to_string(P.n) + (fp16 ? "h" : "b"), P, run_lp, dpa, b, st)))
-            continue;                            // FP64 tiles below
-        lp_used[b] = 1;
-        KTimer kt(ctx, st, "screen_lp");
-        run_lp();
-    }
-    // 6b. FP64 dense tiles, merged per (operator class, padded targets)
-    std::map<std::pair<int, int>, std::vector<int>> groups;
-    for (int b : order) {
-        const Problem& P = PS[b];
-        if (P.pairs && P.plan->dense_ops && !lp_used[b])
-            groups[{P.plan->dense_cls, P.TP}].push_back(b);
-    }
-    int gi = 0;
+    // FP64 dense tiles of problems mem, all of one (operator class, padded
+    // targets): gi numbers the group's tables and work queue
     unsigned long long* const gqueues = PS.empty() ? nullptr : PS[0].queues;
-    for (auto& g : groups) {
-        const int cls = g.first.first, TP = g.first.second;
-        const std::vector<int>& mem = g.second;
+    auto run_dense = [&](const std::vector<int>& mem, int cls, int TP, const std::string& gi, unsigned long long* queue) {
         int J = 1;
         bool useq = prm.sched > 0;
         if (prm.tile_j > 0) {
             while (J * 2 <= std::min(prm.tile_j, max_J(TP))) J *= 2;
         }
-        if (prm.tile_j == 0 || prm.sched == 0) {
+        if (!forced) {
+            // matrix form.  Tile shape by the work items (tiles x operator sets)
+            // and the products of one 16 x 16 tile (16-sample chunks x (2 +
+            // targets)): large tiles once they give every SIMD a wave, else one
+            // 16 x 16 tile per wave, or per block where tiles are few or long.
+            // Measured us for a tile per block, per wave, large: 234 items of 378
+            // products 46, 75, 125; 513 of 342 91, 133, 135; 513 of 1250 165, 343,
+            // 539; 1785 of 630 217, 233, 294; but 513 of 57 42, 31, 73; 1053 of 78
+            // 70, 44, 50; 1785 of 128 126, 68, 111; 6834 of 375 (1 target) 577, 466,
+            // 426; of 1250 (8 targets) 1434, 1415, 1380; of 500 and 750 (2 and 4
+            // targets, whose larger tiles lost) 571, 517, 533 and 757, 727, 779.
+            int64_t nbig = 0, nsml = 0, prod = 0;
+            for (int b : mem) {
+                const int64_t t = 3 * (int64_t)PS[b].plan->mmtiles[0].size();
+                nbig += 3 * (int64_t)PS[b].plan->mmtiles[1].size();
+                nsml += t;
+                prod += t * cdiv(PS[b].n, 16) * (TP + 2);
+            }
+            const int shape = (TP == 1 || TP == 8) && nbig >= 1024 ? 2
+                              : nsml <= 256 || (nsml < 2048 && prod >= 256 * nsml) ? 0 : 1;
+            std::vector<int4> work;
+            for (int b : mem) {
+                const uint32_t ops = PS[b].plan->dense_ops;
+                for (const int2& t : PS[b].plan->mmtiles[shape == 2 ? 1 : 0])
+                    for (int sel = 0; sel < 3; sel++)
+                        if (ops & (sel == 0 ? 7u : sel == 1 ? 8u : 16u)) work.push_back(make_int4(b, t.x, t.y, sel));
+            }
+            launch_pairs_mm(dpa, ctx->upload("scr_mmwork" + gi, work, st), (int64_t)work.size(), TP, shape, st);
+            // what the matrix form leaves runs as one persistent launch, two
+            // operand features per wave for one target (the width that timing
+            // chose for tables of 16 to 20 features)
+            J = std::min(2, max_J(TP));
+            useq = true;
+        } else if (prm.tile_j == 0 || prm.sched == 0) {
             // shape class: operator class, padded targets, buckets of the
             // largest n and of the tile count
             int nmax = 0;
@@ -3484,11 +3531,55 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             PS[b].tile_j = J;
             for (const int2& t : PS[b].plan->dtilesJ[jx]) tiles.push_back(make_int4(b, t.x, t.y, 0));
         }
-        const int4* dt = ctx->upload("scr_dtiles" + std::to_string(gi), tiles, st);
-        KTimer kt(ctx, st, "screen_pairs");
-        if (useq && gi >= MAX_QUEUES) useq = false;   // (more groups than queue counters)
-        launch_pairs(cls, dpa, dt, (int64_t)tiles.size(), false, TP, J, st, useq ? gqueues + gi : nullptr);
+        const int4* dt = ctx->upload("scr_dtiles" + gi, tiles, st);
+        launch_pairs(cls, dpa, dt, (int64_t)tiles.size(), false, TP, J, st, useq ? queue : nullptr,
+                     forced ? nullptr : PS[0].route, nb);
         check_launch("k_screen_pairs");
+    };
+    // 6a. precision form: per problem, BF16/FP16 screening with FP64 guard-band
+    // rescore, where the autotuner found it faster than the FP64 kernels for
+    // this problem's shape (either gives the same selection)
+    std::vector<char> lp_used(nb, 0);
+    for (int b = 0; b < nb; b++) {
+        Problem& P = PS[b];
+        const Plan& pl = *P.plan;
+        if (!P.pairs || !pl.dense_ops || prm.precision == DISCOVER_FP64) continue;
+        const bool fp16 = prm.precision == DISCOVER_FP16_GUARD;
+        dim3 gy((unsigned)cdiv(P.ldl, 256), 16);
+        if (fp16) k_targets_lp<true><<<gy, 256, 0, st>>>(P.n, P.T, P.ldn, P.ldl, P.Yn, (_Float16*)P.ylp);
+        else k_targets_lp<false><<<gy, 256, 0, st>>>(P.n, P.T, P.ldn, P.ldl, P.Yn, (__bf16*)P.ylp);
+        PairArgs a = pa[b];
+        a.tiles = pl.ptiles; a.n_tiles = pl.n_ptiles;
+        const double dl = lowprec_delta(prm.precision, P.n);
+        auto run_lp = [&] {
+            if (fp16) launch_lp<true>(pl.dense_cls, a, P.ylp, P.ldl, dl, st);
+            else launch_lp<false>(pl.dense_cls, a, P.ylp, P.ldl, dl, st);
+            check_launch("k_screen_lp");
+        };
+        auto run_f64 = [&] {
+            fill_all(ctx, "tune_qfill", {fill_seg(ctx->buf<unsigned long long>("tune_queue", 1), 8, 0u)}, st);
+            run_dense({b}, pl.dense_cls, P.TP, "_tune", ctx->buf<unsigned long long>("tune_queue", 1));
+        };
+        if (prm.lp_pairs < 0 ||
+            (prm.lp_pairs == 0 &&
+             !tune_precision(ctx, "lp" + pl.key + std::to_string(P.n) + (fp16 ? "h" : "b"), P, run_lp, run_f64, st)))
+            continue;                            // FP64 tiles below
+        lp_used[b] = 1;
+        KTimer kt(ctx, st, "screen_lp");
+        run_lp();
+    }
+    // 6b. FP64 dense tiles, merged per (operator class, padded targets)
+    std::map<std::pair<int, int>, std::vector<int>> groups;
+    for (int b : order) {
+        const Problem& P = PS[b];
+        if (P.pairs && P.plan->dense_ops && !lp_used[b])
+            groups[{P.plan->dense_cls, P.TP}].push_back(b);
+    }
+    int gi = 0;
+    for (auto& g : groups) {
+        KTimer kt(ctx, st, "screen_pairs");
+        // (past the queue counters, one block per tile)
+        run_dense(g.second, g.first.first, g.first.second, std::to_string(gi), gi < MAX_QUEUES ? gqueues + gi : nullptr);
         gi++;
     }
     // 6c. same-unit add/sub partner lists (FP64 in every form), merged per TP
@@ -3501,7 +3592,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
     if (!lgroups.empty()) {
         // list-mode arguments differ from the dense ones only in the operator mask
         std::vector<PairArgs> pl2 = pa;
-        for (int b = 0; b < nb; b++) pl2[b].opmask = PS[b].plan->list_ops;
+        for (int b = 0; b < nb; b++) { pl2[b].opmask = PS[b].plan->list_ops; pl2[b].route = nullptr; }
         const ctab<PairArgs> dpl = ct(ctx->upload("scr_pairs_list", pl2, st));
         int li = 0;
         for (auto& g : lgroups) {
@@ -3945,7 +4036,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         s.n_raw = P.plan->sp.n_raw();
         s.n_unit_valid = P.plan->sp.n_unit_valid;
         s.tile_j = P.tile_j;
-        margin[b] = 4.0 * P.n * EPS64 * KAPPA_MAX;
+        margin[b] = 4.0 * P.n * EPS64 * PAIR_KAPPA;
         if (prm.precision != DISCOVER_FP64) {
             s.guard_band = lowprec_margin(prm.precision, P.n);
             // rung 3 in BF16 carries its FP32 moments' error as well

@@ -9,7 +9,7 @@
 // The matrix form (k_pairs_mm) computes them on the FP64 matrix cores; the
 // vector form (k_screen_pairs) shifts every candidate by an estimate of its
 // mean, and takes the data that unshifted moments cannot carry (see
-// PAIR_KAPPA and k_pair_route).
+// pair_kappa and k_pair_route).
 #pragma once
 
 #include "dsc_common.h"
@@ -41,28 +41,36 @@ struct PairArgs {
     double* r2q;
     const double* msq;        // mean square of every operand feature
     const uint8_t* cls;       // range class of every operand feature (PC_*)
+    const short2* ex;         // binary exponents of max |f| and max |1/f|
+    double kappa;             // conditioning the matrix form's moments are trusted to (pair_kappa)
     const double* fy;         // [Mc][TP] sum of (f - mean) y_t
-    const int* route;         // the problem's dense pairs: 1 matrix form, 0 vector form; NULL: vector form
+    const int* route;         // form of the problem's dense pairs: 1 matrix, 0 vector
 };
 
 // Conditioning S2 / (S2 - S1^2 / n) up to which the matrix form's unshifted
-// moments are trusted.  The score's error stays below 4 n eps kappa, which
-// the selection margin covers (7e-9 at n = 2000); a candidate beyond goes
-// to the exact fix-up.  64, the vector form's limit, would send products of
-// features with a relative spread below 13 % there.
-constexpr double PAIR_KAPPA = 4096.0;
+// moments are trusted: a score's error stays below 4 n eps kappa, and this
+// keeps it within PAIR_MARGIN, which the selection margin covers (some
+// hundred more pool entries among 10^8 candidates).  A candidate beyond
+// goes to the exact fix-up.  At n = 2000 that is 2e6, the product of two
+// columns with a spread of 0.1 % of their means; 64, the vector form's
+// limit, would send products of columns with one of 13 % there.
+constexpr double PAIR_MARGIN = 2e-6;
+inline double pair_kappa(int n) { return PAIR_MARGIN / (4.0 * n * 1.1102230246251565e-16); }
 
 // Range classes of an operand feature f.
 enum : uint8_t {
-    PC_NARROW = 1,            // variance below 1/2048 of the mean square
-    PC_VAL = 2,               // max |f| outside [1e-40, 1e50]
-    PC_RCP = 4,               // max |1/f| outside it
+    PC_NARROW = 1,            // variance below 4 / pair_kappa of the mean square
+    PC_RCP = 4,               // 1/f overflows though f has no zero
     PC_ZERO = 8               // f has a zero
 };
-constexpr double PC_MAX = 1e50, PC_MIN = 1e-40;
-// With the classes' limits a product's square sum has lost at most n 2e-208
-// to subnormal squares, nothing of one above this.
-constexpr double PC_S2MIN = 1e-180;
+// The matrix form scales every feature by a power of two so that its
+// largest value lies in [1, 2) (correlations do not change), so squares
+// neither overflow nor vanish; a product whose largest possible value lies
+// outside [2^-480, 2^498] goes to the exact fix-up, which knows whether its
+// values and their squares are finite, and so does one whose scaled square
+// sum is small enough for subnormal squares to matter.
+constexpr int PC_EMIN = -480, PC_EMAX = 498;
+constexpr double PC_S2MIN = 1e-250;
 
 // Samples padded to whole 16-sample chunks are read: Vf, Rf and Yn hold
 // zeros from n to ldn (a multiple of 64).

@@ -41,7 +41,7 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
     if (*g.route == 0) return;
     DSC_GLOBAL(g.Vf); DSC_GLOBAL(g.Rf); DSC_GLOBAL(g.mu); DSC_GLOBAL(g.valid); DSC_GLOBAL(g.mat_raw); DSC_GLOBAL(g.Yn);
     DSC_GLOBAL(g.ysum); DSC_GLOBAL(g.scores); DSC_GLOBAL(g.nscored); DSC_GLOBAL(g.fix_ids); DSC_GLOBAL(g.fix_cnt);
-    DSC_GLOBAL(g.msq); DSC_GLOBAL(g.cls); DSC_GLOBAL(g.fy);
+    DSC_GLOBAL(g.msq); DSC_GLOBAL(g.cls); DSC_GLOBAL(g.ex); DSC_GLOBAL(g.fy);
     const int lane = threadIdx.x & 63, r16 = lane & 15, kq = lane >> 4;
     const int i0 = wk.y, j0 = wk.z, sel = wk.w;
     const int64_t ldn = g.ldn;
@@ -49,10 +49,19 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
     const double* __restrict__ Vb = sel == 1 ? g.Rf : g.Vf;
     const double* pa[RT];
     const double* pb[CT];
+    double sa[RT], sb[CT];                       // the features' scales
 #pragma unroll
-    for (int u = 0; u < RT; u++) pa[u] = Va + (int64_t)min(i0 + 16 * u + r16, g.Mc - 1) * ldn + 4 * kq;
+    for (int u = 0; u < RT; u++) {
+        const int i = min(i0 + 16 * u + r16, g.Mc - 1);
+        pa[u] = Va + (int64_t)i * ldn + 4 * kq;
+        sa[u] = ldexp(1.0, -(sel == 2 ? g.ex[i].y : g.ex[i].x));
+    }
 #pragma unroll
-    for (int v = 0; v < CT; v++) pb[v] = Vb + (int64_t)min(j0 + 16 * v + r16, g.Mc - 1) * ldn + 4 * kq;
+    for (int v = 0; v < CT; v++) {
+        const int j = min(j0 + 16 * v + r16, g.Mc - 1);
+        pb[v] = Vb + (int64_t)j * ldn + 4 * kq;
+        sb[v] = ldexp(1.0, -(sel == 1 ? g.ex[j].y : g.ex[j].x));
+    }
     const double* __restrict__ py = g.Yn + 4 * kq;
     pr_v4d acc[RT][CT][TK];
 #pragma unroll
@@ -67,9 +76,9 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
     const int last = 16 * (KS == 1 ? nch : (nch * (wv + 1)) / KS) - 16;
     pr_v4d a[RT], b[CT];
 #pragma unroll
-    for (int u = 0; u < RT; u++) a[u] = *(const pr_v4d*)(pa[u] + first);
+    for (int u = 0; u < RT; u++) a[u] = *(const pr_v4d*)(pa[u] + first) * sa[u];
 #pragma unroll
-    for (int v = 0; v < CT; v++) b[v] = *(const pr_v4d*)(pb[v] + first);
+    for (int v = 0; v < CT; v++) b[v] = *(const pr_v4d*)(pb[v] + first) * sb[v];
     for (int s = first; s <= last; s += 16) {
         const int sn = min(s + 16, last);
         pr_v4d an[RT], bn[CT];
@@ -104,12 +113,12 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
 #pragma unroll
         for (int u = 0; u < RT; u++) {
             asm("" : "+v"(an[u].x), "+v"(an[u].y), "+v"(an[u].z), "+v"(an[u].w));
-            a[u] = an[u];
+            a[u] = an[u] * sa[u];
         }
 #pragma unroll
         for (int v = 0; v < CT; v++) {
             asm("" : "+v"(bn[v].x), "+v"(bn[v].y), "+v"(bn[v].z), "+v"(bn[v].w));
-            b[v] = bn[v];
+            b[v] = bn[v] * sb[v];
         }
     }
 
@@ -120,7 +129,7 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
     auto emit = [&](int op, int64_t ri, int64_t rj, double varn, double kappa, bool sure, double mean, double msq,
                     const double (&num)[TP]) {
         const int64_t id = pair_id(g.sd, g.r, op, ri, rj);
-        if (!sure || !(kappa <= PAIR_KAPPA)) {
+        if (!sure || !(kappa <= g.kappa)) {
             const unsigned long long slot = wave_slot(g.fix_cnt);
             if ((int64_t)slot < g.fix_cap) g.fix_ids[slot] = id;
             return;
@@ -152,35 +161,39 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
         if (!(j < g.jc_end && i < g.i_end && i < j) || !g.valid[i] || !g.valid[j]) return;
         const int64_t ri = g.mat_raw[i], rj = g.mat_raw[j];
         const uint8_t ci = g.cls[i], cj = g.cls[j];
+        const short2 xi = g.ex[i], xj = g.ex[j];
+        const int ei = sel == 2 ? xi.y : xi.x, ej = sel == 1 ? xj.y : xj.x;
+        const double back = ldexp(1.0, ei + ej);     // undoes the scales
         const double S1 = m[TP], S2 = m[TP + 1];
         double num[TP];
         // the product of this operator set; a zero divisor makes every
         // quotient non-finite (the slot stays invalid)
         const int op = sel == 0 ? OP_MUL : sel == 1 ? OP_DIV : OP_RDIV;
-        const bool zero = sel == 1 ? (cj & PC_ZERO) != 0 : sel == 2 ? (ci & PC_ZERO) != 0 : false;
-        if (((g.opmask >> (op - OP_ADD)) & 1u) && !zero) {
-            const uint8_t bad = sel == 0 ? (ci | cj) & PC_VAL
-                                : sel == 1 ? (ci & PC_VAL) | (cj & PC_RCP) : (ci & PC_RCP) | (cj & PC_VAL);
+        const uint8_t cd = sel == 0 ? 0 : sel == 1 ? cj : ci;
+        if (((g.opmask >> (op - OP_ADD)) & 1u) && !(cd & PC_ZERO)) {
+            const bool sure = !(cd & PC_RCP) && ei + ej >= PC_EMIN && ei + ej <= PC_EMAX && S2 >= PC_S2MIN;
             const double varn = S2 - S1 * (S1 / nn);
             const double kappa = varn > 0.0 ? S2 / varn : INFINITY;
+            const double mean = S1 / nn * back;
 #pragma unroll
             for (int t = 0; t < TP; t++) num[t] = m[t] - S1 * ys[t];
-            emit(op, ri, rj, varn, kappa, !bad && S2 >= PC_S2MIN, S1 / nn, S2 / nn, num);
+            emit(op, ri, rj, varn, kappa, sure, mean, S2 / nn * back * back, num);
         }
         if (sel != 0 || !(g.opmask & 3u)) return;
-        const double ma = g.mu[i], mb = g.mu[j];
+        const double ma = g.mu[i], mb = g.mu[j], M1 = S1 * back;
         const double B = nn * (g.msq[i] + g.msq[j]);
+        const bool sure = max(xi.x, xj.x) <= PC_EMAX && max(xi.x, xj.x) >= PC_EMIN;
 #pragma unroll
         for (int o = 0; o < 2; o++) {
             if (!((g.opmask >> o) & 1u)) continue;
             const double sg = o == 0 ? 1.0 : -1.0;
             const double mean = fma(sg, mb, ma);
-            const double q = fma(2.0 * sg, S1, B);
+            const double q = fma(2.0 * sg, M1, B);
             const double varn = q - nn * mean * mean;
             const double kappa = varn > 0.0 ? B / varn : INFINITY;
 #pragma unroll
             for (int t = 0; t < TP; t++) num[t] = fma(sg, g.fy[(int64_t)j * TP + t], g.fy[(int64_t)i * TP + t]);
-            emit(OP_ADD + o, ri, rj, varn, kappa, !((ci | cj) & PC_VAL) && B >= PC_S2MIN, mean, q / nn, num);
+            emit(OP_ADD + o, ri, rj, varn, kappa, sure, mean, q / nn, num);
         }
     };
     if constexpr (KS > 1) {

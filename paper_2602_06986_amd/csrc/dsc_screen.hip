@@ -143,7 +143,8 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
                                                    double* __restrict__ Vf, double* __restrict__ Rf,
                                                    double* __restrict__ Cf, double* __restrict__ mu,
                                                    double* __restrict__ mur, double* __restrict__ msq,
-                                                   uint8_t* __restrict__ valid, uint8_t* __restrict__ cls) {
+                                                   uint8_t* __restrict__ valid, uint8_t* __restrict__ cls,
+                                                   short2* __restrict__ ex, double narrow) {
     const int c = c0 + blockIdx.x * 4 + wave_id();
     const int lane = threadIdx.x & 63;
     if (c >= c1) return;
@@ -201,9 +202,10 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
         mu[c] = m;
         mur[c] = sr / n;
         msq[c] = q / n + m * m;
-        cls[c] = (uint8_t)((q / n < (q / n + m * m) * (1.0 / 2048.0) ? PC_NARROW : 0) |
-                           (vmax >= PC_MIN && vmax <= PC_MAX ? 0 : PC_VAL) |
-                           (rmax >= PC_MIN && rmax <= PC_MAX ? 0 : PC_RCP) | (anyzero ? PC_ZERO : 0));
+        cls[c] = (uint8_t)((q / n < (q / n + m * m) * narrow ? PC_NARROW : 0) |
+                           (isfinite(rmax) || anyzero ? 0 : PC_RCP) | (anyzero ? PC_ZERO : 0));
+        auto exponent = [](double v) { return (short)(v > 0.0 && v < INFINITY ? ilogb(v) : 0); };
+        ex[c] = make_short2(exponent(vmax), exponent(rmax));
     }
 }
 
@@ -219,6 +221,8 @@ struct MatArgs {
     double *Vf, *Rf, *Cf, *mu, *mur, *msq;
     uint8_t* valid;
     uint8_t* cls;             // range classes
+    short2* ex;               // binary exponents of max |f| and max |1/f|
+    double narrow;            // share of the mean square below which a variance is narrow
     int* route;               // form of the dense pairs
 };
 
@@ -236,18 +240,18 @@ __global__ __launch_bounds__(256) void k_mat_stats(ctab<MatArgs> A, int level) {
     DSC_GLOBAL(a.op); DSC_GLOBAL(a.ca); DSC_GLOBAL(a.cb); DSC_GLOBAL(a.Vf); DSC_GLOBAL(a.Rf); DSC_GLOBAL(a.Cf); DSC_GLOBAL(a.mu); DSC_GLOBAL(a.mur); DSC_GLOBAL(a.msq); DSC_GLOBAL(a.valid);
     if (level >= a.nlev) return;
     d_mat_stats(a.n, a.ldn, a.rs[level], a.rs[level + 1], a.op, a.ca, a.cb, a.Vf, a.Rf, a.Cf, a.mu,
-                a.mur, a.msq, a.valid, a.cls);
+                a.mur, a.msq, a.valid, a.cls, a.ex, a.narrow);
 }
 
 // Form of each problem's dense pairs (one block per problem): the matrix
 // form when at most 1/256 of them are expected in the exact fix-up through
-// the operands' ranges: two narrow operands (an unshifted product then has
-// a conditioning of about 1000 or more), or one outside the safe range.
-// The fix-up decides about 2 candidates a microsecond at n = 2000, so that
+// the operands' ranges: two narrow operands, whose unshifted product may
+// pass the matrix form's conditioning, or one whose reciprocal overflows.
+// The fix-up decides a few candidates a microsecond at n = 2000, so that
 // share costs less than the matrix form saves; data beyond it (every
-// column with a spread of 1 % of its mean, say) keeps the shifted vector
-// form.  The choice is made on the device: it depends on the data and must
-// hold for a captured call.
+// column within 0.05 % of its mean, say) keeps the shifted vector form.
+// The choice is made on the device: it depends on the data and must hold
+// for a captured call.
 __global__ __launch_bounds__(256) void k_pair_route(ctab<MatArgs> A) {
     const MatArgs& a = tab(A, blockIdx.x);
     __shared__ int nn, nr;
@@ -258,14 +262,14 @@ __global__ __launch_bounds__(256) void k_pair_route(ctab<MatArgs> A) {
     for (int c = threadIdx.x; c < M; c += 256) {
         if (!a.valid[c]) continue;
         narrow += (a.cls[c] & PC_NARROW) != 0;
-        range += (a.cls[c] & (PC_VAL | PC_RCP)) != 0 && !(a.cls[c] & PC_ZERO);
+        range += (a.cls[c] & PC_RCP) != 0;
     }
     if (narrow) atomicAdd(&nn, narrow);
     if (range) atomicAdd(&nr, range);
     __syncthreads();
     if (threadIdx.x == 0) {
         const double m = (double)M;
-        *a.route = (nn / m) * (nn / m) + 2.0 * (nr / m) <= 1.0 / 256.0 ? 1 : 0;
+        *a.route = (nn / m) * (nn / m) + nr / m <= 1.0 / 256.0 ? 1 : 0;
     }
 }
 
@@ -559,7 +563,6 @@ __device__ __forceinline__ void pair_tile(ctab<PairArgs> A, const int4 tile) {
     constexpr int PAIR_SPLIT = pair_split<LIST>();
     __shared__ double red[PAIR_SPLIT - 1][SL][64];
     const PairArgs& g = tab(A, tile.x);
-    if (!LIST && g.route && *g.route) return;    // (block-uniform) the matrix form has this problem
     DSC_GLOBAL(g.ilist); DSC_GLOBAL(g.Vs); DSC_GLOBAL(g.Rs); DSC_GLOBAL(g.Cs); DSC_GLOBAL(g.Vf); DSC_GLOBAL(g.Rf); DSC_GLOBAL(g.Cf); DSC_GLOBAL(g.mu); DSC_GLOBAL(g.mur); DSC_GLOBAL(g.valid);
     DSC_GLOBAL(g.mat_raw); DSC_GLOBAL(g.Yn); DSC_GLOBAL(g.ysum); DSC_GLOBAL(g.scores); DSC_GLOBAL(g.nscored); DSC_GLOBAL(g.fix_ids); DSC_GLOBAL(g.fix_cnt); DSC_GLOBAL(g.msq);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform: scalar loop
@@ -756,24 +759,27 @@ template <int OPS, int J, int TP, bool LIST, bool QUEUE>
 __global__ __launch_bounds__(64 * pair_split<LIST>()) void k_screen_pairs(ctab<PairArgs> A,
                                                       const int4* __restrict__ tiles, int64_t n_tiles,
                                                       unsigned long long* __restrict__ queue,
-                                                      const int* __restrict__ routes, int n_routes) {
-    if (routes) {                                // nothing to do when every problem takes the matrix form
-        int vec = 0;
-        for (int b = threadIdx.x; b < n_routes; b += 64 * pair_split<LIST>()) vec |= routes[b] == 0;
-        if (!__syncthreads_or(vec)) return;
-    }
+                                                      const int* __restrict__ routes, int one) {
     if (!QUEUE) {
+        // a problem that the matrix form has (routes: one flag per problem;
+        // one: a single problem, its flag read without waiting for the tile).
+        // Ahead of any barrier, past which the operands' scalar loads become
+        // vector loads and the kernel takes twice as long
+        if (!LIST && routes && routes[one ? 0 : tiles[blockIdx.x].x]) return;
         pair_tile<OPS, J, TP, LIST>(A, tiles[blockIdx.x]);
         return;
     }
+    // the next tile is fetched while the current one is screened
     __shared__ int64_t s_t;
-    for (;;) {
-        if (threadIdx.x == 0) s_t = (int64_t)atomicAdd(queue, 1ull);
-        __syncthreads();
-        const int64_t t = s_t;
-        __syncthreads();
-        if (t >= n_tiles) break;
+    if (threadIdx.x == 0) s_t = (int64_t)atomicAdd(queue, 1ull);
+    __syncthreads();
+    for (int64_t t = s_t; t < n_tiles; t = s_t) {
+        __syncthreads();                         // s_t read
+        int64_t next = 0;
+        if (threadIdx.x == 0) next = (int64_t)atomicAdd(queue, 1ull);
         pair_tile<OPS, J, TP, LIST>(A, tiles[t]);
+        if (threadIdx.x == 0) s_t = next;
+        __syncthreads();
     }
 }
 
@@ -2815,47 +2821,47 @@ static int max_J(int TP) { return TP == 1 ? 4 : TP == 2 ? 2 : 1; }
 
 template <int OPS, int J, int TP>
 static void launch_pairs_t(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list,
-                           unsigned long long* queue, const int* routes, int n_routes, hipStream_t st) {
+                           unsigned long long* queue, const int* routes, int one, hipStream_t st) {
     if (n == 0) return;
     if (list) {
         k_screen_pairs<OPS, 1, TP, true, false><<<(unsigned)n, 64 * pair_split<true>(), 0, st>>>(A, tiles, n, nullptr, nullptr, 0);
     } else if (queue) {                        // persistent: 8 blocks per CU at most
         const unsigned g = (unsigned)std::min<int64_t>(n, 8 * 256);
-        k_screen_pairs<OPS, J, TP, false, true><<<g, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, queue, routes, n_routes);
+        k_screen_pairs<OPS, J, TP, false, true><<<g, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, queue, nullptr, 0);
     } else {                                   // one block per tile
-        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr, routes, n_routes);
+        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr, routes, one);
     }
 }
 
 template <int OPS>
 static void launch_pairs_ops(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
-                             int J, unsigned long long* q, const int* routes, int n_routes, hipStream_t st) {
+                             int J, unsigned long long* q, const int* routes, int one, hipStream_t st) {
     switch (TP) {
     case 1:
-        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, routes, n_routes, st);
-        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, routes, n_routes, st);
-        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, routes, n_routes, st);
+        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, routes, one, st);
+        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, routes, one, st);
+        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, routes, one, st);
         break;
     case 2:
-        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, routes, n_routes, st);
-        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, routes, n_routes, st);
+        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, routes, one, st);
+        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, routes, one, st);
         break;
-    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, routes, n_routes, st); break;
-    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, routes, n_routes, st); break;
-    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, routes, n_routes, st); break;
+    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, routes, one, st); break;
+    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, routes, one, st); break;
+    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, routes, one, st); break;
     }
 }
 
 // queue: a zeroed device counter to run the dense tiles as one persistent
 // launch over a work queue, or NULL for one block per tile.  routes: the
-// forms of the call's problems, where the matrix form may have taken some.
+// problems' forms, where the matrix form may have taken some (no queue).
 static void launch_pairs(int OPS, ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
-                         int J, hipStream_t st, unsigned long long* queue = nullptr, const int* routes = nullptr,
-                         int n_routes = 0) {
+                         int J, hipStream_t st, unsigned long long* queue = nullptr,
+                         const int* routes = nullptr, int one = 0) {
     switch (OPS) {
-    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
-    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
-    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, routes, n_routes, st); break;
+    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
+    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
+    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
     default: DSC_FAIL(DISCOVER_E_UNSUPPORTED, "operator class %d", OPS);
     }
 }
@@ -3089,6 +3095,7 @@ struct Problem {
     double *Vf, *Rf, *Cf, *Vs, *Rs, *Cs, *mu, *mur, *msq, *Yc, *Yn, *syy, *ysum, *scores;
     uint8_t* valid;
     uint8_t* cls;                             // operand range classes
+    short2* ex;                               // operand exponents
     int* route;                               // form of the dense pairs
     double* fy;                               // operand features' sums with the targets
     unsigned long long* ctr;                  // [0] bad target (int), [1] fix count, [2] scored, [3] rung-3 fix count
@@ -3161,6 +3168,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         for (int k = 0; k < 3; k++) u.push_back(ao.add(Mc * 8));                // mu mur msq
         u.push_back(ao.add(Mc));                                               // valid
         u.push_back(ao.add(Mc));                                               // cls
+        u.push_back(ao.add(Mc * 4));                                           // ex
         for (int k = 0; k < 3; k++) u.push_back(ao.add(P.pairs ? n * ldm * 8 : 8));  // Vs Rs Cs
         v.push_back(ar.add((size_t)P.T * ldn * 8));                            // Yc
         v.push_back(ar.add((size_t)P.TP * ldn * 8));                           // Yn
@@ -3198,6 +3206,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         P.mu = (double*)ato(); P.mur = (double*)ato(); P.msq = (double*)ato();
         P.valid = (uint8_t*)ato();
         P.cls = (uint8_t*)ato();
+        P.ex = (short2*)ato();
         P.route = (int*)(obase + routes) + b;
         P.Vs = (double*)ato(); P.Rs = (double*)ato(); P.Cs = (double*)ato();
         P.Yc = (double*)at(); P.Yn = (double*)at(); P.syy = (double*)at(); P.ysum = (double*)at();
@@ -3367,6 +3376,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.Vf = P.Vf; a.Rf = P.Rf; a.Cf = P.Cf; a.mu = P.mu; a.mur = P.mur; a.msq = P.msq;
         a.valid = P.valid;
         a.cls = P.cls;
+        a.ex = P.ex;
+        a.narrow = 4.0 / pair_kappa(P.n);
         a.route = P.route;
         nlev = std::max(nlev, a.nlev);
         nmax = std::max(nmax, P.n);
@@ -3462,8 +3473,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.r2v = P.r2v; a.r2m = P.r2m; a.r2q = P.r2q; a.msq = P.msq;
         a.ilist = pl.ilist;
         a.opmask = pl.dense_ops;
-        a.cls = P.cls; a.fy = P.fy;
-        a.route = forced ? nullptr : P.route;
+        a.cls = P.cls; a.ex = P.ex; a.kappa = pair_kappa(P.n); a.fy = P.fy;
+        a.route = P.route;
     }
     const ctab<PairArgs> dpa = ct(ctx->upload("scr_pairs", pa, st));
     const std::vector<int> order = by_weight(PS);
@@ -3504,11 +3515,9 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                         if (ops & (sel == 0 ? 7u : sel == 1 ? 8u : 16u)) work.push_back(make_int4(b, t.x, t.y, sel));
             }
             launch_pairs_mm(dpa, ctx->upload("scr_mmwork" + gi, work, st), (int64_t)work.size(), TP, shape, st);
-            // what the matrix form leaves runs as one persistent launch, two
-            // operand features per wave for one target (the width that timing
-            // chose for tables of 16 to 20 features)
+            // what the matrix form leaves: two operand features per wave for one
+            // target (the width that timing chose for tables of 16 to 20 features)
             J = std::min(2, max_J(TP));
-            useq = true;
         } else if (prm.tile_j == 0 || prm.sched == 0) {
             // shape class: operator class, padded targets, buckets of the
             // largest n and of the tile count
@@ -3533,7 +3542,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         }
         const int4* dt = ctx->upload("scr_dtiles" + gi, tiles, st);
         launch_pairs(cls, dpa, dt, (int64_t)tiles.size(), false, TP, J, st, useq ? queue : nullptr,
-                     forced ? nullptr : PS[0].route, nb);
+                     forced ? nullptr : PS[0].route, nb == 1);
         check_launch("k_screen_pairs");
     };
     // 6a. precision form: per problem, BF16/FP16 screening with FP64 guard-band
@@ -3592,7 +3601,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
     if (!lgroups.empty()) {
         // list-mode arguments differ from the dense ones only in the operator mask
         std::vector<PairArgs> pl2 = pa;
-        for (int b = 0; b < nb; b++) { pl2[b].opmask = PS[b].plan->list_ops; pl2[b].route = nullptr; }
+        for (int b = 0; b < nb; b++) pl2[b].opmask = PS[b].plan->list_ops;
         const ctab<PairArgs> dpl = ct(ctx->upload("scr_pairs_list", pl2, st));
         int li = 0;
         for (auto& g : lgroups) {
@@ -4036,7 +4045,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         s.n_raw = P.plan->sp.n_raw();
         s.n_unit_valid = P.plan->sp.n_unit_valid;
         s.tile_j = P.tile_j;
-        margin[b] = 4.0 * P.n * EPS64 * PAIR_KAPPA;
+        margin[b] = std::max(4.0 * P.n * EPS64 * KAPPA_MAX, P.pairs && P.plan->dense_ops ? PAIR_MARGIN : 0.0);
         if (prm.precision != DISCOVER_FP64) {
             s.guard_band = lowprec_margin(prm.precision, P.n);
             // rung 3 in BF16 carries its FP32 moments' error as well

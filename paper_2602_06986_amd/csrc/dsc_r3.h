@@ -59,7 +59,7 @@ inline double r3_moment_err(int n) { return 3.0 * ((n + 50) * 5.9604644775390625
 // add/sub tiles' (FP64 layout) at r3_as_offset bytes.
 inline size_t r3_as_offset(const R3Plan& p, int TP, int n) {
     const size_t f64 = (size_t)p.n_ctiles * (TP + 2) * r3_quads(n) * 64 * 8;
-    const size_t lp = (size_t)p.n_ctiles * r3_chunks(n) * 512 * (4 + TP * 2);
+    const size_t lp = (size_t)p.n_ctiles * r3_chunks(n) * 1024 * (4 + TP);
     return (std::max(f64, lp) + 255) & ~(size_t)255;
 }
 // The add/sub tiles' operands end with the targets in the same lane order

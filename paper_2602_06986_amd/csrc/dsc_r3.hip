@@ -105,6 +105,38 @@ __device__ __forceinline__ void r3_rows(const double* Vf, const double* Rf, int6
     }
 }
 
+// How a row's values come from its two operand rows in the precision form:
+// kinds with loops of their own, so that a loop holds no branch.
+enum { RK_PROD, RK_ADD, RK_SUB, RK_OTHER };
+
+// Kind and operand rows (row i of a table b: Vf or Rf, the same for the rows
+// of a tile) for the values g, or (recip) for 1/g: where g is a product or
+// quotient, 1/g is one of the operands' reciprocals and values, which are
+// stored; elsewhere the reciprocal is taken of g.
+__device__ __forceinline__ int r3_rows_lp(const double* Vf, const double* Rf, int k, int l, int op2, bool recip,
+                                          const double*& b1, const double*& b2, int& i1, int& i2) {
+    i1 = op2 < OP_ADD ? l : op2 == OP_RDIV ? l : k;
+    i2 = op2 < OP_ADD ? l : op2 == OP_RDIV ? k : l;
+    b1 = op2 == OP_INV ? Rf : Vf;
+    b2 = op2 == OP_INV || op2 == OP_DIV || op2 == OP_RDIV ? Rf : Vf;
+    switch (op2) {
+    case OP_MUL:
+    case OP_SQ:
+        if (recip) b1 = b2 = Rf;
+        return RK_PROD;
+    case OP_DIV:
+    case OP_RDIV:
+        if (recip) {
+            b1 = Rf;
+            b2 = Vf;
+        }
+        return RK_PROD;
+    case OP_ADD: return RK_ADD;
+    case OP_SUB: return RK_SUB;
+    default: return RK_OTHER;
+    }
+}
+
 __device__ __forceinline__ double r3_regen1(const double* __restrict__ Vf, const double* __restrict__ Rf,
                                             int64_t ldn, int k, int l, int op2, int s) {
     const double b = Vf[(int64_t)l * ldn + s];
@@ -498,9 +530,9 @@ __global__ __launch_bounds__(256) void k_r3_mm(R3mArgs g) {
 }
 
 // ------------------------------------------------------------ precision form
-// BF16 numerators, split-BF16 moments.  Per 32-sample chunk a lane
-// regenerates 8 consecutive samples of its row (rows 16 rung-2 features, as
-// above) in FP64 and rounds them to FP32 (a) and BF16 (a_h).  Every product
+// BF16 numerators, split-BF16 moments.  Per 32-sample chunk a wave
+// regenerates its 16 rows (rung-2 features, as above) in FP64 and rounds
+// them to FP32 (a) and BF16 (a_h).  Every product
 // is a v_mfma_f32_16x16x32_bf16 (lane l supplies row l%16 at samples
 // 8(l/16)..+7 of the chunk and column l%16 at the same samples, and
 // receives D[4(l/16)+e][l%16] in slot e): the T numerators against x y_t
@@ -534,6 +566,7 @@ constexpr double LP_BIG2 = 1e16;        // |f|, |g|, |x| below this: n f^2 stays
 constexpr double LP_SMALL2 = 1e-10;     // ||f|| above this: FP32 subnormals are negligible
 constexpr double LP_KAPPA = 1.21;
 
+typedef double r3_v2d __attribute__((ext_vector_type(2)));
 typedef __attribute__((ext_vector_type(8))) __bf16 r3_bf16x8;
 typedef __attribute__((ext_vector_type(4))) float r3_f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned r3_u32x4;
@@ -560,20 +593,20 @@ __device__ __forceinline__ void r3_split(float v0, float v1, unsigned& hi, unsig
 }
 
 // Right-hand operands of the precision form, per column tile c and 32-sample
-// chunk ch (512 entries each, lane-major: entry 8 l + e belongs to column
-// l%16 at sample 32 ch + 8 (l/16) + e): b32[(c NC + ch) 512 + 8 l + e] =
-// FP32(x), blp[((c TP + t) NC + ch) 512 + 8 l + e] = BF16(x y_t).
+// chunk ch 4 + TP blocks of 512 BF16, lane-major (entry 8 l + e belongs to
+// column l%16 at sample 32 ch + 8(l/16) + e): the splits x_h, x_l, (x^2)_h,
+// (x^2)_l of FP32(x) and its square, then x y_t rounded, t < TP.  This is
+// the layout the screen's blocks copy into LDS.
 __global__ __launch_bounds__(256) void k_r3_bmat_lp(int n, int64_t ldn, int TP, int NC, int nct,
                                                     const int32_t* __restrict__ coldesc,
                                                     const double* __restrict__ Vf, const double* __restrict__ Rf,
-                                                    const double* __restrict__ Yn, float* __restrict__ b32,
-                                                    __bf16* __restrict__ blp) {
-    const int64_t per = (int64_t)NC * 512;
-    const int64_t total = (int64_t)nct * (1 + TP) * per;
+                                                    const double* __restrict__ Yn, __bf16* __restrict__ blp) {
+    const int TB = 4 + TP;
+    const int64_t total = (int64_t)nct * NC * 512;
     for (int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x; f < total; f += (int64_t)gridDim.x * 256) {
-        const int64_t r = f % per, ck = f / per;
-        const int c = (int)(ck / (1 + TP)), v = (int)(ck % (1 + TP));
-        const int ch = (int)(r / 512), w = (int)(r % 512);
+        const int w = (int)(f % 512);
+        const int64_t cc = f / 512;
+        const int ch = (int)(cc % NC), c = (int)(cc / NC);
         const int l = w >> 3, e = w & 7;
         const int j = l & 15, s = 32 * ch + 8 * (l >> 4) + e;
         const int32_t d = coldesc[c * 16 + j];
@@ -582,20 +615,23 @@ __global__ __launch_bounds__(256) void k_r3_bmat_lp(int n, int64_t ldn, int TP, 
             const int p = d & 0xFFFF, kind = d >> 16;
             x = kind == 3 ? 1.0 : kind == 1 ? Rf[(int64_t)p * ldn + s] : Vf[(int64_t)p * ldn + s];
         }
-        if (v == 0) {
-            b32[(int64_t)c * per + r] = (float)x;
-        } else {
-            const int t = v - 1;
-            const double yv = (s < n) ? Yn[(int64_t)t * ldn + s] : 0.0;
-            const unsigned pk = r3_bf16_pack((float)(x * yv), 0.0f);
-            blp[((int64_t)c * TP + t) * per + r] = __builtin_bit_cast(__bf16, (unsigned short)(pk & 0xFFFFu));
+        unsigned short* o = (unsigned short*)blp + cc * TB * 512 + w;
+        const float x32 = (float)x;
+        unsigned hi, lo;
+        r3_split(x32, x32 * x32, hi, lo);
+        o[0] = (unsigned short)hi;
+        o[512] = (unsigned short)lo;
+        o[1024] = (unsigned short)(hi >> 16);
+        o[1536] = (unsigned short)(lo >> 16);
+        for (int t = 0; t < TP; t++) {
+            const double yv = s < n ? Yn[(int64_t)t * ldn + s] : 0.0;
+            o[(4 + t) * 512] = (unsigned short)r3_bf16_pack((float)(x * yv), 0.0f);
         }
     }
 }
 
 struct R3lpArgs {
     R3mArgs m;
-    const float* b32;
     const __bf16* blp;
     const double* r2q;        // mean square of each rung-2 feature (by id - off[2])
     int NC;
@@ -609,18 +645,27 @@ typedef float r3_f32x2 __attribute__((ext_vector_type(2)));
 // A block's four waves take four row tiles (16 rung-2 features each)
 // against CT column tiles (16 partner columns each): a wave regenerates its
 // row values once per chunk and issues the products of every column tile
-// from them.  The column tiles' operands of a chunk (x, x^2 and the TP
-// products x y_t: 4 + TP KB per tile) are staged once per block in LDS,
-// double-buffered, and each wave reads them there (16 contiguous bytes per
-// lane per read).  The next chunk's operands are loaded into registers (a
-// share of 8 + 16 TP/4 bytes per tile per thread) and the next chunk's row
-// operands per wave while the current chunk's products are issued.
+// from them.  The column tiles' operands of a chunk (4 + TP KB per tile) are
+// copied from memory into LDS once per block, double-buffered, and each wave
+// reads them there (16 contiguous bytes per lane per read).
+// The row operands are loaded with the samples across the lanes (16 lanes
+// read 256 contiguous bytes of a row), combined and rounded to FP32 in that
+// order and turned to the products' order (a lane's 8 samples of one row)
+// through 2 KB of the wave's own LDS: loaded in the products' order, each
+// load would touch 64 cache lines, and their look-ups in the first-level
+// cache took three quarters of the kernel's cycles.
+// Bound: LDS (the blocks' reads and copies, two thirds of the cycles), then
+// the second-level cache.  Measured with 24 partners, 8 targets and 2000
+// samples, all rung-2 features: mul / rdiv tiles 7.6 ms (operands through
+// registers, two column tiles per wave and rows in the products' order:
+// 11.9; three tiles and copies to LDS, rows in the products' order: 8.4),
+// div tiles 5.5 ms (7.1; 6.5).
 // HK: the launch's column tiles multiply 1/g (div), else g (mul, rdiv);
 // the two kinds are separate launches, so that neither carries the
 // other's per-sample work.  Column tiles past the launch's range (the last
 // group may be short) repeat its last tile and store nothing.
 template <int TP, int CT, bool HK>
-__global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs a) {
+__global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     const R3mArgs& g = a.m;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -629,14 +674,16 @@ __global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs
     const int cb = lb / g.n_gblk;
     const int ctb = a.ct0 + cb * CT;                     // first column tile of the block
     const int64_t tile0 = (int64_t)(lb - cb * g.n_gblk) * 4 + r3_wave();
-    // a wave without a row tile still stages its share and meets every barrier
+    // a wave without a row tile still stages its share and meets every
+    // barrier (and forms products that are not stored)
     const bool active = tile0 * 16 < g.n_grec;
     constexpr bool hk = HK;
     bool rok;
     int64_t j2;
-    int oo;
-    const double* p1;
-    const double* p2;
+    int oo, rkind;
+    const double* b1;
+    const double* b2;
+    unsigned ri1[4], ri2[4];
     {
         const int64_t t16 = min(tile0, (g.n_grec >> 4) - 1) * 16;
         const int64_t rec = tile0 * 16 + r16;
@@ -647,11 +694,17 @@ __global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs
         rok = rec < g.n_grec && k != -2;
         j2 = rok ? r3_j2(g.sd, g.mat_raw, k, l, op2) : 0;
         rok = rok && g.r2v[j2 - g.sd.off[2]];
-        r3_rows(g.Vf, g.Rf, g.ldn, op2 < OP_ADD ? -1 : (rok ? k : 0), rok ? l : 0, op2, p1, p2);
+        int i1, i2;
+        rkind = r3_rows_lp(g.Vf, g.Rf, rok ? k : 0, rok ? l : 0, op2, hk, b1, b2, i1, i2);
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            ri1[h] = (unsigned)__shfl(i1, 4 * h + kq, 64);
+            ri2[h] = (unsigned)__shfl(i2, 4 * h + kq, 64);
+        }
     }
     r3_f32x4 s1[CT], s2[CT], c1[CT], c2[CT];              // moments: a_h x_h and cross terms
     r3_f32x4 pa[CT][TP];
-    double hmx = 0.0;                                    // div tiles: max |1/g| of the lane's samples
+    float hmx = 0.0f;                                    // div tiles: max |1/g| of the lane's samples
 #pragma unroll
     for (int c = 0; c < CT; c++) {
         s1[c] = r3_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -661,158 +714,207 @@ __global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs
 #pragma unroll
         for (int t = 0; t < TP; t++) pa[c][t] = r3_f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    // LDS buffer: per column tile the splits x_h, x_l, (x^2)_h, (x^2)_l
-    // (512 BF16 each), then the TP x y_t blocks (512 BF16 each), all
-    // lane-major as in b32 and blp
+    // LDS buffer: per column tile the 4 + TP blocks of a chunk, copied
+    // straight from memory (1 KB per wave instruction)
     constexpr int TB = (4 + TP) * 1024;
     constexpr int BUF = CT * TB;
     __shared__ __attribute__((aligned(16))) char smem[2 * BUF];
-    constexpr int NPB = (TP * 64 + 255) / 256;           // 16-byte pieces of x y_t per thread and tile
-    const float* gx[CT];
-    const __bf16* gb[CT];
-#pragma unroll
-    for (int c = 0; c < CT; c++) {
-        const int ctc = min(ctb + c, a.ct1 - 1);
-        gx[c] = a.b32 + (int64_t)ctc * a.NC * 512;
-        gb[c] = a.blp + (int64_t)ctc * TP * a.NC * 512;
-    }
-    r3_f32x2 sx[CT];
-    r3_u32x4 sb[CT][NPB];
-    // piece i of thread tid: q = tid + 256 i (with fewer than 256 pieces,
-    // threads share pieces and write the same bytes); every thread loads and
-    // stores on every chunk, so that no load sits behind a branch
-    auto piece = [&](int i) { return TP * 64 >= 256 ? tid + 256 * i : (tid & (TP * 64 - 1)); };
-    auto stage_load = [&](int ch) {
+    __shared__ __attribute__((aligned(16))) char trow[4 * 2048];
+    const int wv = r3_wave();
+    auto stage = [&](int ch, int buf) {
 #pragma unroll
         for (int c = 0; c < CT; c++) {
-            sx[c] = *(const r3_f32x2*)(gx[c] + (int64_t)ch * 512 + 2 * tid);
+            const int ctc = min(ctb + c, a.ct1 - 1);
+            const char* src = (const char*)a.blp + ((int64_t)ctc * a.NC + ch) * TB + wv * 1024;
+            __asm__("" : "+s"(src));                     // (uniform base, lane offset: no address registers)
+            char* dst = smem + buf * BUF + c * TB;
 #pragma unroll
-            for (int i = 0; i < NPB; i++) {
-                const int q = piece(i);
-                sb[c][i] = *(const r3_u32x4*)(gb[c] + ((int64_t)(q >> 6) * a.NC + ch) * 512 + (q & 63) * 8);
+            for (int v = 0; v < (4 + TP + 3) / 4; v++) {
+                const int b = 4 * v + wv;
+                if ((4 + TP) % 4 == 0 || b < 4 + TP)
+                    __builtin_amdgcn_global_load_lds(
+                        (const __attribute__((address_space(1))) void*)(src + v * 4096 + (unsigned)(lane * 16)),
+                        (__attribute__((address_space(3))) void*)(dst + b * 1024), 16, 0, 0);
             }
         }
     };
-    auto stage_store = [&](int buf) {
-#pragma unroll
-        for (int c = 0; c < CT; c++) {
-            // thread tid holds entries 2 tid, 2 tid + 1: one 4-byte BF16 pair
-            // per split
-            char* xs = smem + buf * BUF + c * TB + 4 * tid;
-            const float x0 = sx[c].x, x1 = sx[c].y;
-            const float q0 = x0 * x0, q1 = x1 * x1;
-            unsigned hi, lo;
-            r3_split(x0, x1, hi, lo);
-            *(unsigned*)xs = hi;
-            *(unsigned*)(xs + 1024) = lo;
-            r3_split(q0, q1, hi, lo);
-            *(unsigned*)(xs + 2048) = hi;
-            *(unsigned*)(xs + 3072) = lo;
-            char* bs = smem + buf * BUF + c * TB + 4096;
-#pragma unroll
-            for (int i = 0; i < NPB; i++) {
-                const int q = piece(i);
-                *(r3_u32x4*)(bs + (q >> 6) * 1024 + (q & 63) * 16) = sb[c][i];
-            }
-        }
-    };
-    // row operands of chunk ch: 8 samples of two operand rows
+    // row operands of chunk ch: lane l loads samples 2(l%16), +1 of rows
+    // l/16 + 4h
     struct Ld {
-        r3_v4d x1[2], x2[2];
+        r3_v2d x1[4], x2[4];
     };
     auto load_rows = [&](int ch, Ld& L) {
-        const int s = 32 * ch + 8 * kq;
+        unsigned ldb = (unsigned)(g.ldn * 8);
+        __asm__("" : "+s"(ldb));                         // (addresses formed here, not kept)
+        const char* q1 = (const char*)b1 + (int64_t)ch * 256 + r16 * 16;
+        const char* q2 = (const char*)b2 + (int64_t)ch * 256 + r16 * 16;
 #pragma unroll
-        for (int h = 0; h < 2; h++) {
-            L.x1[h] = *(const r3_v4d*)(p1 + s + 4 * h);
-            L.x2[h] = *(const r3_v4d*)(p2 + s + 4 * h);
+        for (int h = 0; h < 4; h++) {
+            L.x1[h] = *(const r3_v2d*)(q1 + (uint64_t)ri1[h] * ldb);
+            L.x2[h] = *(const r3_v2d*)(q2 + (uint64_t)ri2[h] * ldb);
         }
     };
-    Ld cur, nxt;
-    stage_load(0);
-    load_rows(0, cur);
-    stage_store(0);
-    __syncthreads();
-    // Only the last chunk holds samples >= n: there the row values are set
-    // to 0 (the right-hand operands are 0 too, but a row value there may be
-    // inf or NaN).  A row whose feature is invalid only reaches its own row
-    // of the products, whose scores are never stored, so it is not masked.
-    // The products of chunk ch from buffer ch & 1 and the rows in cur; the
-    // last chunk (samples >= n masked) runs after the loop as a copy of its
-    // own, so that no other chunk carries the mask.
-    auto chunk = [&](int ch, auto tail_c) {
-        constexpr bool tail = decltype(tail_c)::value;
-        const int s = 32 * ch + 8 * kq;
-        double v[8];
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            const r3_v4d w = r3_combine(oo, cur.x1[h], cur.x2[h]);
-#pragma unroll
-            for (int e = 0; e < 4; e++) v[4 * h + e] = w[e];
-        }
-        float vf[8];
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            double x = v[e];
-            if (hk) x = r3_rcp(x);
-            if (tail && s + e >= g.n) x = 0.0;
-            if (hk) hmx = fabs(x) > hmx ? fabs(x) : hmx;   // NaN leaves it unchanged
-            // FP64 -> FP32 here and FP32 -> BF16 in the pack: two
-            // hardware roundings (the error bound counts both); the
-            // empty asm keeps the compiler from fusing them into one
-            // correctly rounded (and much longer) conversion
-            vf[e] = (float)x;
-            __asm__("" : "+v"(vf[e]));
-        }
-        // av = a_h (also the numerators' operand), al = a_l, qh / ql:
-        // the splits of a^2
+    char* const tw = trow + wv * 2048 + kq * 128 + (r16 & 1) * 8;
+    const int tws = ((r16 >> 1) ^ (kq >> 1)) * 16;
+    const char* const tr = trow + wv * 2048 + r16 * 128;
+    const int trs = ((2 * kq) ^ (r16 >> 1)) * 16;
+    // a chunk's left-hand operands: a_h (also the numerators'), a_l and the
+    // splits of a^2
+    struct Lhs {
         r3_u32x4 ah, al, qh, ql;
+    };
+    // Row values of a chunk, in FP32, to the wave's LDS (row r: 32 values in
+    // eight 16-byte pieces, piece q at q ^ (r / 2): writes and reads touch
+    // every bank once).  Only the last chunk holds samples >= n: there the
+    // values are set to 0 (the right-hand operands are 0 too, but a row value
+    // there may be inf or NaN).  A row whose feature is invalid only reaches
+    // its own row of the products, whose scores are never stored, so it is
+    // not masked.  FP64 -> FP32 here and FP32 -> BF16 in prepare are two
+    // hardware roundings (the error bound counts both).
+    auto form = [&](int ch, const Ld& L, auto kind_c, auto tail_c) {
+        constexpr int kind = decltype(kind_c)::value;
+        constexpr bool tail = decltype(tail_c)::value;
+        double v[8];
+        if constexpr (kind == RK_OTHER) {
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                const r3_v4d w = r3_combine(oo, r3_v4d{L.x1[2 * h].x, L.x1[2 * h].y, L.x1[2 * h + 1].x, L.x1[2 * h + 1].y},
+                                            r3_v4d{0.0, 0.0, 0.0, 0.0});
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[4 * h + e] = w[e];
+            }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const double x = L.x1[e >> 1][e & 1], y = L.x2[e >> 1][e & 1];
+                v[e] = kind == RK_PROD ? x * y : kind == RK_ADD ? x + y : x - y;
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            r3_f32x2 w;
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                double x = v[2 * h + e];
+                if (hk && kind != RK_PROD) x = r3_rcp(x);
+                if (tail && 32 * ch + 2 * r16 + e >= g.n) x = 0.0;
+                w[e] = (float)x;
+            }
+            *(r3_f32x2*)(tw + h * 512 + (tws ^ (32 * h))) = w;
+        }
+    };
+    auto prepare = [&](Lhs& A) {
+        float vf[8];
+        *(r3_f32x4*)vf = *(const r3_f32x4*)(tr + trs);
+        *(r3_f32x4*)(vf + 4) = *(const r3_f32x4*)(tr + (trs ^ 16));
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            if (hk) hmx = fmaxf(hmx, fabsf(vf[e]));      // NaN leaves it unchanged
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             unsigned h, l;
             r3_split(vf[2 * e], vf[2 * e + 1], h, l);
-            ah[e] = h;
-            al[e] = l;
+            A.ah[e] = h;
+            A.al[e] = l;
             r3_split(vf[2 * e] * vf[2 * e], vf[2 * e + 1] * vf[2 * e + 1], h, l);
-            qh[e] = h;
-            ql[e] = l;
-        }
-        const r3_bf16x8 av = __builtin_bit_cast(r3_bf16x8, ah);
-        const r3_bf16x8 avl = __builtin_bit_cast(r3_bf16x8, al);
-        const r3_bf16x8 aq = __builtin_bit_cast(r3_bf16x8, qh);
-        const r3_bf16x8 aql = __builtin_bit_cast(r3_bf16x8, ql);
-#pragma unroll
-        for (int c = 0; c < CT; c++) {
-            const char* xs = smem + (ch & 1) * BUF + c * TB + 16 * lane;
-            const char* bs = smem + (ch & 1) * BUF + c * TB + 4096;
-            const r3_bf16x8 xh = *(const r3_bf16x8*)xs, xl = *(const r3_bf16x8*)(xs + 1024);
-            const r3_bf16x8 x2h = *(const r3_bf16x8*)(xs + 2048), x2l = *(const r3_bf16x8*)(xs + 3072);
-            s1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, xh, s1[c], 0, 0, 0);
-            s2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, x2h, s2[c], 0, 0, 0);
-            c1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, xl, c1[c], 0, 0, 0);
-            c2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, x2l, c2[c], 0, 0, 0);
-            c1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avl, xh, c1[c], 0, 0, 0);
-            c2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aql, x2h, c2[c], 0, 0, 0);
-#pragma unroll
-            for (int t = 0; t < TP; t++) {
-                const r3_bf16x8 bv = *(const r3_bf16x8*)(bs + t * 1024 + lane * 16);
-                pa[c][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, pa[c][t], 0, 0, 0);
-            }
+            A.qh[e] = h;
+            A.ql[e] = l;
         }
     };
-    for (int ch = 0; ch + 1 < a.NC; ch++) {
-        stage_load(ch + 1);
-        load_rows(ch + 1, nxt);
-        if (active) chunk(ch, std::false_type{});
-        stage_store((ch + 1) & 1);
+    // The products of a chunk in groups of up to 4 right-hand operands: per
+    // column tile the moments (x_h, x_l, (x^2)_h, (x^2)_l; 6 products), then
+    // the targets by fours.  A group's operands are read from LDS while the
+    // products of the group before it run (the scheduling barriers keep the
+    // reads there: the compiler would move each to its product and wait out
+    // the LDS latency every time).
+    constexpr int GT = (TP + 3) / 4, NG = CT * (1 + GT);
+    struct Rhs {
+        r3_bf16x8 v[4];
+    };
+    auto read_group = [&](int buf, auto gi_c, Rhs& R) {
+        constexpr int gi = decltype(gi_c)::value, c = gi / (1 + GT), q = gi % (1 + GT);
+        const char* xs = smem + buf * BUF + c * TB + 16 * lane;
+        constexpr int n = q == 0 || TP >= 4 * q ? 4 : TP - 4 * (q - 1);
+#pragma unroll
+        for (int i = 0; i < n; i++) R.v[i] = *(const r3_bf16x8*)(xs + (q * 4 + i) * 1024);
+    };
+    auto mul_group = [&](const Lhs& A, auto gi_c, const Rhs& R) {
+        constexpr int gi = decltype(gi_c)::value, c = gi / (1 + GT), q = gi % (1 + GT);
+        const r3_bf16x8 av = __builtin_bit_cast(r3_bf16x8, A.ah);
+        if constexpr (q == 0) {
+            const r3_bf16x8 avl = __builtin_bit_cast(r3_bf16x8, A.al);
+            const r3_bf16x8 aq = __builtin_bit_cast(r3_bf16x8, A.qh);
+            const r3_bf16x8 aql = __builtin_bit_cast(r3_bf16x8, A.ql);
+            s1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, R.v[0], s1[c], 0, 0, 0);
+            s2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, R.v[2], s2[c], 0, 0, 0);
+            c1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(avl, R.v[0], c1[c], 0, 0, 0);
+            c2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aql, R.v[2], c2[c], 0, 0, 0);
+            c1[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, R.v[1], c1[c], 0, 0, 0);
+            c2[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq, R.v[3], c2[c], 0, 0, 0);
+        } else {
+            constexpr int t0 = 4 * (q - 1), n = TP - t0 < 4 ? TP - t0 : 4;
+#pragma unroll
+            for (int i = 0; i < n; i++)
+                pa[c][t0 + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, R.v[i], pa[c][t0 + i], 0, 0, 0);
+        }
+    };
+    Rhs R[2];
+    auto products = [&](int buf, const Lhs& A) {             // (group 0 has been read)
+        auto step = [&](auto self, auto gi_c) -> void {
+            constexpr int gi = decltype(gi_c)::value;
+            if constexpr (gi + 1 < NG) read_group(buf, std::integral_constant<int, gi + 1>{}, R[(gi + 1) & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            mul_group(A, gi_c, R[gi & 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (gi + 1 < NG) self(self, std::integral_constant<int, gi + 1>{});
+        };
+        step(step, std::integral_constant<int, 0>{});
+    };
+    // Per chunk: the loads of the next chunk's row operands and the copies of
+    // its right-hand operands start, this chunk's left-hand operands and
+    // products are formed, then the next chunk's row values, and the block
+    // meets once the copies are in LDS.
+    auto run = [&](auto kind_c) {
+        const int NC = a.NC;
+        Ld L;
+        Lhs A;
+        stage(0, 0);
+        load_rows(0, L);
+        if (NC > 1)
+            form(0, L, kind_c, std::false_type{});
+        else
+            form(0, L, kind_c, std::true_type{});
+        __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        cur = nxt;
+        for (int ch = 0; ch < NC; ch++) {
+            const bool more = ch + 1 < NC;
+            if (more) {
+                load_rows(ch + 1, L);
+                stage(ch + 1, (ch + 1) & 1);
+            }
+            prepare(A);
+            read_group(ch & 1, std::integral_constant<int, 0>{}, R[0]);
+            products(ch & 1, A);
+            if (!more) break;
+            if (ch + 2 < NC)
+                form(ch + 1, L, kind_c, std::false_type{});
+            else
+                form(ch + 1, L, kind_c, std::true_type{});
+            __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __syncthreads();
+        }
+    };
+    // (the kind is wave-uniform; every kind meets the same barriers)
+    switch (rkind) {
+    case RK_PROD: run(std::integral_constant<int, RK_PROD>{}); break;
+    case RK_ADD: run(std::integral_constant<int, RK_ADD>{}); break;
+    case RK_SUB: run(std::integral_constant<int, RK_SUB>{}); break;
+    default: run(std::integral_constant<int, RK_OTHER>{}); break;
     }
-    if (active) chunk(a.NC - 1, std::true_type{});
     if (!active) return;
     if (hk) {
-        hmx = fmax(hmx, __shfl_xor(hmx, 16, 64));
-        hmx = fmax(hmx, __shfl_xor(hmx, 32, 64));
+        hmx = fmaxf(hmx, __shfl_xor(hmx, 16, 64));
+        hmx = fmaxf(hmx, __shfl_xor(hmx, 32, 64));
     }
     const double nn = (double)g.n;
     unsigned cnt = 0;
@@ -836,7 +938,7 @@ __global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs
             const int i = 4 * kq + e;                      // row of slot e
             const bool ok = __shfl((int)rok, i, 64) != 0 && colok;
             const int64_t gj = __shfl(j2, i, 64);
-            const double hx = hk ? __shfl(hmx, i, 64) : 0.0;
+            const double hx = hk ? (double)__shfl(hmx, i, 64) : 0.0;
             if (!ok) continue;
             // max |g| <= sqrt(sum g^2) = sqrt(n E[g^2]) (E[g^2] recorded by the
             // rung-2 screen; 1 % margin for its rounding): only compared with
@@ -851,9 +953,9 @@ __global__ __launch_bounds__(256, (TP * CT <= 16 ? 2 : 1)) void k_r3_lp(R3lpArgs
                 sure = rmx * xmx < R3_BIG;
                 amx = rmx; fmx = rmx * xmx; bmx = xmx;
             } else if (op3 == OP_DIV) {
-                if (rmn == 0.0) continue;                  // x / 0: not finite
+                // (1/g beyond FP32, a zero of g among it: the fix-up decides)
                 sure = rmn >= R3_TINY && xmx < R3_BIG * rmn;
-                amx = 1.0 / rmn; fmx = xmx / rmn; bmx = xmx;
+                amx = hx; fmx = xmx * hx; bmx = xmx;
             } else {
                 if (xmn == 0.0) continue;                  // g / 0: not finite
                 sure = xmn >= R3_TINY && rmx < R3_BIG * xmn;
@@ -904,16 +1006,16 @@ void launch_lp_range(R3lpArgs l, int ct0, int ct1, hipStream_t st) {
     k_r3_lp<TP, CT, HK><<<(unsigned)((int64_t)l.m.n_gblk * groups), 256, 0, st>>>(l);
 }
 
-// Column tiles per wave: up to 3 at <= 4 targets and 2 at 8 (3 tiles at 8
-// targets hold 266 VGPRs, one wave per SIMD; measured on gfx950 at 8
-// targets: 2 tiles 19.3 ms, 3 tiles 22.8 ms per dimension of the large
-// workload), as many as the range holds; the rest in smaller groups.
+// Column tiles per wave: as many as the range holds, up to the most whose
+// accumulators leave two waves per SIMD (256 registers): 3 up to 8 targets
+// (2 for the div tiles at 8, which would spill), 1 at 16; the rest in
+// smaller groups.
 template <int TP>
 void launch_lp(R3lpArgs l, int n_gct, int nct, int64_t n_grec, hipStream_t st) {
     l.m.n_gblk = (int)((n_grec / 16 + 3) / 4);
-    constexpr int CMAX = TP <= 4 ? 3 : TP <= 8 ? 2 : 1;
     auto range = [&](int c0, int c1, auto hk) {
         constexpr bool HK = decltype(hk)::value;
+        constexpr int CMAX = TP <= 4 || (TP <= 8 && !HK) ? 3 : TP <= 8 ? 2 : 1;
         int c = c0;
         if constexpr (CMAX >= 3) {
             const int m = (c1 - c) / 3 * 3;
@@ -1087,11 +1189,10 @@ void launch_r3(discover_ctx* ctx, const R3Launch& a, hipStream_t st) {
         k_r3_pstat<<<(unsigned)P.pe, 256, 0, st>>>(a.n, a.ldn, P.pe, a.Vf, a.pstat);
         check_launch("k_r3_pstat");
         const int NC = r3_chunks(a.n);
-        float* b32 = (float*)a.bmat;
-        __bf16* blp = (__bf16*)(b32 + (size_t)P.n_ctiles * NC * 512);
-        const int64_t tot = (int64_t)P.n_ctiles * (a.TP + 1) * NC * 512;
+        __bf16* blp = (__bf16*)a.bmat;
+        const int64_t tot = (int64_t)P.n_ctiles * NC * 512;
         k_r3_bmat_lp<<<(unsigned)std::min<int64_t>(cdiv(tot, 256), 16384), 256, 0, st>>>(
-            a.n, a.ldn, a.TP, NC, P.n_ctiles, P.coldesc, a.Vf, a.Rf, a.Yn, b32, blp);
+            a.n, a.ldn, a.TP, NC, P.n_ctiles, P.coldesc, a.Vf, a.Rf, a.Yn, blp);
         check_launch("k_r3_bmat_lp");
         R3lpArgs l{};
         R3mArgs& m = l.m;
@@ -1101,7 +1202,7 @@ void launch_r3(discover_ctx* ctx, const R3Launch& a, hipStream_t st) {
         m.valid = a.valid; m.mat_raw = a.mat_raw; m.r2v = a.r2v; m.ysum = a.ysum; m.sd = a.sd;
         m.sm = a.sm; m.N = a.N; m.scores = a.scores; m.nscored = a.nscored; m.fix_ids = a.fix_ids;
         m.fix_cnt = a.fix_cnt; m.fix_cap = a.fix_cap;
-        l.b32 = b32; l.blp = blp; l.r2q = a.r2q; l.NC = NC; l.delta = a.delta; l.cm = r3_moment_err(a.n);
+        l.blp = blp; l.r2q = a.r2q; l.NC = NC; l.delta = a.delta; l.cm = r3_moment_err(a.n);
         KTimer kt(ctx, st, "screen_r3");
         switch (a.TP) {
         case 1: launch_lp<1>(l, P.n_gct, P.n_ctiles, P.n_grec, st); break;

@@ -1381,15 +1381,16 @@ __device__ __forceinline__ void d_compact(const double* __restrict__ sc, int64_t
 
 // Exact FP64 rescore of the pool (one wave per entry); also flags entries
 // whose ID is excluded.
-// Values of the first cap pool entries as the exact rescoring evaluated
-// them (row w of v, leading dimension ld), with their mean and centred sum
-// of squares (NaN where the candidate is not valid): the duplicate-pair
-// correlations then need one pass over two stored rows instead of two
-// evaluations of each candidate.
+// Values of the first cap rescored entries as the exact rescoring evaluated
+// them (leading dimension ld), with their mean and centred sum of squares:
+// the duplicate-pair correlations then need one pass over two stored rows
+// instead of two evaluations of each candidate.  pos holds the row of each
+// pool entry, or -1 (not valid, not rescored, or past cap).
 struct PoolVals {
     double* v;
     int64_t ld, cap;
     double *mean, *sxx;
+    int32_t* pos;
 };
 
 // ------------------------------------------------------ selection rules
@@ -1508,16 +1509,23 @@ __device__ __forceinline__ bool rules_pass(const RuleTab& R, const Cand& c) {
 
 // The pool is rescored in two stages.  Stage 0 takes the entries whose
 // screening score reaches the selection's lower bound th (at least K of
-// them) and histograms their exact scores; the K-th largest of those, a
+// them) - of the entries that hold only an upper bound of their score
+// (negative: the precision form's ill-conditioned candidates) those among
+// the pool's K largest scores and bounds (hist2, k_pool_hist) - and
+// histograms their exact scores; the K-th largest of those, a
 // lower bound theta1 of the K-th largest exact score, then spares stage 1
 // every remaining entry whose score cannot reach it (|screening| + margin <
 // theta1): those are marked not selectable, and the groups count the pool
 // complete only down to max(th - margin, theta1).  d_split lists each
 // stage's pool positions (pex = 2 marks a position left to stage 1).
+// (The bounds are counted apart because th counts scores alone: most of the
+// best candidates of a rung-3 search in BF16 hold bounds, so that 276,000
+// of 388,000 pool entries reached th = 0.46 where the K-th of 33,000 exact
+// scores was 0.56.)
 __device__ __forceinline__ void d_split(int stage, const unsigned long long* __restrict__ Pp, int64_t cap,
                                         const uint32_t* __restrict__ sel, const int64_t* __restrict__ st,
                                         double margin, int64_t K, const uint32_t* __restrict__ hist1,
-                                        uint32_t* __restrict__ th1d, double* __restrict__ perr,
+                                        const uint32_t* __restrict__ hist2, uint32_t* __restrict__ th1d, double* __restrict__ perr,
                                         uint8_t* __restrict__ pex, double* __restrict__ ps,
                                         int32_t* __restrict__ rank, int32_t* __restrict__ order,
                                         const PoolVals pvs, int32_t* __restrict__ lst,
@@ -1525,7 +1533,11 @@ __device__ __forceinline__ void d_split(int stage, const unsigned long long* __r
     const int64_t P = min((int64_t)*Pp, cap);
     const bool all = st[1] != 0;
     const double th = select_threshold(sel, st);
-    double th1 = 0.0;
+    double th1 = 0.0, tb = 0.0;
+    if (stage == 0 && hist2) {
+        const RadixDigit d = radix_digit(hist2, K, false);
+        tb = d.all ? 0.0 : (double)d.digit * 2.44140625e-4;           // digit * 2^-12
+    }
     if (stage == 1) {
         const RadixDigit d = radix_digit(hist1, K, false);
         th1 = d.all ? 0.0 : (double)d.digit * 2.44140625e-4;          // digit * 2^-12
@@ -1534,13 +1546,15 @@ __device__ __forceinline__ void d_split(int stage, const unsigned long long* __r
     const int lane = threadIdx.x & 63;
     const uint64_t below = (1ull << lane) - 1ull;
     const int64_t l0 = stage == 0 ? 0 : (int64_t)lcnt[0];
-    for (int64_t i0 = (int64_t)blockIdx.x * 256 + (threadIdx.x & ~63); i0 < P; i0 += (int64_t)gridDim.x * 256) {
-        const int64_t w = i0 + lane;
+    __shared__ unsigned s_n[4];
+    __shared__ unsigned long long s_base;
+    for (int64_t i0 = (int64_t)blockIdx.x * 256; i0 < P; i0 += (int64_t)gridDim.x * 256) {
+        const int64_t w = i0 + threadIdx.x;
         bool take = false;
         if (w < P) {
             const double x = fabs(perr[w]);               // the screening score (stage 0)
             if (stage == 0) {
-                take = all || x >= th;
+                take = all || (x >= th && (x >= tb || perr[w] > 0.0));
                 if (!take) pex[w] = 2;
             } else if (pex[w] == 2) {
                 take = x + margin >= th1;
@@ -1550,20 +1564,42 @@ __device__ __forceinline__ void d_split(int stage, const unsigned long long* __r
                     rank[w] = 0;
                     order[w] = (int32_t)w;
                     perr[w] = 0.0;
-                    if (w < pvs.cap) {
-                        pvs.mean[w] = __longlong_as_double(0x7FF8000000000000LL);
-                        pvs.sxx[w] = __longlong_as_double(0x7FF8000000000000LL);
-                    }
+                    pvs.pos[w] = -1;
                 }
             }
         }
+        // one atomic per 256 entries (one per wave: 75 us for 388,000)
         const uint64_t m = __builtin_amdgcn_ballot_w64(take);
-        if (!m) continue;                                 // (wave-uniform)
-        unsigned long long base = 0;
-        if (lane == 0) base = atomicAdd(&lcnt[stage], (unsigned long long)__popcll(m));
-        base = __shfl(base, 0, 64);
-        if (take) lst[l0 + (int64_t)(base + __popcll(m & below))] = (int32_t)w;
+        const int wv = wave_id();
+        if (lane == 0) s_n[wv] = (unsigned)__popcll(m);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            const unsigned all4 = s_n[0] + s_n[1] + s_n[2] + s_n[3];
+            s_base = all4 ? atomicAdd(&lcnt[stage], (unsigned long long)all4) : 0ull;
+        }
+        __syncthreads();
+        unsigned long long base = s_base + (unsigned long long)l0;
+        for (int q = 0; q < wv; q++) base += s_n[q];
+        if (take) lst[base + __popcll(m & below)] = (int32_t)w;
+        __syncthreads();
     }
+}
+
+// Histogram of the pool's screening scores and bounds by size (4096 bins of
+// 2^-12), which d_split ranks the bounds by.
+__device__ __forceinline__ void d_pool_hist(const double* __restrict__ perr,
+                                            const unsigned long long* __restrict__ Pp, int64_t cap,
+                                            uint32_t* __restrict__ hist2) {
+    __shared__ uint32_t h[4096];
+    const int64_t P = min((int64_t)*Pp, cap);
+    if ((int64_t)blockIdx.x * 256 >= P) return;
+    for (int b = threadIdx.x; b < 4096; b += 256) h[b] = 0u;
+    __syncthreads();
+    for (int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x; w < P; w += (int64_t)gridDim.x * 256)
+        atomicAdd(&h[fx_key(fabs(perr[w])) >> 40], 1u);
+    __syncthreads();
+    for (int b = threadIdx.x; b < 4096; b += 256)
+        if (h[b]) atomicAdd(&hist2[b], h[b]);
 }
 
 // Exact scores of the pool, four entries per block (one per wave) in step:
@@ -1604,8 +1640,9 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
     bool ok = has && cand_of_id(ev, id, c);
     // a candidate the rules do not allow keeps its values but is never selected
     const bool allowed = !ok || !rules || rules_pass(*rules, c);
-    const bool keep = has && w < pvs.cap;
-    double* vals = keep ? pvs.v + w * pvs.ld : nullptr;
+    const int64_t row = l0 + wl;
+    const bool keep = has && row < pvs.cap;
+    double* vals = keep ? pvs.v + row * pvs.ld : nullptr;
     // first pass: values, mean, finiteness, add/sub cancellation
     double m = 0.0;
     if (ok) {
@@ -1674,9 +1711,12 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
             if (t < T) r[t] = wave_sum(sxy[t]) / sqrt(sxx * syy[t]);
     }
     if (!has) continue;
-    if (keep && lane == 0) {                              // NaN: nothing stored for this entry
-        pvs.mean[w] = ok ? m : __longlong_as_double(0x7FF8000000000000LL);
-        pvs.sxx[w] = ok ? sxx : __longlong_as_double(0x7FF8000000000000LL);
+    if (lane == 0) {
+        pvs.pos[w] = keep && ok ? (int32_t)row : -1;
+        if (keep && ok) {
+            pvs.mean[row] = m;
+            pvs.sxx[row] = sxx;
+        }
     }
     int ex = 0;
     for (int e = lane; e < n_excl; e += 64) ex |= excl[e] == id;
@@ -1697,7 +1737,7 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
         rank[w] = 0;                                      // counted by k_rankp or set by k_rk_rank
         order[w] = (int32_t)w;                            // (a valid index even before the scatter)
         const double x = perr[w];                         // screening-pass score (from the compaction)
-        perr[w] = s > 0.0 && x > 0.0 ? fabs(x - s) : 0.0; // its maximum is taken by k_groups
+        perr[w] = s > 0.0 && x > 0.0 ? fabs(x - s) : 0.0; // its maximum is taken by k_clusters
         if (stage == 0 && s > 0.0) atomicAdd(&hist1[fx_key(s) >> 40], 1u);
     }
     }
@@ -1864,10 +1904,19 @@ __device__ __forceinline__ void d_rk_range(const double* __restrict__ ps, const 
             v[3] = max(v[3], k);
         }
     }
+    // (one atomic per block: four addresses take them one after another,
+    // 190 us from 4096 waves)
+    __shared__ uint64_t bv[4][4];
 #pragma unroll
     for (int q = 0; q < 4; q++) {
         for (int o = 32; o > 0; o >>= 1) v[q] = max(v[q], (uint64_t)__shfl_xor((unsigned long long)v[q], o, 64));
-        if ((threadIdx.x & 63) == 0 && v[q]) atomicMax(&rkr[q], (unsigned long long)v[q]);
+        if ((threadIdx.x & 63) == 0) bv[q][wave_id()] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        const uint64_t* b = bv[threadIdx.x];
+        const uint64_t x = max(max(b[0], b[1]), max(b[2], b[3]));
+        if (x) atomicMax(&rkr[threadIdx.x], (unsigned long long)x);
     }
 }
 
@@ -2039,14 +2088,17 @@ __device__ __forceinline__ void d_clusters(const double* __restrict__ ss,
 __device__ __forceinline__ bool dup_pair(const int64_t* __restrict__ pool, int32_t iu, int32_t iv,
                                          const EvalCtx& ev, Ops o, int n, const PoolVals& pvs) {
     const int lane = threadIdx.x & 63;
-    if (iu < pvs.cap && iv < pvs.cap && !isnan(pvs.sxx[iu]) && !isnan(pvs.sxx[iv])) {
-        const double* u = pvs.v + (int64_t)iu * pvs.ld;
-        const double* v = pvs.v + (int64_t)iv * pvs.ld;
-        const double mu_ = pvs.mean[iu], mv = pvs.mean[iv];
+    const int64_t ru = pvs.pos[iu], rv = pvs.pos[iv];
+    if (ru >= 0 && rv >= 0) {
+        const double* u = pvs.v + ru * pvs.ld;
+        const double* v = pvs.v + rv * pvs.ld;
+        const double mu_ = pvs.mean[ru], mv = pvs.mean[rv];
         double uv = 0.0;
+        // eight loads in flight per row (30,000 pairs of 2000 samples: 597 -> 472 us)
+#pragma unroll 8
         for (int i = lane; i < n; i += 64) uv += (u[i] - mu_) * (v[i] - mv);
         uv = wave_sum(uv);
-        return fabs(uv) / sqrt(pvs.sxx[iu] * pvs.sxx[iv]) >= 1.0 - TAU_DUP;
+        return fabs(uv) / sqrt(pvs.sxx[ru] * pvs.sxx[rv]) >= 1.0 - TAU_DUP;
     }
     Cand cu, cv;
     if (!(cand_of_id(ev, pool[iu], cu) && cand_of_id(ev, pool[iv], cv))) return false;
@@ -2152,7 +2204,6 @@ __device__ __forceinline__ void d_dedup(const int64_t* __restrict__ pool, const 
     const int lane = threadIdx.x & 63;
     const bool staged = n <= DEDUP_LDS_N;
     volatile int32_t* vpar = parent;
-    auto stored = [&](int32_t i) { return i < pvs.cap && !isnan(pvs.sxx[i]); };
     for (int64_t c = blockIdx.x; c < nc; c += gridDim.x) {
         const int64_t c0 = starts[c];
         // the cluster's end, and its first entry the first-head pass left
@@ -2176,11 +2227,11 @@ __device__ __forceinline__ void d_dedup(const int64_t* __restrict__ pool, const 
                 s_end = lo + 1;
             }
             if (staged && w == 0) {              // head row, centred, into LDS
-                if (stored(ih)) {
-                    const double* u = pvs.v + (int64_t)ih * pvs.ld;
-                    const double mu_ = pvs.mean[ih];
+                if (const int64_t rh = pvs.pos[ih]; rh >= 0) {
+                    const double* u = pvs.v + rh * pvs.ld;
+                    const double mu_ = pvs.mean[rh];
                     for (int i = lane; i < n; i += 64) hc[i] = u[i] - mu_;
-                    if (lane == 0) { s_huu = pvs.sxx[ih]; s_hok = 1; }
+                    if (lane == 0) { s_huu = pvs.sxx[rh]; s_hok = 1; }
                 } else {
                     Cand ch;
                     const bool ok = cand_of_id(ev, pool[ih], ch);
@@ -2213,13 +2264,14 @@ __device__ __forceinline__ void d_dedup(const int64_t* __restrict__ pool, const 
                     dup = dup_pair(pool, ih, iv, ev, o, n, pvs);
                 } else if (!s_hok) {
                     dup = false;
-                } else if (stored(iv)) {
-                    const double* v = pvs.v + (int64_t)iv * pvs.ld;
-                    const double mv = pvs.mean[iv];
+                } else if (const int64_t rv = pvs.pos[iv]; rv >= 0) {
+                    const double* v = pvs.v + rv * pvs.ld;
+                    const double mv = pvs.mean[rv];
                     double uv = 0.0;
+#pragma unroll 8
                     for (int i = lane; i < n; i += 64) uv += hc[i] * (v[i] - mv);
                     uv = wave_sum(uv);
-                    dup = fabs(uv) / sqrt(s_huu * pvs.sxx[iv]) >= 1.0 - TAU_DUP;
+                    dup = fabs(uv) / sqrt(s_huu * pvs.sxx[rv]) >= 1.0 - TAU_DUP;
                 } else {
                     Cand cv;
                     if (!cand_of_id(ev, pool[iv], cv)) {
@@ -2303,14 +2355,13 @@ __device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t* part) {
 
 __device__ __forceinline__ void d_groups(
     const int64_t* __restrict__ pool, const double* __restrict__ ps, const uint8_t* __restrict__ pex,
-    const int32_t* __restrict__ order, const unsigned long long* __restrict__ Pp, int64_t cap,
+    const int32_t* __restrict__ order, const unsigned long long* __restrict__ Pp, int64_t P,
     double tail, int k, const uint32_t* __restrict__ sel,
     const int64_t* __restrict__ st, double margin, const uint32_t* __restrict__ th1d,
     int32_t* __restrict__ parent, int32_t* __restrict__ blk, unsigned long long* __restrict__ repid, int32_t* __restrict__ reppos,
     int32_t* __restrict__ headpos, int64_t* __restrict__ out_ids, double* __restrict__ out_sc,
     int64_t* __restrict__ res) {
     __shared__ int64_t part[GRP_THREADS];
-    const int64_t P = min((int64_t)*Pp, cap);
     const int t = threadIdx.x;
     const bool all = st[1] != 0;
     // the pool is complete down to th - margin, and down to theta1 where the
@@ -2498,10 +2549,10 @@ __device__ __forceinline__ void d_groups_lds(
                 if (o_first == keep_first) e = o;
             }
         if (t < ns) {
-            const int32_t slot = order[(int)((unsigned long long)e.id & 4095ull)];
+            const int64_t row = pvs.pos[order[(int)((unsigned long long)e.id & 4095ull)]];
             out_ids[t] = e.id >> 12;
             out_sc[t] = e.s;
-            vrow[t] = slot < pvs.cap ? (int64_t)(uintptr_t)(pvs.v + (int64_t)slot * pvs.ld) : 0;
+            vrow[t] = row >= 0 ? (int64_t)(uintptr_t)(pvs.v + row * pvs.ld) : 0;
         }
     } else {
     SK* tile = (SK*)par;                                          // 1024 entries = 16 KB
@@ -2528,8 +2579,8 @@ __device__ __forceinline__ void d_groups_lds(
         if (i < ns) {
             out_ids[rank] = ii;
             out_sc[rank] = si;
-            const int32_t slot = order[(int)(rkey[headpos[i]] & 4095ull)];
-            vrow[rank] = slot < pvs.cap ? (int64_t)(uintptr_t)(pvs.v + (int64_t)slot * pvs.ld) : 0;
+            const int64_t row = pvs.pos[order[(int)(rkey[headpos[i]] & 4095ull)]];
+            vrow[rank] = row >= 0 ? (int64_t)(uintptr_t)(pvs.v + row * pvs.ld) : 0;
         }
     }
     }
@@ -2639,7 +2690,7 @@ struct SelArgs {
     double* ss;               // scores in sorted order
     double* perr;             // per pool entry: its screening score, then |screening - exact|
     uint32_t* th1d;           // two-stage rescoring: digit of theta1 + 1 (0: none)
-    int64_t* off;
+    uint32_t* hist2;          // histogram of the pool's scores and bounds, or NULL (FP64: no bounds)
     uint8_t* flag;
     unsigned long long* ncl;  // near-tie clusters listed in wc (starts)
     unsigned long long* pd;   // end of the grouped prefix of the sorted pool
@@ -2649,7 +2700,7 @@ struct SelArgs {
     int64_t* out_ids;
     double* out_sc;
     int64_t* res;
-    PoolVals pvs;             // stored values of the first pvs.cap pool entries
+    PoolVals pvs;             // stored values of the first pvs.cap rescored entries
     int64_t* vrow;            // per selected rank: address of its stored value row, 0 for none
     const RuleTab* rules;     // selection rules, or NULL
     const unsigned long long* ctr;   // the problem's counters
@@ -2673,7 +2724,7 @@ __device__ __forceinline__ void report_list(const SelArgs& a) {
 // grid (blocks, lists) for the streaming kernels, (lists) for the one-block ones
 __global__ __launch_bounds__(256) void k_compact(ctab<SelArgs> A) {
     const SelArgs& a = tab(A, blockIdx.y);
-    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.off); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
+    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
     d_compact(a.sc, a.N, a.hist, a.sel, a.st, a.margin, a.cap, a.pool, a.cnt, a.K, a.ev.sm, a.ev.sd, a.perr);
 }
 
@@ -2682,18 +2733,24 @@ __global__ __launch_bounds__(256) void k_compact(ctab<SelArgs> A) {
 template <int TM>
 __global__ __launch_bounds__(256) void k_rescore(ctab<SelArgs> A, int stage) {
     const SelArgs& a = tab(A, blockIdx.y);
-    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.off); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
+    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
     d_rescore<TM>(a.pool, a.cnt, a.cap, a.ev, a.o, a.n, a.T, a.mode, a.t, a.Yc, a.syy,
                                     a.excl, a.n_excl, a.ps, a.pex, a.perr, a.rank, a.order, a.pvs,
                                     a.rules, a.lo, a.rkr + 4, stage, (uint32_t*)a.hist + 4096);
+}
+
+// grid (blocks, lists); launched for the precision forms only
+__global__ __launch_bounds__(256) void k_pool_hist(ctab<SelArgs> A) {
+    const SelArgs& a = tab(A, blockIdx.y);
+    d_pool_hist(a.perr, a.cnt, a.cap, a.hist2);
 }
 
 // grid (blocks, lists): the pool positions of one rescoring stage (the
 // list in lo, its counts in rkr[4], rkr[5]; both free until the sort)
 __global__ __launch_bounds__(256) void k_split(ctab<SelArgs> A, int stage) {
     const SelArgs& a = tab(A, blockIdx.y);
-    d_split(stage, a.cnt, a.cap, a.sel, a.st, a.margin, a.K, a.hist + 4096, a.th1d, a.perr, a.pex, a.ps,
-            a.rank, a.order, a.pvs, a.lo, a.rkr + 4);
+    d_split(stage, a.cnt, a.cap, a.sel, a.st, a.margin, a.K, a.hist + 4096, a.hist2, a.th1d, a.perr, a.pex,
+            a.ps, a.rank, a.order, a.pvs, a.lo, a.rkr + 4);
 }
 
 // grid (i tiles, j chunks, lists)
@@ -2729,7 +2786,7 @@ __global__ __launch_bounds__(256) void k_rk_rank(ctab<SelArgs> A) {
 
 __global__ __launch_bounds__(256) void k_scatter(ctab<SelArgs> A) {
     const SelArgs& a = tab(A, blockIdx.y);
-    DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.rank); DSC_GLOBAL(a.order); DSC_GLOBAL(a.ss); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.off);
+    DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.rank); DSC_GLOBAL(a.order); DSC_GLOBAL(a.ss); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc);
     d_scatter(a.ps, a.cnt, a.cap, a.rank, a.order, a.ss);
 }
 
@@ -2737,6 +2794,19 @@ __global__ __launch_bounds__(256) void k_clusters(ctab<SelArgs> A) {
     const SelArgs& a = tab(A, blockIdx.y);
     DSC_GLOBAL(a.ss); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.ncl); DSC_GLOBAL(a.pd);
     d_clusters(a.ss, a.cnt, a.cap, a.K, a.dedup, a.parent, a.wc, a.ncl, a.pd);
+    // maximum |screening - exact| over the pool (one atomic per block)
+    __shared__ double emax[4];
+    const int64_t P = min((int64_t)*a.cnt, a.cap);
+    double e = 0.0;
+    for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < P; q += (int64_t)gridDim.x * 256)
+        e = fmax(e, a.perr[q]);
+    e = wave_max(e);
+    if ((threadIdx.x & 63) == 0) emax[wave_id()] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        e = fmax(fmax(emax[0], emax[1]), fmax(emax[2], emax[3]));
+        if (e > 0.0) atomicMax(a.maxerr, (unsigned long long)__double_as_longlong(e));
+    }
 }
 
 constexpr int DEDUP_THREADS = 512;
@@ -2754,22 +2824,8 @@ __global__ __launch_bounds__(DEDUP_THREADS) void k_dedup(ctab<SelArgs> A) {
 
 __global__ __launch_bounds__(GRP_THREADS) void k_groups(ctab<SelArgs> A) {
     const SelArgs& a = tab(A, blockIdx.x);
-    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.off); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
+    DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
     const int64_t P = min((int64_t)*a.cnt, a.cap);
-    {
-        // maximum |screening - exact| over the pool (one atomic per list)
-        __shared__ double emax[GRP_THREADS / 64];
-        double e = 0.0;
-        for (int64_t q = threadIdx.x; q < P; q += GRP_THREADS) e = fmax(e, a.perr[q]);
-        e = wave_max(e);
-        if ((threadIdx.x & 63) == 0) emax[threadIdx.x >> 6] = e;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            for (int w = 1; w < GRP_THREADS / 64; w++) e = fmax(e, emax[w]);
-            if (e > 0.0) atomicMax(a.maxerr, (unsigned long long)__double_as_longlong(e));
-        }
-        __syncthreads();
-    }
     // groups live in the prefix [0, Pd) of the sorted pool
     const int64_t Pd = min((int64_t)*a.pd, P);
     const double tail = Pd < P ? a.ps[a.order[Pd]] : -1.0;
@@ -2783,7 +2839,7 @@ __global__ __launch_bounds__(GRP_THREADS) void k_groups(ctab<SelArgs> A) {
         return;
     }
     for (int64_t i = threadIdx.x; i < a.k; i += GRP_THREADS) a.vrow[i] = 0;   // rows are evaluated
-    d_groups(a.pool, a.ps, a.pex, a.order, a.cnt, a.cap, tail, a.k, a.sel, a.st, a.margin, a.th1d, a.parent, a.blk,
+    d_groups(a.pool, a.ps, a.pex, a.order, a.cnt, Pd, tail, a.k, a.sel, a.st, a.margin, a.th1d, a.parent, a.blk,
              a.repid, a.reppos, a.headpos, a.out_ids, a.out_sc, a.res);
     if (threadIdx.x == 0) report_list(a);
 }
@@ -3667,6 +3723,9 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
 // its arrays (pool, scores, ..., counters at SEL_MISC, histograms at
 // SEL_HIST, stored pool values).
 constexpr int SEL_MISC = 17, SEL_HIST = 18;
+// Histograms of 4096 bins: the selection's, the exact scores of rescoring
+// stage 0, and the pool's scores and bounds.
+constexpr int SEL_HIST_N = 3 * 4096;
 
 static char* sel_layout(discover_ctx* ctx, int k, const std::vector<ListState>& LS,
                         const std::vector<int>& act, std::vector<std::vector<size_t>>& o) {
@@ -3686,7 +3745,7 @@ static char* sel_layout(discover_ctx* ctx, int k, const std::vector<ListState>& 
         v.push_back(ar.add(cap * 4));              // rank
         v.push_back(ar.add(cap * 8));              // ss
         v.push_back(ar.add(cap * 8));              // perr
-        v.push_back(ar.add((cap + 1) * 8));        // off
+        v.push_back(ar.add(cap * 4));              // rows of the stored values
         v.push_back(ar.add(fcap));                 // flag
         v.push_back(ar.add((cap + 1) * 4));        // parent
         v.push_back(ar.add((cap + 1) * 4));        // blk
@@ -3695,7 +3754,7 @@ static char* sel_layout(discover_ctx* ctx, int k, const std::vector<ListState>& 
         v.push_back(ar.add(((size_t)k + 1) * 4));  // headpos
         v.push_back(ar.add(64));                   // res
         v.push_back(ar.add(64));                   // cnt, maxerr, st[2], sel[4]
-        v.push_back(ar.add(8192 * 4));             // hist (two levels)
+        v.push_back(ar.add(SEL_HIST_N * 4));       // hist
         const size_t pvc = (size_t)pool_vals_cap(L.cap, L.n);
         v.push_back(ar.add(pvc * (size_t)L.n * 8)); // stored pool values
         v.push_back(ar.add(pvc * 8));              // their means
@@ -3785,7 +3844,7 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         a.pool = (int64_t*)at(); a.ps = (double*)at(); a.pex = (uint8_t*)at();
         a.order = (int32_t*)at(); a.lo = (int32_t*)at(); a.wc = (int32_t*)at();
         a.rank = (int32_t*)at(); a.ss = (double*)at(); a.perr = (double*)at();
-        a.off = (int64_t*)at(); a.flag = (uint8_t*)at();
+        a.pvs.pos = (int32_t*)at(); a.flag = (uint8_t*)at();
         a.parent = (int32_t*)at(); a.blk = (int32_t*)at(); a.repid = (unsigned long long*)at();
         a.reppos = (int32_t*)at(); a.headpos = (int32_t*)at(); a.res = (int64_t*)at();
         char* misc = at();
@@ -3801,6 +3860,7 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         uint32_t* sel = (uint32_t*)(misc + 32);
         a.th1d = (uint32_t*)(misc + 44);
         a.sel = sel; a.st = stv; a.hist = hist;
+        a.hist2 = prm.precision != DISCOVER_FP64 ? hist + 8192 : nullptr;
         a.sc = P.scores + (int64_t)L.t * P.N; a.N = P.N;
         a.margin = margin[L.b]; a.cap = L.cap; a.fcap = L.fcap; a.K = L.K;
         a.ev = P.ev(); a.o = P.ops(); a.n = P.n; a.T = P.T; a.mode = prm.score_mode; a.t = L.t;
@@ -3817,7 +3877,7 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         a.host = host ? host + (int64_t)HOST_RES * q : nullptr;
         ra[q] = RadixArgs{a.sc, P.N, L.K, hist, sel, stv, nullptr};
         fills.push_back(fill_seg(misc, 64, 0u));            // pool count, maximum error, st, sel, clusters, prefix
-        fills.push_back(fill_seg(hist, 8192 * 4, 0u));
+        fills.push_back(fill_seg(hist, SEL_HIST_N * 4, 0u));
         fills.push_back(fill_seg(a.rkh, RK_NB * 4 + 64, 0u));
         Nmax = std::max(Nmax, P.N);
         capmax = std::max(capmax, L.cap);
@@ -3839,6 +3899,8 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         for (const SelArgs& x : sa) Tm = std::max(Tm, x.T);
         const dim3 rg((unsigned)std::min<int64_t>(std::max(64, 2048 / nl), cdiv(capmax, 4)), nl);
         const dim3 sg((unsigned)std::min<int64_t>(1024, cdiv(capmax, 256)), nl);
+        if (prm.precision != DISCOVER_FP64)
+            k_pool_hist<<<dim3((unsigned)std::min<int64_t>(128, cdiv(capmax, 1024)), nl), 256, 0, st>>>(dsa);
         for (int stage = 0; stage < 2; stage++) {
             k_split<<<sg, 256, 0, st>>>(dsa, stage);
             if (Tm <= 1) k_rescore<1><<<rg, 256, 0, st>>>(dsa, stage);
@@ -3858,7 +3920,7 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         } else {
             // ranks through score buckets (grid-strided over the pool)
             const unsigned rb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(1024, cdiv(capmax, 256)));
-            k_rk_range<<<dim3(rb, nl), 256, 0, st>>>(dsa);
+            k_rk_range<<<dim3(std::min(rb, 256u), nl), 256, 0, st>>>(dsa);
             k_rk_hist<<<dim3(rb, nl), 256, 0, st>>>(dsa);
             k_rk_scan<<<nl, 1024, 0, st>>>(dsa);
             k_rk_scatter<<<dim3(rb, nl), 256, 0, st>>>(dsa);
@@ -3888,9 +3950,9 @@ static void select_reserve(discover_ctx* ctx, const discover_screen_params& prm,
     for (const ListState& L : LS) {
         const size_t cap = (size_t)L.cap, fcap = (size_t)L.fcap;
         const size_t pvc = (size_t)pool_vals_cap(L.cap, L.n);
-        for (size_t b : {cap * 8, cap * 8, cap, cap * 4, cap * 4, cap * 4, cap * 4, cap * 8, cap * 8, (cap + 1) * 8, fcap,
+        for (size_t b : {cap * 8, cap * 8, cap, cap * 4, cap * 4, cap * 4, cap * 4, cap * 8, cap * 8, cap * 4, fcap,
                          (cap + 1) * 4, (cap + 1) * 4, (cap + 1) * 8, (cap + 1) * 4,
-                         ((size_t)prm.k + 1) * 4, (size_t)64, (size_t)64, (size_t)8192 * 4,
+                         ((size_t)prm.k + 1) * 4, (size_t)64, (size_t)64, (size_t)SEL_HIST_N * 4,
                          pvc * (size_t)L.n * 8, pvc * 8, pvc * 8})
             ar.add(b);
     }
@@ -4031,7 +4093,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         char* base = sel_layout(ctx, prm.k, LS, act, o);
         for (size_t q = 0; q < act.size(); q++) {
             fills.push_back(fill_seg(base + o[q][SEL_MISC], 64, 0u));   // pool count, maximum error, st, sel, clusters, prefix
-            fills.push_back(fill_seg(base + o[q][SEL_HIST], 8192 * 4, 0u));
+            fills.push_back(fill_seg(base + o[q][SEL_HIST], SEL_HIST_N * 4, 0u));
             fills.push_back(fill_seg(base + o[q].back(), RK_NB * 4 + 64, 0u));   // rank buckets
         }
     };

@@ -38,3 +38,35 @@ def test_tile_edges(oracle_mod, p, n, T, ops2, mode):
             check_selection(ids[t].cpu().numpy(), sc[t].cpu().numpy(), lists[t][0], lists[t][1], what="list %d" % t)
     finally:
         c.close()
+
+
+@pytest.mark.parametrize("narrow", [0, 3, 7, 10])
+@pytest.mark.parametrize("k,dedup", [(1, True), (40, True), (40, False)])
+def test_bounds_in_the_pool(oracle_mod, narrow, k, dedup):
+    """Pools in which no, some, most or all of the best candidates hold upper
+    bounds of their scores (columns narrow about their mean are too
+    ill-conditioned for BF16 scores): rescoring in stages gives the selection
+    of the exact scores."""
+    import torch
+    import paper_2602_06986_amd as D
+    O = oracle_mod
+    p, n = 10, 150
+    rng = np.random.default_rng(77 + narrow)
+    X = rng.lognormal(0, 0.6, size=(p, n))
+    X[:narrow] = 1.0 + 0.15 * (X[:narrow] - X[:narrow].mean(1, keepdims=True))
+    Y = np.array([X[0] * X[5] + X[9] / X[2] + 0.02 * rng.normal(size=n)])
+    rung_ops = [None, ("sq",), ("mul", "add"), ("mul", "div")]
+    rung_pool = [None, None, None, 0]
+    sp = O.Space(p, 3, O.OPS, rung_ops, rung_pool)
+    lists, _, nvalid = O.sis(sp, X, None, Y, k, (), "per_target", dedup=dedup)
+    every = O.screen_scores(sp, X, Y, None, "per_target")[0]
+    q = D.params(rung=3, k=k, rung_ops=rung_ops, rung_pool=rung_pool, precision=D.BF16_GUARD, dedup=dedup)
+    c = D.Context(0)
+    try:
+        for _ in range(2):                   # the second call starts from settled sizes
+            ids, sc, _, st = c.generate_screen(torch.as_tensor(X, device="cuda"), torch.as_tensor(Y, device="cuda"), q)
+        assert st["n_scored"] == nvalid
+        check_selection(ids[0].cpu().numpy(), sc[0].cpu().numpy(), lists[0][0], lists[0][1],
+                        None if dedup else every[0])
+    finally:
+        c.close()

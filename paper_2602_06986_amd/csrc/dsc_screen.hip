@@ -346,6 +346,70 @@ __device__ __forceinline__ double cand_value(const Cand& c, const Ops& o, int s)
     return apply_op(c.op, a, f2);
 }
 
+// apply_op over B samples: the operator is branched on once.
+template <int B>
+__device__ __forceinline__ void apply_ops(int op, const double (&a)[B], const double (&b)[B], double (&v)[B]) {
+    auto each = [&](auto f) {
+#pragma unroll
+        for (int q = 0; q < B; q++) v[q] = f(a[q], b[q]);
+    };
+    switch (op) {
+    case OP_EXP: each([](double x, double) { return exp(x); }); break;
+    case OP_LOG: each([](double x, double) { return log(x); }); break;
+    case OP_SQRT: each([](double x, double) { return sqrt(x); }); break;
+    case OP_SQ: each([](double x, double) { return x * x; }); break;
+    case OP_NONE: each([](double x, double) { return x; }); break;
+    case OP_ADD: each([](double x, double y) { return x + y; }); break;
+    case OP_SUB: each([](double x, double y) { return x - y; }); break;
+    case OP_MUL: each([](double x, double y) { return x * y; }); break;
+    case OP_DIV: each([](double x, double y) { return x / y; }); break;
+    default: each([](double x, double y) { return y / x; }); break;      // OP_RDIV
+    }
+}
+
+// The operand rows of a candidate: v = op(x, op2(y, z)), with OP_NONE for
+// the first argument itself (1/a is a stored row).
+struct CandRows {
+    const double *x, *y, *z;
+    int op, op2;
+};
+
+__device__ __forceinline__ CandRows cand_rows(const Cand& c, const Ops& o) {
+    auto row = [&](const double* b, int i) { return b + (int64_t)(i < 0 ? 0 : i) * o.ldn; };
+    CandRows r;
+    r.x = row(c.kind == 1 && c.op == OP_INV ? o.Rf : o.Vf, c.ca);
+    r.op = c.kind == 0 || (c.kind == 1 && c.op == OP_INV) ? OP_NONE : c.op;
+    r.op2 = OP_NONE;
+    r.y = r.z = r.x;
+    if (c.kind == 2) {
+        r.y = r.z = row(o.Vf, c.cb);
+    } else if (c.kind == 3) {
+        const bool inv = c.cd < 0 && c.op2 == OP_INV;
+        r.y = row(inv ? o.Rf : o.Vf, c.cc);
+        r.z = c.cd < 0 ? r.y : row(o.Vf, c.cd);
+        r.op2 = inv ? OP_NONE : c.op2;
+    }
+    return r;
+}
+
+// cand_value of samples s + 64 q (q < B), in v, and the candidate's operands
+// in x and f2: the loads of the (up to three) rows are in flight together.
+// Samples past the row's end are the caller's to mask (they read n - 1).
+template <int B>
+__device__ __forceinline__ void cand_values(const CandRows& r, int s, int n, double (&v)[B], double (&x)[B],
+                                            double (&f2)[B]) {
+    double y[B], z[B];
+#pragma unroll
+    for (int q = 0; q < B; q++) {
+        const int i = min(s + 64 * q, n - 1);
+        x[q] = r.x[i];
+        y[q] = r.y[i];
+        z[q] = r.z[i];
+    }
+    apply_ops<B>(r.op2, y, z, f2);
+    apply_ops<B>(r.op, x, f2, v);
+}
+
 // Decode an ID into an evaluable candidate; false when an operand is not an
 // operand feature (unit-illegal) or is invalid.
 __device__ __forceinline__ bool cand_of_id(const EvalCtx& e, int64_t id, Cand& c) {
@@ -378,29 +442,30 @@ __device__ __forceinline__ bool cand_of_id(const EvalCtx& e, int64_t id, Cand& c
 
 // Exact two-pass Pearson of one candidate against T centered targets by one
 // wave.  Returns false when the candidate is not finite or is constant.
+// Four samples per lane at a time, so that their loads overlap.
 template <int TMAX>
 __device__ bool wave_exact_r(const Cand& c, const Ops& o, int n, int T,
                              const double* __restrict__ Yc, const double* __restrict__ syy,
                              double* r, double* mean_out = nullptr, double* msq_out = nullptr,
-                             double* __restrict__ vals = nullptr, double* sxx_out = nullptr) {
+                             double* sxx_out = nullptr) {
     const int lane = threadIdx.x & 63;
+    const CandRows rows = cand_rows(c, o);
     double s = 0.0;
     int bad = 0;
     const bool addsub = (c.kind == 2 || c.kind == 3) && (c.op == OP_ADD || c.op == OP_SUB);
     double ff = 0.0, ab = 0.0;
-    for (int i = lane; i < n; i += 64) {
-        const double f = cand_value(c, o, i);
-        bad |= !isfinite(f);
-        s += f;
-        if (vals) vals[i] = f;
-        if (addsub) {
-            const double a = o.Vf[(int64_t)c.ca * o.ldn + i];
-            double b;
-            if (c.kind == 2) b = o.Vf[(int64_t)c.cb * o.ldn + i];
-            else b = c.cd < 0 ? unary_value(c.op2, o, c.cc, i)
-                              : apply_op(c.op2, o.Vf[(int64_t)c.cc * o.ldn + i], o.Vf[(int64_t)c.cd * o.ldn + i]);
-            ff += f * f;
-            ab += a * a + b * b;
+    for (int i0 = lane; i0 < n; i0 += 256) {
+        double f[4], xa[4], xb[4];
+        cand_values<4>(rows, i0, n, f, xa, xb);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            if (i0 + 64 * q >= n) break;
+            bad |= !isfinite(f[q]);
+            s += f[q];
+            if (addsub) {
+                ff += f[q] * f[q];
+                ab += xa[q] * xa[q] + xb[q] * xb[q];
+            }
         }
     }
     if (__any(bad)) return false;
@@ -413,12 +478,24 @@ __device__ bool wave_exact_r(const Cand& c, const Ops& o, int n, int T,
     double sxx = 0.0, sxy[TMAX];
 #pragma unroll
     for (int t = 0; t < TMAX; t++) sxy[t] = 0.0;
-    for (int i = lane; i < n; i += 64) {
-        const double d = cand_value(c, o, i) - m;
-        sxx += d * d;
+    for (int i0 = lane; i0 < n; i0 += 256) {
+        double d[4], xa[4], xb[4];
+        cand_values<4>(rows, i0, n, d, xa, xb);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            d[q] = i0 + 64 * q < n ? d[q] - m : 0.0;
+            sxx += d[q] * d[q];
+        }
 #pragma unroll
         for (int t = 0; t < TMAX; t++)
-            if (t < T) sxy[t] += d * Yc[(int64_t)t * o.ldn + i];
+            if (t < T) {
+                const double* y = Yc + (int64_t)t * o.ldn;
+                double yv[4];
+#pragma unroll
+                for (int q = 0; q < 4; q++) yv[q] = y[min(i0 + 64 * q, n - 1)];
+#pragma unroll
+                for (int q = 0; q < 4; q++) sxy[t] += d[q] * yv[q];
+            }
     }
     sxx = wave_sum(sxx);
     if (!isfinite(sxx)) return false;
@@ -440,15 +517,51 @@ struct ListItem {
     int32_t kind, op, ca, cb;
 };
 
+template <int TMAX>
 __device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uint8_t* __restrict__ valid,
                                              int n, int T, int mode, const double* __restrict__ Yc,
                                              const double* __restrict__ syy, int64_t N,
                                              double* __restrict__ scores, unsigned* nok,
                                              uint8_t* __restrict__ r2v, double* __restrict__ r2m,
                                              double* __restrict__ r2q, int64_t off2, int64_t off3,
-                                             double* __restrict__ fy, int TP);
+                                             double* __restrict__ fy, int TP) {
+    Cand c{it.kind, it.op, it.ca, it.cb, OP_NONE, -1, -1};
+    bool ok = valid[c.ca] && (c.kind < 2 || valid[c.cb]);
+    if (c.kind == 0) ok = valid[c.ca];
+    double r[TMAX], mean = 0.0, msq = 0.0, sxx = 0.0;
+    ok = ok && wave_exact_r<TMAX>(c, o, n, T, Yc, syy, r, &mean, &msq, &sxx);
+    if ((threadIdx.x & 63) == 0) {
+        // an operand feature's sums (f - mean) y_t, for the matrix form's sums and differences
+        if (fy && ok && it.kind == 0)
+#pragma unroll
+            for (int t = 0; t < TMAX; t++)
+                if (t < TP) fy[(int64_t)it.ca * TP + t] = t < T ? r[t] * sqrt(sxx) : 0.0;
+        if (!ok) {
+            for (int t = 0; t < (mode ? 1 : T); t++) scores[(int64_t)t * N + it.id] = __longlong_as_double(-1LL);
+            return;
+        }
+        atomicAdd(nok, 1u);
+        if (r2v && it.id >= off2 && it.id < off3) {
+            r2v[it.id - off2] = 1;
+            r2m[it.id - off2] = mean;
+            r2q[it.id - off2] = msq;
+        }
+        if (mode == DISCOVER_SCORE_MAX) {
+            double mx = 0.0;
+#pragma unroll
+            for (int t = 0; t < TMAX; t++)
+                if (t < T) mx = fmax(mx, fabs(r[t]));
+            scores[it.id] = mx;
+        } else {
+#pragma unroll
+            for (int t = 0; t < TMAX; t++)
+                if (t < T) scores[(int64_t)t * N + it.id] = fabs(r[t]);
+        }
+    }
+}
 
 // One wave per listed candidate (exact two-pass score).
+template <int TMAX>
 __device__ __forceinline__ void d_score_list(const ListItem* __restrict__ items, int64_t m,
                                                     Ops o, const uint8_t* __restrict__ valid,
                                                     int n, int T, int mode,
@@ -464,46 +577,10 @@ __device__ __forceinline__ void d_score_list(const ListItem* __restrict__ items,
     if (threadIdx.x == 0) nok = 0u;
     __syncthreads();
     const int64_t w = (int64_t)blockIdx.x * 4 + wave_id();
-    if (w < m) d_score_item(items[w], o, valid, n, T, mode, Yc, syy, N, scores, &nok, r2v, r2m, r2q,
+    if (w < m) d_score_item<TMAX>(items[w], o, valid, n, T, mode, Yc, syy, N, scores, &nok, r2v, r2m, r2q,
                             off2, off3, fy, TP);
     __syncthreads();
     if (threadIdx.x == 0 && nok) atomicAdd(nscored, (unsigned long long)nok);
-}
-
-__device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uint8_t* __restrict__ valid,
-                                             int n, int T, int mode, const double* __restrict__ Yc,
-                                             const double* __restrict__ syy, int64_t N,
-                                             double* __restrict__ scores, unsigned* nok,
-                                             uint8_t* __restrict__ r2v, double* __restrict__ r2m,
-                                             double* __restrict__ r2q, int64_t off2, int64_t off3,
-                                             double* __restrict__ fy, int TP) {
-    Cand c{it.kind, it.op, it.ca, it.cb, OP_NONE, -1, -1};
-    bool ok = valid[c.ca] && (c.kind < 2 || valid[c.cb]);
-    if (c.kind == 0) ok = valid[c.ca];
-    double r[DISCOVER_MAX_TARGETS], mean = 0.0, msq = 0.0, sxx = 0.0;
-    ok = ok && wave_exact_r<DISCOVER_MAX_TARGETS>(c, o, n, T, Yc, syy, r, &mean, &msq, nullptr, &sxx);
-    if ((threadIdx.x & 63) == 0) {
-        // an operand feature's sums (f - mean) y_t, for the matrix form's sums and differences
-        if (fy && ok && it.kind == 0)
-            for (int t = 0; t < TP; t++) fy[(int64_t)it.ca * TP + t] = t < T ? r[t] * sqrt(sxx) : 0.0;
-        if (!ok) {
-            for (int t = 0; t < (mode ? 1 : T); t++) scores[(int64_t)t * N + it.id] = __longlong_as_double(-1LL);
-            return;
-        }
-        atomicAdd(nok, 1u);
-        if (r2v && it.id >= off2 && it.id < off3) {
-            r2v[it.id - off2] = 1;
-            r2m[it.id - off2] = mean;
-            r2q[it.id - off2] = msq;
-        }
-        if (mode == DISCOVER_SCORE_MAX) {
-            double mx = 0.0;
-            for (int t = 0; t < T; t++) mx = fmax(mx, fabs(r[t]));
-            scores[it.id] = mx;
-        } else {
-            for (int t = 0; t < T; t++) scores[(int64_t)t * N + it.id] = fabs(r[t]);
-        }
-    }
 }
 
 struct ListArgs {
@@ -523,12 +600,16 @@ struct ListArgs {
     int TP;
 };
 
-// grid (item blocks of 4, problems)
-__global__ __launch_bounds__(256) void k_score_list(ctab<ListArgs> A) {
+// grid (item blocks of 4, problems); TM: the most targets (padded) of any
+// problem of the launch.  Bound by latency, two passes over a few rows per
+// wave: 190 -> 100 us for the 1580 candidates of 20 primaries at 8 targets
+// with the loads of four samples together and sums for 8 targets, not 16.
+template <int TM>
+__global__ __launch_bounds__(256, 4) void k_score_list(ctab<ListArgs> A) {
     const ListArgs& a = tab(A, blockIdx.y);
     DSC_GLOBAL(a.items); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.valid); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.scores); DSC_GLOBAL(a.nscored);
     if ((int64_t)blockIdx.x * 4 >= a.m) return;
-    d_score_list(a.items, a.m, a.o, a.valid, a.n, a.T, a.mode, a.Yc, a.syy, a.N, a.scores, a.nscored,
+    d_score_list<TM>(a.items, a.m, a.o, a.valid, a.n, a.T, a.mode, a.Yc, a.syy, a.N, a.scores, a.nscored,
                  a.r2v, a.r2m, a.r2q, a.off2, a.off3, a.fy, a.TP);
 }
 
@@ -1604,16 +1685,19 @@ __device__ __forceinline__ void d_pool_hist(const double* __restrict__ perr,
 
 // Exact scores of the pool, four entries per block (one per wave) in step:
 // the first pass (values, mean, finiteness) per wave; in the second the
-// block stages the centred targets of each 64-sample chunk in LDS once
-// (double-buffered, one barrier per chunk) and every wave reads them there,
-// so the T target rows are read from memory once per four entries instead
-// of once per entry.  Per entry the arithmetic (and its order) is that of
-// wave_exact_r.
+// block stages the centred targets of each chunk of RS_CH samples in LDS once
+// (double-buffered, one barrier per chunk, the next chunk's loads in flight)
+// and every wave reads them there, so the T target rows are read from memory
+// once per four entries instead of once per entry.  Both passes take four
+// samples per lane at a time, so that their loads overlap: bound by latency
+// otherwise (80,000 entries of 2000 samples, 8 targets: 1.85 ms one sample
+// at a time and chunks of 64, 1.16 ms so).  Per entry the arithmetic (and its
+// order) is that of wave_exact_r.
 template <int TMAX>
 __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
                                                  const unsigned long long* __restrict__ Pp, int64_t cap,
                                                  const EvalCtx& ev, Ops o, int n,
-                                                 int T, int mode, int tlist,
+                                                 int T, int mode,
                                                  const double* __restrict__ Yc,
                                                  const double* __restrict__ syy,
                                                  const int64_t* __restrict__ excl, int n_excl,
@@ -1630,7 +1714,9 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
     const int64_t l0 = stage == 0 ? 0 : (int64_t)lcnt[0];
     const int64_t P = min((int64_t)lcnt[stage], cap - l0);
     const int lane = threadIdx.x & 63;
-    __shared__ double ys[2][TMAX][64];
+    constexpr int RS_CH = TMAX <= 8 ? 256 : 128;
+    constexpr int YR = (TMAX * RS_CH + 255) / 256;       // staged values per thread
+    __shared__ double ys[2][TMAX][RS_CH];
     for (int64_t g = blockIdx.x; g * 4 < P; g += gridDim.x) {      // uniform over the block
     const int64_t wl = g * 4 + wave_id();
     const bool has = wl < P;
@@ -1640,6 +1726,7 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
     bool ok = has && cand_of_id(ev, id, c);
     // a candidate the rules do not allow keeps its values but is never selected
     const bool allowed = !ok || !rules || rules_pass(*rules, c);
+    const CandRows rows = ok ? cand_rows(c, o) : CandRows{o.Vf, o.Vf, o.Vf, OP_NONE, OP_NONE};
     const int64_t row = l0 + wl;
     const bool keep = has && row < pvs.cap;
     double* vals = keep ? pvs.v + row * pvs.ld : nullptr;
@@ -1650,19 +1737,20 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
         int bad = 0;
         const bool addsub = (c.kind == 2 || c.kind == 3) && (c.op == OP_ADD || c.op == OP_SUB);
         double ff = 0.0, ab = 0.0;
-        for (int i = lane; i < n; i += 64) {
-            const double f = cand_value(c, o, i);
-            bad |= !isfinite(f);
-            s += f;
-            if (vals) vals[i] = f;
-            if (addsub) {
-                const double a = o.Vf[(int64_t)c.ca * o.ldn + i];
-                double b;
-                if (c.kind == 2) b = o.Vf[(int64_t)c.cb * o.ldn + i];
-                else b = c.cd < 0 ? unary_value(c.op2, o, c.cc, i)
-                                  : apply_op(c.op2, o.Vf[(int64_t)c.cc * o.ldn + i], o.Vf[(int64_t)c.cd * o.ldn + i]);
-                ff += f * f;
-                ab += a * a + b * b;
+        for (int i0 = lane; i0 < n; i0 += 256) {
+            double f[4], xa[4], xb[4];
+            cand_values<4>(rows, i0, n, f, xa, xb);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                const int i = i0 + 64 * q;
+                if (i >= n) break;
+                bad |= !isfinite(f[q]);
+                s += f[q];
+                if (vals) vals[i] = f[q];
+                if (addsub) {
+                    ff += f[q] * f[q];
+                    ab += xa[q] * xa[q] + xb[q] * xb[q];
+                }
             }
         }
         if (__any(bad)) ok = false;
@@ -1677,22 +1765,46 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
     double sxx = 0.0, sxy[TMAX];
 #pragma unroll
     for (int t = 0; t < TMAX; t++) sxy[t] = 0.0;
-    for (int i0 = 0, it = 0; i0 < n; i0 += 64, it++) {
-        double(*yb)[64] = ys[it & 1];
-        for (int q = threadIdx.x; q < T * 64; q += blockDim.x) {
-            const int t = q >> 6, j = q & 63;
-            yb[t][j] = i0 + j < n ? Yc[(int64_t)t * o.ldn + i0 + j] : 0.0;
+    double yr[YR];
+    auto load_y = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < YR; u++) {
+            const int q = threadIdx.x + 256 * u, t = q / RS_CH, j = q % RS_CH;
+            yr[u] = t < T && i0 + j < n ? Yc[(int64_t)t * o.ldn + i0 + j] : 0.0;
+        }
+    };
+    load_y(0);
+    for (int i0 = 0, it = 0; i0 < n; i0 += RS_CH, it++) {
+        double(*yb)[RS_CH] = ys[it & 1];
+#pragma unroll
+        for (int u = 0; u < YR; u++) {
+            const int q = threadIdx.x + 256 * u;
+            if (q / RS_CH < T) yb[q / RS_CH][q % RS_CH] = yr[u];
         }
         __syncthreads();
-        const int i = i0 + lane;
-        if (ok && i < n) {
+        if (i0 + RS_CH < n) load_y(i0 + RS_CH);
+        if (!ok) continue;
+        for (int j0 = lane; j0 < RS_CH && i0 + j0 < n; j0 += 256) {
             // the first pass's values: stored (read back by the lane that
             // wrote them) or evaluated again
-            const double d = (vals ? vals[i] : cand_value(c, o, i)) - m;
-            sxx += d * d;
+            constexpr int B = RS_CH / 64;
+            double f[B];
+            if (vals) {
 #pragma unroll
-            for (int t = 0; t < TMAX; t++)
-                if (t < T) sxy[t] += d * yb[t][lane];
+                for (int q = 0; q < B; q++) f[q] = i0 + j0 + 64 * q < n ? vals[i0 + j0 + 64 * q] : 0.0;
+            } else {
+                double xa[B], xb[B];
+                cand_values<B>(rows, i0 + j0, n, f, xa, xb);
+            }
+#pragma unroll
+            for (int q = 0; q < B; q++) {
+                if (i0 + j0 + 64 * q >= n) break;
+                const double d = f[q] - m;
+                sxx += d * d;
+#pragma unroll
+                for (int t = 0; t < TMAX; t++)
+                    if (t < T) sxy[t] += d * yb[t][j0 + 64 * q];
+            }
         }
     }
     __syncthreads();                               // the buffers are refilled by the next group
@@ -1726,9 +1838,11 @@ __device__ __forceinline__ void d_rescore(const int64_t* __restrict__ pool,
         if (ok) {
             if (mode == DISCOVER_SCORE_MAX) {
                 s = 0.0;
-                for (int t = 0; t < T; t++) s = fmax(s, fabs(r[t]));
+#pragma unroll
+                for (int t = 0; t < TMAX; t++)
+                    if (t < T) s = fmax(s, fabs(r[t]));
             } else {
-                s = fabs(r[tlist]);
+                s = fabs(r[0]);
             }
             if (!(s > 0.0) || !allowed) s = -1.0;
         }
@@ -1774,10 +1888,14 @@ __device__ __forceinline__ void d_fixup(const int64_t* __restrict__ ids,
         }
         if (mode == DISCOVER_SCORE_MAX) {
             double mx = 0.0;
-            for (int t = 0; t < T; t++) mx = fmax(mx, fabs(r[t]));
+#pragma unroll
+            for (int t = 0; t < TMAX; t++)
+                if (t < T) mx = fmax(mx, fabs(r[t]));
             scores[sl] = mx;
         } else {
-            for (int t = 0; t < T; t++) scores[(int64_t)t * N + sl] = fabs(r[t]);
+#pragma unroll
+            for (int t = 0; t < TMAX; t++)
+                if (t < T) scores[(int64_t)t * N + sl] = fabs(r[t]);
         }
     }
     if ((threadIdx.x & 63) == 0 && nfix) atomicAdd(nscored, (unsigned long long)nfix);
@@ -2676,7 +2794,7 @@ struct SelArgs {
     unsigned long long* cnt;  // pool entries found (may exceed cap)
     EvalCtx ev;
     Ops o;
-    int n, T, mode, t, k, dedup;
+    int n, T, mode, k, dedup; // T targets from Yc
     const double *Yc, *syy;
     const int64_t* excl;
     int n_excl;
@@ -2731,10 +2849,10 @@ __global__ __launch_bounds__(256) void k_compact(ctab<SelArgs> A) {
 // TM: the most targets of any list of the launch (1, 8 or 16 registers of
 // sums per lane).
 template <int TM>
-__global__ __launch_bounds__(256) void k_rescore(ctab<SelArgs> A, int stage) {
+__global__ __launch_bounds__(256, TM <= 8 ? 4 : 3) void k_rescore(ctab<SelArgs> A, int stage) {
     const SelArgs& a = tab(A, blockIdx.y);
     DSC_GLOBAL(a.sc); DSC_GLOBAL(a.sel); DSC_GLOBAL(a.st); DSC_GLOBAL(a.pool); DSC_GLOBAL(a.cnt); DSC_GLOBAL(a.ev.raw2c); DSC_GLOBAL(a.ev.valid); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.ps); DSC_GLOBAL(a.pex); DSC_GLOBAL(a.maxerr); DSC_GLOBAL(a.order); DSC_GLOBAL(a.lo); DSC_GLOBAL(a.wc); DSC_GLOBAL(a.flag); DSC_GLOBAL(a.parent); DSC_GLOBAL(a.blk); DSC_GLOBAL(a.repid); DSC_GLOBAL(a.reppos); DSC_GLOBAL(a.headpos); DSC_GLOBAL(a.out_ids); DSC_GLOBAL(a.out_sc); DSC_GLOBAL(a.res);
-    d_rescore<TM>(a.pool, a.cnt, a.cap, a.ev, a.o, a.n, a.T, a.mode, a.t, a.Yc, a.syy,
+    d_rescore<TM>(a.pool, a.cnt, a.cap, a.ev, a.o, a.n, a.T, a.mode, a.Yc, a.syy,
                                     a.excl, a.n_excl, a.ps, a.pex, a.perr, a.rank, a.order, a.pvs,
                                     a.rules, a.lo, a.rkr + 4, stage, (uint32_t*)a.hist + 4096);
 }
@@ -3484,7 +3602,13 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
     }
     {
         KTimer kt(ctx, st, "screen_list");
-        k_score_list<<<dim3((unsigned)cdiv(mmax, 4), nb), 256, 0, st>>>(ct(ctx->upload("scr_list", la, st)));
+        int Tm = 1;
+        for (const ListArgs& x : la) Tm = std::max(Tm, x.TP);
+        const dim3 grid((unsigned)cdiv(mmax, 4), nb);
+        const ctab<ListArgs> d = ct(ctx->upload("scr_list", la, st));
+        if (Tm <= 1) k_score_list<1><<<grid, 256, 0, st>>>(d);
+        else if (Tm <= 8) k_score_list<8><<<grid, 256, 0, st>>>(d);
+        else k_score_list<DISCOVER_MAX_TARGETS><<<grid, 256, 0, st>>>(d);
         check_launch("k_score_list");
     }
     // 5. sample-major copies of the operands of the pair kernels
@@ -3863,9 +3987,12 @@ static void select_round(discover_ctx* ctx, const discover_problem* probs,
         a.hist2 = prm.precision != DISCOVER_FP64 ? hist + 8192 : nullptr;
         a.sc = P.scores + (int64_t)L.t * P.N; a.N = P.N;
         a.margin = margin[L.b]; a.cap = L.cap; a.fcap = L.fcap; a.K = L.K;
-        a.ev = P.ev(); a.o = P.ops(); a.n = P.n; a.T = P.T; a.mode = prm.score_mode; a.t = L.t;
+        a.ev = P.ev(); a.o = P.ops(); a.n = P.n; a.mode = prm.score_mode;
         a.k = k; a.dedup = prm.dedup;
-        a.Yc = P.Yc; a.syy = P.syy;
+        // the targets the list's scores take: all of them, or the list's own
+        const int64_t t0 = prm.score_mode == DISCOVER_SCORE_MAX ? 0 : L.t;
+        a.T = prm.score_mode == DISCOVER_SCORE_MAX ? P.T : 1;
+        a.Yc = P.Yc + t0 * P.ldn; a.syy = P.syy + t0;
         a.excl = pb.exclude; a.n_excl = pb.exclude ? pb.n_exclude : 0;
         auto rt = rtab.find(L.b);
         if (rt == rtab.end()) rt = rtab.emplace(L.b, rule_table(ctx, P, L.b, st)).first;

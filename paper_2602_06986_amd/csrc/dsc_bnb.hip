@@ -510,11 +510,23 @@ __global__ __launch_bounds__(256) void k_bnb_leaves(BnbLaunch g) {
 //     R^2 = R^2(P) + ct_p^2 / gt_p + e^2 / piv
 // (pivots gt_p and piv are the row-order Cholesky pivots of p and j: <=
 // PIV_TOL is singular).  The children p of P are cut by bound(P, p) as an
-// expansion cuts them; each child's leaves j in steps of 64 by bound(P + p,
-// j).  A leaf list that would overflow is counted, not written (the host
-// redoes the launch after compacting).
+// expansion cuts them; each child's leaves j end at the first step of 64
+// whose bound(P + p, j) fails.  A leaf list that would overflow is counted,
+// not written (the host redoes the launch after compacting).
+//
+// Bound: vector instructions, two thirds of the cycles (the rest waits for
+// the bounds' table reads).  A bound costs about 500 instructions, a step
+// of 64 leaves about 60, so the bounds of 32 children and two steps are
+// taken by one wave at once, a lane each; a leaf is divided out only where
+// e^2 reaches (thr - R^2 so far) piv, which says whether it can be listed.
+// 400 rows, D = 5, of 1600 samples (4.6e9 leaves): 46.4 ms with a bound
+// per child and 128 leaves, formed by every lane of a wave alike, and all
+// parents taken from a queue; 14.9 ms so (2.7e9 leaves).
+// Waves per SIMD the pair kernel's registers are held to.
+__host__ __device__ constexpr int bnb_pair_waves(int a) { return a <= 3 ? 4 : 2; }
+
 template <int A>
-__global__ __launch_bounds__(256) void k_bnb_pairs(BnbLaunch g, int64_t cap) {
+__global__ __launch_bounds__(256, bnb_pair_waves(A)) void k_bnb_pairs(BnbLaunch g, int64_t cap) {
     extern __shared__ double lds[];              // [A + 2][S]: w_r, gt_r, ct_r by row r - r0 (lanes contiguous)
     __shared__ int pcut_s;
     __shared__ int64_t next_s;
@@ -531,16 +543,26 @@ __global__ __launch_bounds__(256) void k_bnb_pairs(BnbLaunch g, int64_t cap) {
     const double cut = thr - BNB_CUT;
     unsigned long long nl = 0;
     double best = -1.0;
-    // parents are taken from a queue: their work varies with the rows after them
+    // neighbouring parents take similar work: the first seven eighths go to
+    // the blocks in turn, the rest by a queue (whose counter gives one number
+    // per 10 ns: all parents by it took 44 of 70 ms for 4.4 million)
+    const int64_t nturn = g.nin - g.nin / 8;
+    int64_t turn = blockIdx.x;
     for (;;) {
-        if (threadIdx.x == 0) next_s = (int64_t)atomicAdd(&g.st->qhead, 1ull);
-        __syncthreads();
-        const int64_t w = next_s;
-        __syncthreads();
-        if (w >= g.nin) break;
+        int64_t w = turn;
+        if (turn < nturn) {
+            turn += gridDim.x;
+        } else {
+            if (threadIdx.x == 0) next_s = nturn + (int64_t)atomicAdd(&g.st->qhead, 1ull);
+            __syncthreads();
+            w = next_s;
+            __syncthreads();
+            if (w >= g.nin) break;
+        }
+        const Node cur = g.in[w];
         int P[8];
 #pragma unroll
-        for (int k = 0; k < 8; k++) P[k] = k < A ? g.in[w].r[k] : 0;
+        for (int k = 0; k < 8; k++) P[k] = k < A ? cur.r[k] : 0;
         const int last = A > 0 ? P[A - 1] : -1;
         const int r0 = last + 1;
         double L[A > 0 ? A : 1][A > 0 ? A : 1], u[A > 0 ? A : 1];
@@ -569,9 +591,23 @@ __global__ __launch_bounds__(256) void k_bnb_pairs(BnbLaunch g, int64_t cap) {
         }
         if (singular) continue;                  // uniform over the block
         // 1. the later rows, residualised against P; the cut of the children
-        if (threadIdx.x == 0) pcut_s = S - 1;
-        __syncthreads();
-        for (int r = r0 + threadIdx.x; r < S; r += 256) {
+        // (one wave takes the bounds, 64 children at a time up to the first
+        // that fails, and the others the rows; the roles move on with the
+        // parents, so that no SIMD takes all the bounds)
+        const int role = (wv + (int)w) & 3;
+        if (role == 0) {
+            int pc = S - 1;
+            for (int c0 = r0; c0 <= S - 2; c0 += 64) {
+                const int r = c0 + lane;
+                const uint64_t fail = __builtin_amdgcn_ballot_w64(r <= S - 2 && bnb_bound<A>(T, P, S - r) < cut);
+                if (fail) {
+                    pc = c0 + __builtin_ctzll(fail);
+                    break;
+                }
+            }
+            if (lane == 0) pcut_s = pc;
+        }
+        for (int r = r0 + (role - 1) * 64 + lane; role > 0 && r < S; r += 192) {
             double* x = lds + (r - r0);
             double gt = T.dg[r], ct = cy[r];
             double v[A > 0 ? A : 1];
@@ -588,64 +624,77 @@ __global__ __launch_bounds__(256) void k_bnb_pairs(BnbLaunch g, int64_t cap) {
             }
             x[A * S] = gt;
             x[(A + 1) * S] = ct;
-            if (r <= S - 2 && bnb_bound<A>(T, P, S - r) < cut) atomicMin(&pcut_s, r);
         }
         __syncthreads();
         const int pcut = pcut_s;                 // children p < pcut survive
-        // 2. the leaves of each surviving child, one child per wave at a time
-        for (int p = r0 + wv; p < pcut; p += 4) {
-            const double* xp = lds + (p - r0);
-            const double gtp = xp[A * S], ctp = xp[(A + 1) * S];
-            if (!(gtp > PIV_TOL)) continue;
-            double wp[A > 0 ? A : 1];
-#pragma unroll
-            for (int k = 0; k < A; k++) wp[k] = xp[k * S];
-            const double base_p = base + ctp * ctp / gtp;
-            const double rg = 1.0 / gtp;
+        // 2. the surviving children, 32 per wave at a time: how many steps of
+        // 64 leaves each has (a lane per child and step takes the bound at
+        // the step's first leaf; the first step's, R^2(P + p + rows > p) =
+        // bound(P, p), passed the cut above), then the leaves
+        for (int b0 = r0; b0 < pcut; b0 += 128) {
+            const int p = b0 + 4 * (lane >> 1) + wv;
+            const int pr = min(p, S - 1) - r0;               // in-bounds row
+            const double gtp = lds[A * S + pr], ctp = lds[(A + 1) * S + pr];
+            bool open = p < pcut && gtp > PIV_TOL;
+            int steps = open ? 1 : 0;
             int Pp[8];
 #pragma unroll
-            for (int k = 0; k < 8; k++) Pp[k] = k < A ? P[k] : (k == A ? p : 0);
-            const double* gp = G + (int64_t)p * ldg;
-            // 128 leaves per step, two per lane (independent chains); the
-            // bound at the step's first leaf covers both.  The first step's
-            // bound, R^2(P + p + rows > p) = bound(P, p), passed the cut above.
-            for (int j0 = p + 1; j0 < S; j0 += 128) {
-                if (j0 > p + 1 && bnb_bound<A + 1>(T, Pp, S - j0) < cut) break;   // uniform over the wave
-                double val[2];
+            for (int k = 0; k < 8; k++) Pp[k] = k < A ? P[k] : (k == A ? min(p, S - 1) : 0);
+            for (int j0 = p + 1 + 64 * (1 + (lane & 1));; j0 += 128) {
+                const bool pass = open && j0 < S && !(bnb_bound<A + 1>(T, Pp, S - j0) < cut);
+                const unsigned two = (unsigned)(__builtin_amdgcn_ballot_w64(pass) >> (lane & ~1)) & 3u;
+                if (open) steps += two == 3u ? 2 : (int)(two & 1u);
+                open = open && two == 3u;
+                if (!__builtin_amdgcn_ballot_w64(open)) break;
+            }
+            const double rgl = 1.0 / gtp;
+            const double bpl = base + ctp * ctp / gtp;
+            uint64_t todo = __builtin_amdgcn_ballot_w64(steps > 0) & 0x5555555555555555ull;
+            while (todo) {
+                const int c = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const int pc = b0 + 2 * c + wv;
+                const int js = min(S, pc + 1 + 64 * __builtin_amdgcn_readlane(steps, c));
+                const double rg = lane_f64(rgl, c), base_p = lane_f64(bpl, c);
+                const double* xp = lds + (pc - r0);
+                const double ctc = xp[(A + 1) * S];
+                double wp[A > 0 ? A : 1];
 #pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    const int j = j0 + 64 * h + lane;
+                for (int k = 0; k < A; k++) wp[k] = xp[k * S];
+                // a leaf below tt cannot be listed, nor raise thr
+                const double tt = thr - GRAM_DELTA - base_p - 1e-12;
+                const double* gp = G + (int64_t)pc * ldg;
+                for (int j0 = pc + 1; j0 < js; j0 += 64) {
+                    const int j = j0 + lane;
                     const int jj = min(j, S - 1);            // in-bounds read; j >= S is discarded
                     const double* xj = lds + (jj - r0);
                     double gpj = gp[jj];
 #pragma unroll
                     for (int k = 0; k < A; k++) gpj -= wp[k] * xj[k * S];
                     const double piv = xj[A * S] - gpj * gpj * rg;
-                    const double e = xj[(A + 1) * S] - gpj * ctp * rg;
+                    const double e = xj[(A + 1) * S] - gpj * ctc * rg;
+                    nl += min(64, S - j0);
+                    const bool may = j < S && e * e >= tt * piv;
+                    if (!__builtin_amdgcn_ballot_w64(may)) continue;
                     // e^2 / piv by a reciprocal refined twice (Newton), a few
                     // ulps from the quotient
                     double r = __builtin_amdgcn_rcp(piv);
                     r = fma(fma(-piv, r, 1.0), r, r);
                     r = fma(fma(-piv, r, 1.0), r, r);
                     const double v = fma(e * e, r, base_p);
-                    val[h] = (j < S && piv > PIV_TOL) ? v : -1.0;
-                }
-                nl += min(128, S - j0);
-                best = fmax(best, fmax(val[0], val[1]));
-#pragma unroll
-                for (int h = 0; h < 2; h++) {
-                    const bool keep = val[h] >= 0.0 && val[h] >= thr - GRAM_DELTA;
+                    const double val = (j < S && piv > PIV_TOL) ? v : -1.0;
+                    best = fmax(best, val);
+                    const bool keep = val >= 0.0 && val >= thr - GRAM_DELTA;
                     const uint64_t km = __builtin_amdgcn_ballot_w64(keep);
                     if (km) {
                         const unsigned long long s = wave_slots(&g.st->ncand, km);
                         if (keep && (int64_t)s < cap) {
-                            const int j = j0 + 64 * h + lane;
                             Node nd;
 #pragma unroll
                             for (int k = 0; k < 8; k++)
-                                nd.r[k] = (int16_t)(k < A ? P[k] : (k == A ? p : (k == A + 1 ? j : 0)));
+                                nd.r[k] = (int16_t)(k < A ? P[k] : (k == A ? pc : (k == A + 1 ? j : 0)));
                             g.cand[s] = nd;
-                            g.cval[s] = val[h];
+                            g.cval[s] = val;
                         }
                     }
                 }
@@ -1037,13 +1086,14 @@ void launch_expand(int a, const BnbLaunch& g, hipStream_t st) {
     check_launch("k_bnb_expand");
 }
 
-constexpr int64_t BNB_PAIR_GRID = 2048;            // blocks of a pair launch
 
 // The leaves of g.nin parents of length a = D - 2 by the pair form, then
 // the threshold update.
 void launch_pairs(discover_ctx* ctx, int a, const BnbLaunch& g, int m, int64_t cap, hipStream_t st) {
-    const unsigned grid = (unsigned)std::min<int64_t>(g.nin, BNB_PAIR_GRID);
     const size_t lds = (size_t)(a + 2) * g.T.S * sizeof(double);
+    // as many blocks as run at once: by registers, and by LDS (160 KB per CU)
+    const int64_t per_cu = std::min<int64_t>(bnb_pair_waves(a), (160 << 10) / (int64_t)(lds + 256));
+    const unsigned grid = (unsigned)std::min<int64_t>(g.nin, 256 * std::max<int64_t>(1, per_cu));
     {
     KTimer kt(ctx, st, "bnb_pairs");
     switch (a) {

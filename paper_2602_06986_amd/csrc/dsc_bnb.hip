@@ -109,45 +109,82 @@ __global__ __launch_bounds__(256) void k_bnb_load(const double* __restrict__ G, 
 // block).  A pivot <= BNB_TAU of the row's own diagonal stops the factor:
 // m0 = that column.  A row that is exactly zero (a constant feature) spans
 // nothing: its column stays zero and is passed over.
+//
+// Bound by its serial chain: one wave factors the panel's own rows, a row
+// per lane and no barrier, then every thread solves one row below them
+// against the factor in LDS (two barriers and a pass over memory per column
+// took 99 us a panel of 400 rows, so 25).
 __global__ __launch_bounds__(1024) void k_bnb_panel(double* __restrict__ A, int lda, int S, int u0,
                                                     const double* __restrict__ G, int ldg,
                                                     BnbState* __restrict__ st) {
     if (st->stop) return;
-    const int u1 = min(S, u0 + BNB_PANEL);
-    for (int u = u0; u < u1; u++) {
-        const double orig = G[(int64_t)rev(u, S) * ldg + rev(u, S)];
-        const double d = A[(int64_t)u * lda + u];
-        if (orig == 0.0) {                      // uniform: every thread reads the same values
-            for (int t = u + threadIdx.x; t <= S; t += blockDim.x) A[(int64_t)t * lda + u] = 0.0;
-            __syncthreads();
-            continue;
-        }
-        if (!(d > BNB_TAU * orig)) {
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                st->stop = 1;
-                st->m0 = u;
-            }
-            return;
-        }
-        const double l = sqrt(d);
-        __syncthreads();
-        for (int t = u + 1 + threadIdx.x; t <= S; t += blockDim.x) A[(int64_t)t * lda + u] /= l;
-        if (threadIdx.x == 0) A[(int64_t)u * lda + u] = l;
-        __syncthreads();
-        // the rest of the panel: A[t][c] -= L[t][u] L[c][u], u < c < u1, t >= c
-        const int w = u1 - u - 1;
-        if (w > 0) {
-            const int64_t rows = S - u;          // t = u + 1 .. S
-            for (int64_t e = threadIdx.x; e < rows * w; e += blockDim.x) {
-                const int t = u + 1 + (int)(e / w);
-                const int c = u + 1 + (int)(e % w);
-                if (c <= t) A[(int64_t)t * lda + c] -= A[(int64_t)t * lda + u] * A[(int64_t)c * lda + u];
+    __shared__ double Ld[BNB_PANEL][BNB_PANEL];
+    __shared__ int done;                         // columns factored
+    const int u1 = min(S, u0 + BNB_PANEL), w = u1 - u0;
+    if (threadIdx.x < 64) {
+        const int r = threadIdx.x;
+        double* row = A + (int64_t)(u0 + min(r, w - 1)) * lda + u0;
+        const int64_t gd = rev(u0 + min(r, w - 1), S);
+        const double og = G[gd * ldg + gd];
+        double a[BNB_PANEL];
+#pragma unroll
+        for (int c = 0; c < BNB_PANEL; c++) a[c] = r < w && c <= r ? row[c] : 0.0;
+        int ks = w;
+#pragma unroll
+        for (int k = 0; k < BNB_PANEL; k++) {
+            if (k >= ks) continue;               // uniform, as all below
+            __builtin_amdgcn_sched_barrier(0);
+            const double orig = lane_f64(og, k), d = lane_f64(a[k], k);
+            if (orig == 0.0) {
+                a[k] = 0.0;
+            } else if (!(d > BNB_TAU * orig)) {
+                ks = k;
+            } else {
+                const double l = sqrt(d);
+                a[k] = r > k ? a[k] / l : r == k ? l : a[k];
+#pragma unroll
+                for (int c = k + 1; c < BNB_PANEL; c++) {
+                    a[c] -= a[k] * lane_f64(a[k], c);    // (not used where c > r)
+                }
             }
         }
-        __syncthreads();
+        if (r < w) {
+#pragma unroll
+            for (int c = 0; c < BNB_PANEL; c++)
+                if (c <= r) {
+                    row[c] = a[c];
+                    Ld[r][c] = a[c];
+                }
+        }
+        if (r == 0) done = ks;
     }
-    if (threadIdx.x == 0 && u1 == S) st->m0 = S;
+    __syncthreads();
+    const int ks = done;
+    for (int t = u1 + threadIdx.x; t <= S; t += 1024) {
+        double* row = A + (int64_t)t * lda + u0;
+        double a[BNB_PANEL];
+#pragma unroll
+        for (int c = 0; c < BNB_PANEL; c++) a[c] = c < w ? row[c] : 0.0;
+#pragma unroll
+        for (int k = 0; k < BNB_PANEL; k++) {
+            if (k >= ks) continue;
+            __builtin_amdgcn_sched_barrier(0);   // (all of Ld loaded ahead would spill)
+            double x = a[k];
+#pragma unroll
+            for (int i = 0; i < k; i++) x -= a[i] * Ld[k][i];
+            const double lk = Ld[k][k];
+            a[k] = lk == 0.0 ? 0.0 : x / lk;     // (a zero column spans nothing)
+            row[k] = a[k];
+        }
+    }
+    if (threadIdx.x == 0) {
+        if (ks < w) {
+            st->stop = 1;
+            st->m0 = u0 + ks;
+        } else if (u1 == S) {
+            st->m0 = S;
+        }
+    }
 }
 
 // Trailing update after panel u0: A[t][c] -= sum_u L[t][u] L[c][u] over the

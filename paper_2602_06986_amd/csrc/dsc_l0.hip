@@ -50,28 +50,34 @@ __device__ __forceinline__ void d_l0_prep(int n, int S, const double* __restrict
 // G = Z Z^T for M = S + 1 rows on the FP64 matrix cores.  A block covers a
 // 32 x 32 tile of the upper triangle (mirrored when written) as 2 x 2
 // products of v_mfma_f64_16x16x4f64, and its four waves split the sum over
-// samples into four runs of whole 16-sample chunks; the partial tiles meet
+// samples into four runs of whole 32-sample chunks; the partial tiles meet
 // in LDS and are added in wave order, so the result does not depend on
 // timing.  (Each wave owning a whole chain keeps the MFMA pipe busy between
 // loads; a 64 x 64 tile per block left small Gram matrices to a few dozen
 // blocks, each waiting on its loads.)  The instruction takes A[i][k] from
 // lane i + 16 k and B[k][j] from lane j + 16 k and leaves D[i][j] in lane
-// j + 16 (i mod 4), register i / 4.  The sum over samples may run in any
-// order, so lane l takes samples k0 + 4 (l / 16) + s at step s of a chunk
-// of 16: its four samples of a row are one 32-byte load, and the four lanes
-// of a row read 128 contiguous bytes.  The next chunk's fragments are
-// loaded while the current chunk's 16 products run.  ldz is a multiple of
-// 16 and Z is zero past n, rows are 32-byte aligned.
+// j + 16 (i mod 4), register i / 4.  Rows are loaded with the samples across
+// the lanes (16 lanes read 256 contiguous bytes) and turned to that order
+// through LDS of the wave's own: loaded in it, each load touches 64 cache
+// lines, whose look-ups bounded the kernel (2001 rows of 2000 samples: 284 us,
+// so 241).  The next chunk's rows are loaded while the current chunk's
+// products run.  The sum over samples may run in any order: lane l takes
+// samples 8 q + 2 (l / 16) + e at steps 2 q + e of a chunk.
 typedef double dsc_v4d __attribute__((ext_vector_type(4)));
+
+typedef double dsc_v2d __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ void d_gram(int M, int ldz, int nk, const double* __restrict__ Z,
                                        double* __restrict__ G, int ldg, int bi, int bj,
                                        double* __restrict__ dg) {
-    __shared__ dsc_v4d part[3][4][64];        // waves 1..3: their 2 x 2 partial tiles
+    // per wave: four 16-row tiles of 32 samples (16-byte piece p of row r at
+    // p ^ r, so that writes and reads touch every bank once), then waves
+    // 1..3: their 2 x 2 partial tiles
+    __shared__ __attribute__((aligned(16))) char buf[4][4][4096];
     const int wv = wave_id();
     const int lane = threadIdx.x & 63;
-    const int r16 = lane & 15, kg = 4 * (lane >> 4);
-    const int nch = nk >> 4;                  // chunks of 16 samples; wave wv takes [ch0, ch1)
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int nch = (nk + 31) >> 5;           // chunks of 32 samples; wave wv takes [ch0, ch1)
     const int ch0 = (nch * wv) >> 2, ch1 = (nch * (wv + 1)) >> 2;
     dsc_v4d acc[2][2];
 #pragma unroll
@@ -79,50 +85,55 @@ __device__ __forceinline__ void d_gram(int M, int ldz, int nk, const double* __r
 #pragma unroll
         for (int v = 0; v < 2; v++) acc[u][v] = dsc_v4d{0.0, 0.0, 0.0, 0.0};
     if (ch1 > ch0) {                          // (wave-uniform)
-        const double* pa[2];
-        const double* pb[2];
+        dsc_v2d L[4][4];
+        auto load = [&](int ch) {             // row 4 h + l / 16 of each tile, samples 2 (l % 16), + 1
+            unsigned ldb = (unsigned)ldz * 8u;
+            asm("" : "+s"(ldb));              // (addresses are formed here, not kept)
+            const int s = 32 * ch + 2 * r16;
+            const bool in = s < nk;           // the last chunk may be half a one
+            const char* z = (const char*)(Z + (in ? s : 0));
 #pragma unroll
-        for (int t = 0; t < 2; t++) {
-            pa[t] = Z + (int64_t)min(bi + 16 * t + r16, M - 1) * ldz + kg;
-            pb[t] = Z + (int64_t)min(bj + 16 * t + r16, M - 1) * ldz + kg;
-        }
-        double4 A[2], B[2];
-        const int kbeg = ch0 * 16, klast = ch1 * 16 - 16;
+            for (int t = 0; t < 4; t++)
 #pragma unroll
-        for (int t = 0; t < 2; t++) { A[t] = *(const double4*)(pa[t] + kbeg); B[t] = *(const double4*)(pb[t] + kbeg); }
-        for (int k0 = kbeg; k0 <= klast; k0 += 16) {
-            double4 An[2], Bn[2];
-            const int kn = min(k0 + 16, klast);   // the last chunk reloads itself
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                An[t] = *(const double4*)(pa[t] + kn);
-                Bn[t] = *(const double4*)(pb[t] + kn);
-            }
-#pragma unroll
-            for (int u = 0; u < 2; u++)
-#pragma unroll
-                for (int v = 0; v < 2; v++) {
-                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].x, B[v].x, acc[u][v], 0, 0, 0);
-                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].y, B[v].y, acc[u][v], 0, 0, 0);
-                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].z, B[v].z, acc[u][v], 0, 0, 0);
-                    acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[u].w, B[v].w, acc[u][v], 0, 0, 0);
+                for (int h = 0; h < 4; h++) {
+                    const int row = min((t < 2 ? bi + 16 * t : bj + 16 * (t - 2)) + 4 * h + kq, M - 1);
+                    const dsc_v2d x = *(const dsc_v2d*)(z + (uint64_t)(unsigned)row * ldb);
+                    L[t][h] = in ? x : dsc_v2d{0.0, 0.0};
                 }
-            // the loaded fragments pass through an empty asm: without it the
-            // compiler folds this load into a load at the top of the next
-            // chunk that waits for its own result
+        };
+        char* const wb = &buf[wv][0][0];
+        load(ch0);
+        for (int ch = ch0; ch < ch1; ch++) {
 #pragma unroll
-            for (int t = 0; t < 2; t++) {
-                asm("" : "+v"(An[t].x), "+v"(An[t].y), "+v"(An[t].z), "+v"(An[t].w));
-                asm("" : "+v"(Bn[t].x), "+v"(Bn[t].y), "+v"(Bn[t].z), "+v"(Bn[t].w));
-                A[t] = An[t]; B[t] = Bn[t];
+            for (int t = 0; t < 4; t++)
+#pragma unroll
+                for (int h = 0; h < 4; h++) {
+                    const int r = 4 * h + kq;
+                    *(dsc_v2d*)(wb + t * 4096 + r * 256 + ((r16 ^ r) << 4)) = L[t][h];
+                }
+            if (ch + 1 < ch1) load(ch + 1);
+#pragma unroll
+            for (int q = 0; q < 4; q++) {
+                dsc_v2d f[4];
+#pragma unroll
+                for (int t = 0; t < 4; t++)
+                    f[t] = *(const dsc_v2d*)(wb + t * 4096 + r16 * 256 + (((4 * q + kq) ^ r16) << 4));
+#pragma unroll
+                for (int e = 0; e < 2; e++)
+#pragma unroll
+                    for (int u = 0; u < 2; u++)
+#pragma unroll
+                        for (int v = 0; v < 2; v++)
+                            acc[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(f[u][e], f[2 + v][e], acc[u][v], 0, 0, 0);
             }
         }
     }
+    auto part = [&](int w, int uv) { return (dsc_v4d*)&buf[w][0][0] + uv * 64 + lane; };
     if (wv > 0)
 #pragma unroll
         for (int u = 0; u < 2; u++)
 #pragma unroll
-            for (int v = 0; v < 2; v++) part[wv - 1][2 * u + v][lane] = acc[u][v];
+            for (int v = 0; v < 2; v++) *part(wv, 2 * u + v) = acc[u][v];
     __syncthreads();
     if (wv != 0) return;
 #pragma unroll
@@ -131,7 +142,7 @@ __device__ __forceinline__ void d_gram(int M, int ldz, int nk, const double* __r
         for (int v = 0; v < 2; v++) {
             dsc_v4d t = acc[u][v];
 #pragma unroll
-            for (int w = 0; w < 3; w++) t += part[w][2 * u + v][lane];
+            for (int w = 1; w < 4; w++) t += *part(w, 2 * u + v);
 #pragma unroll
             for (int r = 0; r < 4; r++) {
                 const int i = bi + 16 * u + (lane >> 4) + 4 * r, j = bj + 16 * v + r16;

@@ -475,8 +475,8 @@ def large_main(args):
                 "avg_launch_ms": r3["avg_launch_ms"], "launches_timed": r3["launches_per_step"] * args.steps,
                 "work": "(4 + 2T) n flop per unit-valid rung-3 candidate and launch-average dimension "
                         "(T = 1, 8, 8), all on the BF16 matrix cores (12 + 2T n executed: split moments)",
-                "note": "the matrix cores are not what holds this kernel: it spends its time on "
-                        "regenerating rung-2 rows from rung-1 operand rows (loads and vector work)"}
+                "note": "the matrix cores are not what holds this kernel: reads and copies of the "
+                        "column operands in LDS take two thirds of its cycles"}
     if "screen_r3" in res["fp64"][2]:
         r3 = res["fp64"][2]["screen_r3"]
         flops = sum(valid3 * w["n"] * (4 + 2 * T) for T in Ts) / r3["launches_per_step"]

@@ -2049,25 +2049,41 @@ __device__ __forceinline__ void d_rk_hist(const double* __restrict__ ps, const i
 }
 
 // Exclusive prefix sum of the bucket counts, in place (one block of 1024).
+// A wave takes 4096 counts, four per lane and load, and scans them in
+// registers: 27 us with 64 counts per thread read and written one by one
+// and a scan over LDS, 8.5 so.
 __device__ __forceinline__ void d_rk_scan(uint32_t* __restrict__ rkh) {
-    constexpr int PER = RK_NB / 1024;
-    __shared__ uint32_t part[1024];
-    const int t = threadIdx.x;
-    uint32_t sum = 0;
-    for (int q = 0; q < PER; q++) sum += rkh[t * PER + q];
-    part[t] = sum;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {                   // inclusive scan of the parts
-        const uint32_t v = t >= o ? part[t - o] : 0u;
-        __syncthreads();
-        part[t] += v;
-        __syncthreads();
+    static_assert(RK_NB == 16 * 4096, "a wave scans 16 x 64 x 4 counts");
+    __shared__ uint32_t part[16];
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    uint4* r4 = (uint4*)rkh + wv * 1024 + lane;
+    uint4 c[16];
+    uint32_t ex[16], tot = 0;
+#pragma unroll
+    for (int i = 0; i < 16; i++) c[i] = r4[64 * i];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        const uint32_t sum = c[i].x + c[i].y + c[i].z + c[i].w;
+        uint32_t x = sum;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        ex[i] = tot + x - sum;
+        tot += __shfl(x, 63, 64);
     }
-    uint32_t run = part[t] - sum;
-    for (int q = 0; q < PER; q++) {
-        const uint32_t c = rkh[t * PER + q];
-        rkh[t * PER + q] = run;
-        run += c;
+    if (lane == 0) part[wv] = tot;
+    __syncthreads();
+    uint32_t base = 0;
+    for (int w = 0; w < wv; w++) base += part[w];
+#pragma unroll
+    for (int i = 0; i < 16; i++) {
+        uint4 r;
+        r.x = base + ex[i];
+        r.y = r.x + c[i].x;
+        r.z = r.y + c[i].y;
+        r.w = r.z + c[i].z;
+        r4[64 * i] = r;
     }
 }
 
@@ -2456,19 +2472,28 @@ __device__ __forceinline__ void d_dedup(const int64_t* __restrict__ pool, const 
 // res: [0] selected, [1] complete, [2] merged duplicates.
 constexpr int GRP_THREADS = 1024;
 
+// Exclusive sum over the block's threads; the total is left in
+// part[GRP_THREADS - 1].  (By waves: 4 barriers instead of 21.)
 __device__ __forceinline__ int64_t block_excl_scan(int64_t v, int64_t* part) {
-    const int t = threadIdx.x;
-    part[t] = v;
-    __syncthreads();
-    for (int o = 1; o < GRP_THREADS; o <<= 1) {
-        const int64_t x = t >= o ? part[t - o] : 0;
-        __syncthreads();
-        part[t] += x;
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wv = wave_id();
+    int64_t x = v;
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t y = __shfl_up((long long)x, o, 64);
+        if (lane >= o) x += y;
     }
-    const int64_t incl = part[t];
+    __syncthreads();                                       // part is free
+    if (lane == 63) part[wv] = x;
     __syncthreads();
-    return incl - v;
+    int64_t base = 0, tot = 0;
+    for (int w = 0; w < GRP_THREADS / 64; w++) {
+        const int64_t p = part[w];
+        base += w < wv ? p : 0;
+        tot += p;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) part[GRP_THREADS - 1] = tot;
+    __syncthreads();
+    return base + x - v;
 }
 
 __device__ __forceinline__ void d_groups(

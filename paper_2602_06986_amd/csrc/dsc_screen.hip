@@ -38,6 +38,10 @@ constexpr double TAU_DUP = 1e-9;     // 1 - |corr| at or below which two feature
 constexpr double KAPPA_MAX = 64.0;   // shifted-moment conditioning accepted without inflation
 constexpr double TAU_CANCEL = 1e-10; // add/sub with rms <= TAU_CANCEL * operand rms => constant
 constexpr double EPS64 = 1.1102230246251565e-16;
+// The exact pass rounds a pair's values to 64 bits before it centres them,
+// the pair screens do not: up to 3 eps rms / std between their scores, and
+// std > TAU_CONST rms.
+constexpr double VALUE_MARGIN = 3.0 * EPS64 / TAU_CONST;
 
 // ------------------------------------------------------------------ targets
 // One block per target: two-pass mean, centered and unit-norm copies.
@@ -143,8 +147,9 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
                                                    double* __restrict__ Vf, double* __restrict__ Rf,
                                                    double* __restrict__ Cf, double* __restrict__ mu,
                                                    double* __restrict__ mur, double* __restrict__ msq,
+                                                   double* __restrict__ css, double* __restrict__ cssr,
                                                    uint8_t* __restrict__ valid, uint8_t* __restrict__ cls,
-                                                   short2* __restrict__ ex, double narrow) {
+                                                   short2* __restrict__ ex) {
     const int c = c0 + blockIdx.x * 4 + wave_id();
     const int lane = threadIdx.x & 63;
     if (c >= c1) return;
@@ -170,14 +175,16 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
     rmax = wave_max(rmax);
     const int anyzero = __any(zero);
     const int anybad = __any(bad);
-    const double m = s / n;
-    double q = 0.0;
+    const double m = s / n, mr = sr / n;
+    double q = 0.0, qr = 0.0;
     for (int i = lane; i < n; i += 64) {
-        const double d = v[i] - m;
+        const double d = v[i] - m, dr = Rf[(int64_t)c * ldn + i] - mr;
         Cf[(int64_t)c * ldn + i] = d;
         q += d * d;
+        qr += dr * dr;
     }
     q = wave_sum(q);
+    qr = wave_sum(qr);
     // cancellation rule for sums and differences
     const int o = mop[c];
     double ff = 0.0, ab = 0.0;
@@ -200,10 +207,11 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
         if (cb[c] >= 0) ok = ok && valid[cb[c]];
         valid[c] = ok;
         mu[c] = m;
-        mur[c] = sr / n;
+        mur[c] = mr;
+        css[c] = q;
+        cssr[c] = qr;
         msq[c] = q / n + m * m;
-        cls[c] = (uint8_t)((q / n < (q / n + m * m) * narrow ? PC_NARROW : 0) |
-                           (isfinite(rmax) || anyzero ? 0 : PC_RCP) | (anyzero ? PC_ZERO : 0));
+        cls[c] = (uint8_t)((isfinite(rmax) || anyzero ? 0 : PC_RCP) | (anyzero ? PC_ZERO : 0));
         auto exponent = [](double v) { return (short)(v > 0.0 && v < INFINITY ? ilogb(v) : 0); };
         ex[c] = make_short2(exponent(vmax), exponent(rmax));
     }
@@ -218,12 +226,10 @@ struct MatArgs {
     const int8_t* op;
     const int32_t *ca, *cb;
     const int64_t* raw;
-    double *Vf, *Rf, *Cf, *mu, *mur, *msq;
+    double *Vf, *Rf, *Cf, *mu, *mur, *msq, *css, *cssr;
     uint8_t* valid;
     uint8_t* cls;             // range classes
     short2* ex;               // binary exponents of max |f| and max |1/f|
-    double narrow;            // share of the mean square below which a variance is narrow
-    int* route;               // form of the dense pairs
 };
 
 // grid (sample blocks, features of the level, problems)
@@ -240,37 +246,7 @@ __global__ __launch_bounds__(256) void k_mat_stats(ctab<MatArgs> A, int level) {
     DSC_GLOBAL(a.op); DSC_GLOBAL(a.ca); DSC_GLOBAL(a.cb); DSC_GLOBAL(a.Vf); DSC_GLOBAL(a.Rf); DSC_GLOBAL(a.Cf); DSC_GLOBAL(a.mu); DSC_GLOBAL(a.mur); DSC_GLOBAL(a.msq); DSC_GLOBAL(a.valid);
     if (level >= a.nlev) return;
     d_mat_stats(a.n, a.ldn, a.rs[level], a.rs[level + 1], a.op, a.ca, a.cb, a.Vf, a.Rf, a.Cf, a.mu,
-                a.mur, a.msq, a.valid, a.cls, a.ex, a.narrow);
-}
-
-// Form of each problem's dense pairs (one block per problem): the matrix
-// form when at most 1/256 of them are expected in the exact fix-up through
-// the operands' ranges: two narrow operands, whose unshifted product may
-// pass the matrix form's conditioning, or one whose reciprocal overflows.
-// The fix-up decides a few candidates a microsecond at n = 2000, so that
-// share costs less than the matrix form saves; data beyond it (every
-// column within 0.05 % of its mean, say) keeps the shifted vector form.
-// The choice is made on the device: it depends on the data and must hold
-// for a captured call.
-__global__ __launch_bounds__(256) void k_pair_route(ctab<MatArgs> A) {
-    const MatArgs& a = tab(A, blockIdx.x);
-    __shared__ int nn, nr;
-    if (threadIdx.x == 0) nn = nr = 0;
-    __syncthreads();
-    const int M = a.rs[a.nlev];
-    int narrow = 0, range = 0;
-    for (int c = threadIdx.x; c < M; c += 256) {
-        if (!a.valid[c]) continue;
-        narrow += (a.cls[c] & PC_NARROW) != 0;
-        range += (a.cls[c] & PC_RCP) != 0;
-    }
-    if (narrow) atomicAdd(&nn, narrow);
-    if (range) atomicAdd(&nr, range);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const double m = (double)M;
-        *a.route = (nn / m) * (nn / m) + nr / m <= 1.0 / 256.0 ? 1 : 0;
-    }
+                a.mur, a.msq, a.css, a.cssr, a.valid, a.cls, a.ex);
 }
 
 // Feature-major [M][ldn] -> sample-major [n][ldm] (padding left as is).
@@ -293,7 +269,7 @@ struct TrArgs {
     int n, M, ldn, ldm;
     const double* src[3];
     double* dst[3];
-    const int* route;         // skipped when *route is 1 (no vector-form kernel reads the copies); NULL: never
+    const unsigned* bad;      // skipped where the matrix form takes the pairs (no vector-form kernel reads the copies); NULL: never
 };
 
 // grid (sample tiles, feature tiles, 3 x problems)
@@ -301,7 +277,7 @@ __global__ void k_transpose(ctab<TrArgs> A) {
     const TrArgs& a = tab(A, blockIdx.z / 3);
     const int w = blockIdx.z % 3;
     DSC_GLOBAL(a.src[w]); DSC_GLOBAL(a.dst[w]);
-    if ((int)blockIdx.x * 32 >= a.n || (int)blockIdx.y * 32 >= a.M || (a.route && *a.route)) return;
+    if ((int)blockIdx.x * 32 >= a.n || (int)blockIdx.y * 32 >= a.M || (a.bad && *a.bad <= PROBE_MAX)) return;
     d_transpose(a.n, a.M, a.ldn, a.ldm, a.src[w], a.dst[w]);
 }
 
@@ -511,11 +487,57 @@ __device__ bool wave_exact_r(const Cand& c, const Ops& o, int n, int T,
 }
 
 // Exact scores of an explicit candidate list (operand features and unary
-// candidates of the streamed rung), written into the score slots.
+// candidates of the streamed rung), written into the score slots, and, after
+// them, the probes that decide for the matrix form of the pairs.
 struct ListItem {
     int64_t id;
     int32_t kind, op, ca, cb;
 };
+constexpr int32_t LI_PROBE = 4;          // kind past the candidates': op (ca, cb), of weight id
+
+// What the items read and write for the matrix form (all NULL where it does not run).
+struct PairSums {
+    double* fy;
+    const double *mu, *mur;
+    const short2* ex;
+    const uint8_t* cls;
+    unsigned* bad;
+    int TP;
+};
+
+// A probe: whether a pair candidate's sums cancel (K beyond PAIR_KAPPA, from
+// up to 256 samples) or its values leave the matrix form's range.
+__device__ __forceinline__ void d_probe(const ListItem it, Ops o, const uint8_t* __restrict__ valid, int n,
+                                        const PairSums& q) {
+    const int i = it.ca, j = it.cb, op = it.op, lane = threadIdx.x & 63;
+    if (!valid[i] || !valid[j]) return;
+    const bool ri = op == OP_RDIV, rj = op == OP_DIV;
+    if ((ri ? q.cls[i] : rj ? q.cls[j] : 0) & PC_ZERO) return;                // never finite
+    const short2 xi = q.ex[i], xj = q.ex[j];
+    // the operand that the matrix form centres (1/b of a quotient a/b) and the other one
+    const double* a = rj ? o.Rf + (int64_t)j * o.ldn : (ri ? o.Rf : o.Vf) + (int64_t)i * o.ldn;
+    const double* b = o.Vf + (int64_t)(rj ? i : j) * o.ldn;
+    const double A = rj ? q.mur[j] : ri ? q.mur[i] : q.mu[i], B = q.mu[rj ? i : j];
+    const int m = min(n, 256);
+    double s1 = 0.0, s2 = 0.0, t = 0.0, qa = 0.0, qb = 0.0;
+    for (int k = lane; k < m; k += 64) {
+        const int64_t s = (int64_t)k * n / m;
+        const double x = a[s] - A, y = b[s] - B;
+        const double f1 = op < OP_MUL ? x : A * y, f2 = op == OP_ADD ? y : op == OP_SUB ? -y : x * b[s];
+        s1 += f1 + f2;
+        s2 += (f1 + f2) * (f1 + f2);
+        t += f1 * f1 + f2 * f2;
+        qa += x * x;
+        qb += y * y;
+    }
+    s1 = wave_sum(s1);
+    const double v = wave_sum(s2) - s1 * (s1 / m);
+    t = wave_sum(t);
+    if (op >= OP_MUL) t += fabs(s1) / m * sqrt(wave_sum(qa)) * sqrt(wave_sum(qb));
+    const bool range = op < OP_MUL ? max(xi.x, xj.x) <= PC_EMAX && max(xi.x, xj.x) >= PC_EMIN
+                                   : pair_range(ri ? xi.y : xi.x, rj ? xj.y : xj.x);
+    if (lane == 0 && !(range && t <= PAIR_KAPPA * v)) atomicAdd(q.bad, (unsigned)it.id);
+}
 
 template <int TMAX>
 __device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uint8_t* __restrict__ valid,
@@ -524,18 +546,21 @@ __device__ __forceinline__ void d_score_item(const ListItem it, Ops o, const uin
                                              double* __restrict__ scores, unsigned* nok,
                                              uint8_t* __restrict__ r2v, double* __restrict__ r2m,
                                              double* __restrict__ r2q, int64_t off2, int64_t off3,
-                                             double* __restrict__ fy, int TP) {
+                                             const PairSums& ps) {
+    if (it.kind == LI_PROBE) {
+        d_probe(it, o, valid, n, ps);
+        return;
+    }
     Cand c{it.kind, it.op, it.ca, it.cb, OP_NONE, -1, -1};
     bool ok = valid[c.ca] && (c.kind < 2 || valid[c.cb]);
-    if (c.kind == 0) ok = valid[c.ca];
     double r[TMAX], mean = 0.0, msq = 0.0, sxx = 0.0;
     ok = ok && wave_exact_r<TMAX>(c, o, n, T, Yc, syy, r, &mean, &msq, &sxx);
     if ((threadIdx.x & 63) == 0) {
-        // an operand feature's sums (f - mean) y_t, for the matrix form's sums and differences
-        if (fy && ok && it.kind == 0)
+        // an operand feature's sums (f - mean) y_t
+        if (ps.fy && ok && it.kind == 0)
 #pragma unroll
             for (int t = 0; t < TMAX; t++)
-                if (t < TP) fy[(int64_t)it.ca * TP + t] = t < T ? r[t] * sqrt(sxx) : 0.0;
+                if (t < ps.TP) ps.fy[(int64_t)it.ca * ps.TP + t] = t < T ? r[t] * sqrt(sxx) : 0.0;
         if (!ok) {
             for (int t = 0; t < (mode ? 1 : T); t++) scores[(int64_t)t * N + it.id] = __longlong_as_double(-1LL);
             return;
@@ -571,14 +596,14 @@ __device__ __forceinline__ void d_score_list(const ListItem* __restrict__ items,
                                                     unsigned long long* __restrict__ nscored,
                                                     uint8_t* __restrict__ r2v, double* __restrict__ r2m,
                                                     double* __restrict__ r2q, int64_t off2, int64_t off3,
-                                                    double* __restrict__ fy, int TP) {
+                                                    const PairSums& ps) {
     // the block's valid candidates are counted in LDS and added once
     __shared__ unsigned nok;
     if (threadIdx.x == 0) nok = 0u;
     __syncthreads();
     const int64_t w = (int64_t)blockIdx.x * 4 + wave_id();
     if (w < m) d_score_item<TMAX>(items[w], o, valid, n, T, mode, Yc, syy, N, scores, &nok, r2v, r2m, r2q,
-                            off2, off3, fy, TP);
+                            off2, off3, ps);
     __syncthreads();
     if (threadIdx.x == 0 && nok) atomicAdd(nscored, (unsigned long long)nok);
 }
@@ -596,8 +621,7 @@ struct ListArgs {
     uint8_t* r2v;
     double *r2m, *r2q;
     int64_t off2, off3;
-    double* fy;               // or NULL
-    int TP;
+    PairSums ps;
 };
 
 // grid (item blocks of 4, problems); TM: the most targets (padded) of any
@@ -610,7 +634,7 @@ __global__ __launch_bounds__(256, 4) void k_score_list(ctab<ListArgs> A) {
     DSC_GLOBAL(a.items); DSC_GLOBAL(a.o.Vf); DSC_GLOBAL(a.o.Rf); DSC_GLOBAL(a.valid); DSC_GLOBAL(a.Yc); DSC_GLOBAL(a.syy); DSC_GLOBAL(a.scores); DSC_GLOBAL(a.nscored);
     if ((int64_t)blockIdx.x * 4 >= a.m) return;
     d_score_list<TM>(a.items, a.m, a.o, a.valid, a.n, a.T, a.mode, a.Yc, a.syy, a.N, a.scores, a.nscored,
-                 a.r2v, a.r2m, a.r2q, a.off2, a.off3, a.fy, a.TP);
+                 a.r2v, a.r2m, a.r2q, a.off2, a.off3, a.ps);
 }
 
 // --------------------------------------------------- streamed pair screen
@@ -840,13 +864,13 @@ template <int OPS, int J, int TP, bool LIST, bool QUEUE>
 __global__ __launch_bounds__(64 * pair_split<LIST>()) void k_screen_pairs(ctab<PairArgs> A,
                                                       const int4* __restrict__ tiles, int64_t n_tiles,
                                                       unsigned long long* __restrict__ queue,
-                                                      const int* __restrict__ routes, int one) {
+                                                      const unsigned* __restrict__ bad, int one) {
     if (!QUEUE) {
-        // a problem that the matrix form has (routes: one flag per problem;
-        // one: a single problem, its flag read without waiting for the tile).
+        // a problem that the matrix form has (bad: one weight per problem;
+        // one: a single problem, its weight read without waiting for the tile).
         // Ahead of any barrier, past which the operands' scalar loads become
         // vector loads and the kernel takes twice as long
-        if (!LIST && routes && routes[one ? 0 : tiles[blockIdx.x].x]) return;
+        if (!LIST && bad && bad[one ? 0 : tiles[blockIdx.x].x] <= PROBE_MAX) return;
         pair_tile<OPS, J, TP, LIST>(A, tiles[blockIdx.x]);
         return;
     }
@@ -3020,7 +3044,7 @@ static int max_J(int TP) { return TP == 1 ? 4 : TP == 2 ? 2 : 1; }
 
 template <int OPS, int J, int TP>
 static void launch_pairs_t(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list,
-                           unsigned long long* queue, const int* routes, int one, hipStream_t st) {
+                           unsigned long long* queue, const unsigned* bad, int one, hipStream_t st) {
     if (n == 0) return;
     if (list) {
         k_screen_pairs<OPS, 1, TP, true, false><<<(unsigned)n, 64 * pair_split<true>(), 0, st>>>(A, tiles, n, nullptr, nullptr, 0);
@@ -3028,39 +3052,39 @@ static void launch_pairs_t(ctab<PairArgs> A, const int4* tiles, int64_t n, bool 
         const unsigned g = (unsigned)std::min<int64_t>(n, 8 * 256);
         k_screen_pairs<OPS, J, TP, false, true><<<g, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, queue, nullptr, 0);
     } else {                                   // one block per tile
-        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr, routes, one);
+        k_screen_pairs<OPS, J, TP, false, false><<<(unsigned)n, 64 * pair_split<false>(), 0, st>>>(A, tiles, n, nullptr, bad, one);
     }
 }
 
 template <int OPS>
 static void launch_pairs_ops(ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
-                             int J, unsigned long long* q, const int* routes, int one, hipStream_t st) {
+                             int J, unsigned long long* q, const unsigned* bad, int one, hipStream_t st) {
     switch (TP) {
     case 1:
-        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, routes, one, st);
-        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, routes, one, st);
-        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, routes, one, st);
+        if (J == 4) launch_pairs_t<OPS, 4, 1>(A, tiles, n, list, q, bad, one, st);
+        else if (J == 2) launch_pairs_t<OPS, 2, 1>(A, tiles, n, list, q, bad, one, st);
+        else launch_pairs_t<OPS, 1, 1>(A, tiles, n, list, q, bad, one, st);
         break;
     case 2:
-        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, routes, one, st);
-        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, routes, one, st);
+        if (J == 2) launch_pairs_t<OPS, 2, 2>(A, tiles, n, list, q, bad, one, st);
+        else launch_pairs_t<OPS, 1, 2>(A, tiles, n, list, q, bad, one, st);
         break;
-    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, routes, one, st); break;
-    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, routes, one, st); break;
-    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, routes, one, st); break;
+    case 4: launch_pairs_t<OPS, 1, 4>(A, tiles, n, list, q, bad, one, st); break;
+    case 8: launch_pairs_t<OPS, 1, 8>(A, tiles, n, list, q, bad, one, st); break;
+    default: launch_pairs_t<OPS, 1, 16>(A, tiles, n, list, q, bad, one, st); break;
     }
 }
 
 // queue: a zeroed device counter to run the dense tiles as one persistent
-// launch over a work queue, or NULL for one block per tile.  routes: the
-// problems' forms, where the matrix form may have taken some (no queue).
+// launch over a work queue, or NULL for one block per tile.  bad: the
+// problems' probe weights, where the matrix form may have taken some (no queue).
 static void launch_pairs(int OPS, ctab<PairArgs> A, const int4* tiles, int64_t n, bool list, int TP,
                          int J, hipStream_t st, unsigned long long* queue = nullptr,
-                         const int* routes = nullptr, int one = 0) {
+                         const unsigned* bad = nullptr, int one = 0) {
     switch (OPS) {
-    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
-    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
-    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, routes, one, st); break;
+    case 31: launch_pairs_ops<31>(A, tiles, n, list, TP, J, queue, bad, one, st); break;
+    case 28: launch_pairs_ops<28>(A, tiles, n, list, TP, J, queue, bad, one, st); break;
+    case 3: launch_pairs_ops<3>(A, tiles, n, list, TP, J, queue, bad, one, st); break;
     default: DSC_FAIL(DISCOVER_E_UNSUPPORTED, "operator class %d", OPS);
     }
 }
@@ -3116,9 +3140,10 @@ struct Plan {
     int8_t* mat_op = nullptr;
     int32_t *mat_a = nullptr, *mat_b = nullptr;
     ListItem* items = nullptr;
-    int64_t n_items = 0;
+    int64_t n_items = 0;                      // candidates among them
+    int64_t n_items_mm = 0;                   // and with the probes
     std::vector<int2> dtilesJ[3];             // dense (jc0, ic0) tiles for J = 1, 2, 4
-    std::vector<int2> mmtiles[2];             // matrix form: (i0, j0) of 16 x 16 and of big tiles
+    std::vector<int2> mmtiles;                // matrix form: (i0, j0) of 16 x 16 pairs
     uint32_t dense_ops = 0;
     int dense_cls = 0;
     int2* ptiles = nullptr;                   // (j, i0) tiles of one j for the precision form
@@ -3193,10 +3218,12 @@ static std::shared_ptr<Plan> get_plan(discover_ctx* ctx, const discover_problem&
                     items.push_back({unary_id(sd, R, o, sp.mat_raw[c]), 1, o, c, -1});
         }
     }
-    P->items = P->up(items);
-    P->n_items = (int64_t)items.size();
+    P->n_items = P->n_items_mm = (int64_t)items.size();
     P->sm.s3 = P->sm.n = sp.n_raw();                     // slot = ID (rung 3 below)
-    if (!R) return ctx->plans[key] = P, P;
+    if (!R) {
+        P->items = P->up(items);
+        return ctx->plans[key] = P, P;
+    }
     uint32_t bin = 0;
     for (int o = OP_ADD; o <= OP_RDIV; o++)
         if (sd.block[R][o] >= 0) bin |= 1u << (o - OP_ADD);
@@ -3217,14 +3244,28 @@ static std::shared_ptr<Plan> get_plan(discover_ctx* ctx, const discover_problem&
                 for (int32_t i0 = 0; i0 < ilim; i0 += 64) tiles.push_back(make_int2(j, i0));
             }
         }
-        for (int big = 0; big < 2; big++) {
-            int rows, cols;
-            pairs_mm_tile(P->TP, big ? 2 : 0, rows, cols);
-            for (int32_t j0 = jc0; j0 < jc1; j0 += cols) {
-                const int32_t ilim = std::min<int32_t>(i_end, std::min<int32_t>(j0 + cols, jc1) - 1);
-                for (int32_t i0 = 0; i0 < ilim; i0 += rows) P->mmtiles[big].push_back(make_int2(i0, j0));
-            }
+        for (int32_t j0 = jc0; j0 < jc1; j0 += 16) {
+            const int32_t ilim = std::min<int32_t>(i_end, std::min<int32_t>(j0 + 16, jc1) - 1);
+            for (int32_t i0 = 0; i0 < ilim; i0 += 16) P->mmtiles.push_back(make_int2(i0, j0));
         }
+        // probes spread over all candidates
+        std::vector<int64_t> ends;
+        int64_t tot = 0;
+        for (int32_t j = jc0; j < jc1; j++) ends.push_back(tot += std::min<int32_t>(i_end, j));
+        std::vector<int> ops;
+        for (int o = 0; o < 5; o++)
+            if ((P->dense_ops >> o) & 1u) ops.push_back(OP_ADD + o);
+        const int64_t all = tot * (int64_t)ops.size(), np = std::min<int64_t>(all, PAIR_PROBES);
+        for (int64_t t = 0; t < np; t++) {
+            uint64_t z = (uint64_t)(t + 1) * 0x9E3779B97F4A7C15ull;            // SplitMix64
+            z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+            z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+            const int64_t c = np == all ? t : (int64_t)((z ^ (z >> 31)) % (uint64_t)all), e = c % tot;
+            const int64_t q = std::upper_bound(ends.begin(), ends.end(), e) - ends.begin();
+            items.push_back({PAIR_PROBES / np, LI_PROBE, ops[(size_t)(c / tot)], (int32_t)(e - (q ? ends[q - 1] : 0)),
+                             jc0 + (int32_t)q});
+        }
+        P->n_items_mm = (int64_t)items.size();
         std::vector<int2> pt;
         for (int32_t j = jc0; j < jc1; j++) {
             const int32_t ilim = std::min<int32_t>(i_end, j);
@@ -3233,6 +3274,7 @@ static std::shared_ptr<Plan> get_plan(discover_ctx* ctx, const discover_problem&
         P->ptiles = P->up(pt);
         P->n_ptiles = (int64_t)pt.size();
     }
+    P->items = P->up(items);
     std::vector<int32_t> il;
     if (P->list_ops) {
         std::map<std::string, std::vector<int32_t>> by_unit;
@@ -3295,8 +3337,9 @@ struct Problem {
     uint8_t* valid;
     uint8_t* cls;                             // operand range classes
     short2* ex;                               // operand exponents
-    int* route;                               // form of the dense pairs
+    double *css, *cssr;                       // centred square sums of f and 1/f
     double* fy;                               // operand features' sums with the targets
+    unsigned* bad;                            // weight of the probes that cancel
     unsigned long long* ctr;                  // [0] bad target (int), [1] fix count, [2] scored, [3] rung-3 fix count
     int64_t *fix_ids, *fix_ids3;
     uint8_t* r2v = nullptr;                   // rung-2 operand statistics (streamed rung 3)
@@ -3364,7 +3407,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         auto& v = o[b];
         auto& u = oo[b];
         for (int k = 0; k < 3; k++) u.push_back(ao.add(Mc * ldn * 8));          // Vf Rf Cf
-        for (int k = 0; k < 3; k++) u.push_back(ao.add(Mc * 8));                // mu mur msq
+        for (int k = 0; k < 5; k++) u.push_back(ao.add(Mc * 8));                // mu mur msq css cssr
         u.push_back(ao.add(Mc));                                               // valid
         u.push_back(ao.add(Mc));                                               // cls
         u.push_back(ao.add(Mc * 4));                                           // ex
@@ -3387,7 +3430,7 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         v.push_back(ar.add(r3 ? r3_pstat_bytes(*r3, P.TP) : 8));                  // partner ranges, sums
         v.push_back(ar.add(P.pairs ? Mc * P.TP * 8 : 8));                         // fy
     }
-    const size_t routes = ao.add((size_t)nb * sizeof(int));
+    const size_t bad = ar.add((size_t)nb * sizeof(unsigned));
     char* base = (char*)ctx->raw("scr_arena", ar.total);
     char* obase = (char*)ctx->raw("scr_ops" + ctx->ops_tag, ao.total);
     // counters stay apart from the shared arena: a captured run checks the
@@ -3403,10 +3446,11 @@ static void layout_problems(discover_ctx* ctx, const discover_problem* probs, in
         auto ato = [&](void) { return obase + u[qo++]; };
         P.Vf = (double*)ato(); P.Rf = (double*)ato(); P.Cf = (double*)ato();
         P.mu = (double*)ato(); P.mur = (double*)ato(); P.msq = (double*)ato();
+        P.css = (double*)ato(); P.cssr = (double*)ato();
         P.valid = (uint8_t*)ato();
         P.cls = (uint8_t*)ato();
         P.ex = (short2*)ato();
-        P.route = (int*)(obase + routes) + b;
+        P.bad = (unsigned*)(base + bad) + b;
         P.Vs = (double*)ato(); P.Rs = (double*)ato(); P.Cs = (double*)ato();
         P.Yc = (double*)at(); P.Yn = (double*)at(); P.syy = (double*)at(); P.ysum = (double*)at();
         P.scores = (double*)at();
@@ -3548,6 +3592,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         fills.push_back(fill_seg(P.scores, (size_t)P.Tl * P.N * 8, 0xFFFFFFFFu));
         if (P.r2v) fills.push_back(fill_seg(P.r2v, ((size_t)P.plan->sp.d.L[2] + 3) & ~size_t(3), 0u));
     }
+    fills.push_back(fill_seg(PS[0].bad, nb * sizeof(unsigned), 0u));
     if (more_fills) more_fills(fills);                  // e.g. the first selection round's counters
     fill_all(ctx, "scr_fills", fills, st);
     // 2. targets
@@ -3573,11 +3618,10 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.X = probs[b].X; a.ldx = probs[b].ldx;
         a.op = pl.mat_op; a.ca = pl.mat_a; a.cb = pl.mat_b; a.raw = pl.mat_raw;
         a.Vf = P.Vf; a.Rf = P.Rf; a.Cf = P.Cf; a.mu = P.mu; a.mur = P.mur; a.msq = P.msq;
+        a.css = P.css; a.cssr = P.cssr;
         a.valid = P.valid;
         a.cls = P.cls;
         a.ex = P.ex;
-        a.narrow = 4.0 / pair_kappa(P.n);
-        a.route = P.route;
         nlev = std::max(nlev, a.nlev);
         nmax = std::max(nmax, P.n);
         for (int r = 0; r < a.nlev; r++) wmax[r] = std::max(wmax[r], a.rs[r + 1] - a.rs[r]);
@@ -3603,32 +3647,35 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             k_mat_values<<<dim3((unsigned)cdiv(nmax, 256), (unsigned)wmax[r], nb), 256, 0, st>>>(dma, r);
             k_mat_stats<<<dim3((unsigned)cdiv(wmax[r], 4), nb), 256, 0, st>>>(dma, r);
         }
-        if (std::any_of(PS.begin(), PS.end(), [](const Problem& P) { return P.pairs && P.plan->dense_ops; }))
-            k_pair_route<<<nb, 256, 0, st>>>(dma);
         check_launch("k_mat");
     }
-    // 4. exact list: operand features and unary candidates of the streamed rung
+    // 4. exact list: operand features and unary candidates of the streamed rung,
+    // and what the matrix form of the dense pairs needs (where it may run: the
+    // vector form's tile width and schedule can be forced, as can the precision form)
+    const bool forced = prm.tile_j > 0 || prm.sched != 0;
+    const bool mm = !forced && (prm.precision == DISCOVER_FP64 || prm.lp_pairs <= 0);
     std::vector<ListArgs> la(nb);
     int64_t mmax = 0;
+    int Tm = 1;
     for (int b = 0; b < nb; b++) {
         const Problem& P = PS[b];
         const Plan& pl = *P.plan;
         const SpaceDev& sd = pl.sp.d;
         ListArgs& a = la[b];
         a = ListArgs{};
-        a.items = pl.items; a.m = pl.n_items; a.o = P.ops(); a.valid = P.valid;
+        a.items = pl.items; a.m = mm ? pl.n_items_mm : pl.n_items; a.o = P.ops(); a.valid = P.valid;
         a.n = P.n; a.T = P.T; a.mode = prm.score_mode; a.Yc = P.Yc; a.syy = P.syy; a.N = P.N;
         a.scores = P.scores; a.nscored = P.ctr + 2;
         a.r2v = P.r2v; a.r2m = P.r2m; a.r2q = P.r2q;
         a.off2 = pl.sp.stream3 ? sd.off[2] : 0;
         a.off3 = pl.sp.stream3 ? sd.off[3] : 0;
-        a.fy = P.pairs ? P.fy : nullptr; a.TP = P.TP;
+        if (mm && P.pairs && pl.dense_ops)
+            a.ps = PairSums{P.fy, P.mu, P.mur, P.ex, P.cls, P.bad, P.TP};
+        Tm = std::max(Tm, P.TP);
         mmax = std::max(mmax, a.m);
     }
     {
         KTimer kt(ctx, st, "screen_list");
-        int Tm = 1;
-        for (const ListArgs& x : la) Tm = std::max(Tm, x.TP);
         const dim3 grid((unsigned)cdiv(mmax, 4), nb);
         const ctab<ListArgs> d = ct(ctx->upload("scr_list", la, st));
         if (Tm <= 1) k_score_list<1><<<grid, 256, 0, st>>>(d);
@@ -3644,8 +3691,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         const Problem& P = PS[b];
         if (!P.pairs) continue;
         // (list tiles, the precision form and forced vector tiles always read the copies)
-        const bool mm_only = prm.precision == DISCOVER_FP64 && prm.tile_j == 0 && prm.sched == 0 && !P.plan->list_ops;
-        tr.push_back(TrArgs{P.n, P.Mc, P.ldn, P.ldm, {P.Vf, P.Rf, P.Cf}, {P.Vs, P.Rs, P.Cs}, mm_only ? P.route : nullptr});
+        const bool mm_only = mm && prm.precision == DISCOVER_FP64 && P.plan->dense_ops && !P.plan->list_ops;
+        tr.push_back(TrArgs{P.n, P.Mc, P.ldn, P.ldm, {P.Vf, P.Rf, P.Cf}, {P.Vs, P.Rs, P.Cs}, mm_only ? P.bad : nullptr});
         tn = std::max(tn, P.n);
         tm = std::max(tm, P.Mc);
     }
@@ -3654,10 +3701,9 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                       dim3(32, 8), 0, st>>>(ct(ctx->upload("scr_tr", tr, st)));
         check_launch("k_transpose");
     }
-    // 6. pair kernels.  The vector form's tile width and schedule can be
-    // forced; else each problem takes the matrix form or, where its data
-    // need it, the vector form (decided on the device).
-    const bool forced = prm.tile_j > 0 || prm.sched != 0;
+    // 6. pair kernels.  Unless the vector form is forced, each problem takes the
+    // matrix form or, where its data need it, the vector form (decided on the
+    // device).
     std::vector<PairArgs> pa(nb);
     for (int b = 0; b < nb; b++) {
         const Problem& P = PS[b];
@@ -3678,8 +3724,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         a.r2v = P.r2v; a.r2m = P.r2m; a.r2q = P.r2q; a.msq = P.msq;
         a.ilist = pl.ilist;
         a.opmask = pl.dense_ops;
-        a.cls = P.cls; a.ex = P.ex; a.kappa = pair_kappa(P.n); a.fy = P.fy;
-        a.route = P.route;
+        a.cls = P.cls; a.ex = P.ex; a.bad = P.bad;
+        a.css = P.css; a.cssr = P.cssr; a.fy = P.fy;
     }
     const ctab<PairArgs> dpa = ct(ctx->upload("scr_pairs", pa, st));
     const std::vector<int> order = by_weight(PS);
@@ -3693,33 +3739,29 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             while (J * 2 <= std::min(prm.tile_j, max_J(TP))) J *= 2;
         }
         if (!forced) {
-            // matrix form.  Tile shape by the work items (tiles x operator sets)
-            // and the products of one 16 x 16 tile (16-sample chunks x (2 +
-            // targets)): large tiles once they give every SIMD a wave, else one
-            // 16 x 16 tile per wave, or per block where tiles are few or long.
-            // Measured us for a tile per block, per wave, large: 234 items of 378
-            // products 46, 75, 125; 513 of 342 91, 133, 135; 513 of 1250 165, 343,
-            // 539; 1785 of 630 217, 233, 294; but 513 of 57 42, 31, 73; 1053 of 78
-            // 70, 44, 50; 1785 of 128 126, 68, 111; 6834 of 375 (1 target) 577, 466,
-            // 426; of 1250 (8 targets) 1434, 1415, 1380; of 500 and 750 (2 and 4
-            // targets, whose larger tiles lost) 571, 517, 533 and 757, 727, 779.
-            int64_t nbig = 0, nsml = 0, prod = 0;
+            // matrix form.  One work item (tile x operator set) per wave, or per
+            // block where items are few or long: by their number and the products of
+            // one (16-sample chunks x (3 + targets)).  Measured us per block, per
+            // wave: 102 items of 28, 77, 500 and 1375 products 15, 23; 21, 30; 41,
+            // 130; 126, 228; 402 of 28, 133 and 315 30, 26; 37, 44; 49, 92; 1050 of
+            // 52, 252 and 352 70, 44; 90, 108; 123, 129; 1302 of 128 89, 66; 2967 of
+            // 128 and 2375 171, 100; 1378, 1549; 7026 of 128, 500, 625, 875 and 1375
+            // 365, 179; 564, 560; 689, 696; 900, 892; 1723, 1372.
+            int64_t items = 0, prod = 0;
             for (int b : mem) {
-                const int64_t t = 3 * (int64_t)PS[b].plan->mmtiles[0].size();
-                nbig += 3 * (int64_t)PS[b].plan->mmtiles[1].size();
-                nsml += t;
-                prod += t * cdiv(PS[b].n, 16) * (TP + 2);
+                const int64_t t = 3 * (int64_t)PS[b].plan->mmtiles.size();
+                items += t;
+                prod += t * cdiv(PS[b].n, 16) * (TP + 3);
             }
-            const int shape = (TP == 1 || TP == 8) && nbig >= 1024 ? 2
-                              : nsml <= 256 || (nsml < 2048 && prod >= 256 * nsml) ? 0 : 1;
+            const bool split = items <= 256 || (items < 4096 && prod >= items * (items / 8 + 64));
             std::vector<int4> work;
             for (int b : mem) {
                 const uint32_t ops = PS[b].plan->dense_ops;
-                for (const int2& t : PS[b].plan->mmtiles[shape == 2 ? 1 : 0])
+                for (const int2& t : PS[b].plan->mmtiles)
                     for (int sel = 0; sel < 3; sel++)
                         if (ops & (sel == 0 ? 7u : sel == 1 ? 8u : 16u)) work.push_back(make_int4(b, t.x, t.y, sel));
             }
-            launch_pairs_mm(dpa, ctx->upload("scr_mmwork" + gi, work, st), (int64_t)work.size(), TP, shape, st);
+            launch_pairs_mm(dpa, ctx->upload("scr_mmwork" + gi, work, st), (int64_t)work.size(), TP, split, st);
             // what the matrix form leaves: two operand features per wave for one
             // target (the width that timing chose for tables of 16 to 20 features)
             J = std::min(2, max_J(TP));
@@ -3747,7 +3789,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         }
         const int4* dt = ctx->upload("scr_dtiles" + gi, tiles, st);
         launch_pairs(cls, dpa, dt, (int64_t)tiles.size(), false, TP, J, st, useq ? queue : nullptr,
-                     forced ? nullptr : PS[0].route, nb == 1);
+                     forced ? nullptr : PS[0].bad, nb == 1);
         check_launch("k_screen_pairs");
     };
     // 6a. precision form: per problem, BF16/FP16 screening with FP64 guard-band
@@ -4259,7 +4301,7 @@ static void generate_screen_once(discover_ctx* ctx, const discover_problem* prob
         s.n_raw = P.plan->sp.n_raw();
         s.n_unit_valid = P.plan->sp.n_unit_valid;
         s.tile_j = P.tile_j;
-        margin[b] = std::max(4.0 * P.n * EPS64 * KAPPA_MAX, P.pairs && P.plan->dense_ops ? PAIR_MARGIN : 0.0);
+        margin[b] = 4.0 * P.n * EPS64 * KAPPA_MAX + (P.pairs ? VALUE_MARGIN : 0.0);
         if (prm.precision != DISCOVER_FP64) {
             s.guard_band = lowprec_margin(prm.precision, P.n);
             // rung 3 in BF16 carries its FP32 moments' error as well

@@ -78,7 +78,7 @@ struct R3Launch {
     const R3Plan* plan;
     int n, ldn, TP, T, mode;
     const double *Vf, *Rf, *Cf, *mu, *msq;
-    const uint8_t* valid;
+    const uint8_t *valid, *cls;       // of the operand features: validity, range classes (PC_*)
     const int64_t* mat_raw;
     const double *Yn, *ysum;
     const uint8_t* r2v;

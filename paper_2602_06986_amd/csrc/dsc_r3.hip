@@ -21,6 +21,7 @@
 // a larger kappa, or whose values might overflow, are listed for the exact
 // two-pass fix-up; candidates whose values are certainly not finite (a
 // division by an exact zero) are left invalid.
+#include "dsc_pairs.h"
 #include "dsc_r3.h"
 
 #include <algorithm>
@@ -276,7 +277,7 @@ struct R3mArgs {
     const double* pstat;
     int pe;
     uint32_t ops;
-    const uint8_t* valid;
+    const uint8_t *valid, *cls;
     const int64_t* mat_raw;
     const uint8_t* r2v;
     const double* ysum;
@@ -681,6 +682,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     bool rok;
     int64_t j2;
     int oo, rkind;
+    bool rzero;                                          // 1/g is infinite through a zero operand
     const double* b1;
     const double* b2;
     unsigned ri1[4], ri2[4];
@@ -696,6 +698,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
         rok = rok && g.r2v[j2 - g.sd.off[2]];
         int i1, i2;
         rkind = r3_rows_lp(g.Vf, g.Rf, rok ? k : 0, rok ? l : 0, op2, hk, b1, b2, i1, i2);
+        rzero = hk && rkind == RK_PROD && (((b1 == g.Rf ? g.cls[i1] : 0) | (b2 == g.Rf ? g.cls[i2] : 0)) & PC_ZERO);
 #pragma unroll
         for (int h = 0; h < 4; h++) {
             ri1[h] = (unsigned)__shfl(i1, 4 * h + kq, 64);
@@ -704,7 +707,11 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     }
     r3_f32x4 s1[CT], s2[CT], c1[CT], c2[CT];              // moments: a_h x_h and cross terms
     r3_f32x4 pa[CT][TP];
-    float hmx = 0.0f;                                    // div tiles: max |1/g| of the lane's samples
+    // div tiles: max |1/g| of the lane's samples of row l/16 + 4h, and whether
+    // g itself has a zero among them (bit h; for sums and unary values, whose
+    // reciprocal is taken here)
+    double hm[4] = {0.0, 0.0, 0.0, 0.0};
+    unsigned hz = 0;
 #pragma unroll
     for (int c = 0; c < CT; c++) {
         s1[c] = r3_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -796,8 +803,13 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
 #pragma unroll
             for (int e = 0; e < 2; e++) {
                 double x = v[2 * h + e];
-                if (hk && kind != RK_PROD) x = r3_rcp(x);
-                if (tail && 32 * ch + 2 * r16 + e >= g.n) x = 0.0;
+                const bool past = tail && 32 * ch + 2 * r16 + e >= g.n;
+                if (hk && kind != RK_PROD) {
+                    if (x == 0.0 && !past) hz |= 1u << h;
+                    x = r3_rcp(x);
+                }
+                if (past) x = 0.0;
+                if (hk) hm[h] = fabs(x) > hm[h] ? fabs(x) : hm[h];   // NaN leaves it unchanged
                 w[e] = (float)x;
             }
             *(r3_f32x2*)(tw + h * 512 + (tws ^ (32 * h))) = w;
@@ -807,9 +819,6 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
         float vf[8];
         *(r3_f32x4*)vf = *(const r3_f32x4*)(tr + trs);
         *(r3_f32x4*)(vf + 4) = *(const r3_f32x4*)(tr + (trs ^ 16));
-#pragma unroll
-        for (int e = 0; e < 8; e++)
-            if (hk) hmx = fmaxf(hmx, fabsf(vf[e]));      // NaN leaves it unchanged
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             unsigned h, l;
@@ -912,9 +921,25 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     default: run(std::integral_constant<int, RK_OTHER>{}); break;
     }
     if (!active) return;
+    // of rows 4 kq + e: max |1/g|, and whether g has a zero
+    double hx4[4] = {0.0, 0.0, 0.0, 0.0};
+    bool gz4[4] = {false, false, false, false};
     if (hk) {
-        hmx = fmaxf(hmx, __shfl_xor(hmx, 16, 64));
-        hmx = fmaxf(hmx, __shfl_xor(hmx, 32, 64));
+        uint64_t z = 0;                                  // of rows 4 kq .. 4 kq + 3: 16 bits each
+#pragma unroll
+        for (int h = 0; h < 4; h++) {
+            for (int o = 8; o > 0; o >>= 1) hm[h] = fmax(hm[h], __shfl_xor(hm[h], o, 64));
+            const uint64_t m = __builtin_amdgcn_ballot_w64((hz >> h) & 1u);
+            z = kq == h ? m : z;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                const double x = __shfl(hm[h], 16 * e, 64);          // row 4 h + e
+                hx4[e] = kq == h ? x : hx4[e];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+            gz4[e] = __shfl((int)rzero, 4 * kq + e, 64) != 0 || ((z >> (16 * e)) & 0xFFFFu) != 0;
     }
     const double nn = (double)g.n;
     unsigned cnt = 0;
@@ -938,7 +963,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
             const int i = 4 * kq + e;                      // row of slot e
             const bool ok = __shfl((int)rok, i, 64) != 0 && colok;
             const int64_t gj = __shfl(j2, i, 64);
-            const double hx = hk ? (double)__shfl(hmx, i, 64) : 0.0;
+            const double hx = hx4[e];
             if (!ok) continue;
             // max |g| <= sqrt(sum g^2) = sqrt(n E[g^2]) (E[g^2] recorded by the
             // rung-2 screen; 1 % margin for its rounding): only compared with
@@ -953,7 +978,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
                 sure = rmx * xmx < R3_BIG;
                 amx = rmx; fmx = rmx * xmx; bmx = xmx;
             } else if (op3 == OP_DIV) {
-                // (1/g beyond FP32, a zero of g among it: the fix-up decides)
+                if (gz4[e]) continue;                      // x / 0: not finite
                 sure = rmn >= R3_TINY && xmx < R3_BIG * rmn;
                 amx = hx; fmx = xmx * hx; bmx = xmx;
             } else {
@@ -1199,7 +1224,7 @@ void launch_r3(discover_ctx* ctx, const R3Launch& a, hipStream_t st) {
         m.grec = P.grec; m.n_grec = P.n_grec; m.coldesc = P.coldesc; m.n_gct = P.n_gct;
         m.NQ = NQ; m.n = a.n; m.T = a.T; m.mode = a.mode; m.ldn = a.ldn; m.bmat = a.bmat;
         m.Vf = a.Vf; m.Rf = a.Rf; m.pstat = a.pstat; m.pe = P.pe; m.ops = P.ops;
-        m.valid = a.valid; m.mat_raw = a.mat_raw; m.r2v = a.r2v; m.ysum = a.ysum; m.sd = a.sd;
+        m.valid = a.valid; m.cls = a.cls; m.mat_raw = a.mat_raw; m.r2v = a.r2v; m.ysum = a.ysum; m.sd = a.sd;
         m.sm = a.sm; m.N = a.N; m.scores = a.scores; m.nscored = a.nscored; m.fix_ids = a.fix_ids;
         m.fix_cnt = a.fix_cnt; m.fix_cap = a.fix_cap;
         l.blp = blp; l.r2q = a.r2q; l.NC = NC; l.delta = a.delta; l.cm = r3_moment_err(a.n);

@@ -3886,7 +3886,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         g3.plan = pl.r3.get();
         g3.n = P.n; g3.ldn = P.ldn; g3.TP = P.TP; g3.T = P.T; g3.mode = prm.score_mode;
         g3.Vf = P.Vf; g3.Rf = P.Rf; g3.Cf = P.Cf; g3.mu = P.mu; g3.msq = P.msq;
-        g3.valid = P.valid; g3.mat_raw = pl.mat_raw; g3.Yn = P.Yn; g3.ysum = P.ysum;
+        g3.valid = P.valid; g3.cls = P.cls; g3.mat_raw = pl.mat_raw; g3.Yn = P.Yn; g3.ysum = P.ysum;
         g3.r2v = P.r2v; g3.r2m = P.r2m; g3.r2q = P.r2q; g3.sd = sd; g3.sm = pl.sm; g3.N = P.N;
         g3.scores = P.scores; g3.nscored = P.ctr + 2; g3.fix_ids = P.fix_ids3;
         g3.fix_cnt = P.ctr + 3; g3.fix_cap = P.fix_cap; g3.bmat = P.r3b; g3.pstat = P.r3p;

@@ -92,8 +92,9 @@ __host__ __device__ inline bool pair_range(int ei, int ej) {
 constexpr int PAIR_PROBES = 1024;
 constexpr unsigned PROBE_MAX = PAIR_PROBES / 64;
 
-// Samples padded to whole 16-sample chunks are read: Vf, Rf and Yn hold
-// zeros from n to ldn (a multiple of 64).
+// Samples padded to whole 16-sample chunks are read: Vf and Rf hold the
+// feature's mean from n to ldn (a multiple of 64), Yn zeros, so that every
+// product has a factor 0 there.
 // Work items (problem, first row i0, first column j0, operator set: 0 mul,
 // add and sub, 1 div, 2 rdiv) of 16 x 16 pairs; split: the four waves of a
 // block share an item, else each takes one.

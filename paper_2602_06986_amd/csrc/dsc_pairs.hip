@@ -24,17 +24,18 @@ typedef double pr_v4d __attribute__((ext_vector_type(4)));
 // LDS in wave order.  Bound by the matrix cores: (3 + T) 2 n flop per
 // candidate of mul, div and rdiv (add and sub take the mul tile's sums); the
 // operands of a chunk are a few KB against thousands of cycles of products,
-// so nothing is staged in LDS, and the next chunk's operands are loaded while
-// this one's products run.  Measured against the vector form, which issues
-// 3 + T FP64 instructions per sample and operator (7.5 cycles each, its loads
-// exposed at three waves per SIMD), both with their launches: 20 features
-// without units, n = 1999: 8 targets 3170 -> 1380 us (80 % of the FP64 matrix
-// rate), 1 target 1070 -> 560 us (two tiles per wave: 600).  Without the
-// centring (2 + T products, scores off by up to 6e-9 where columns vary by
-// 1 %, here 2e-15 as by the vector form) 1410 and 420 us.
+// so nothing is staged in LDS; the next chunk's operands and the next two
+// targets are loaded while products run (each target's load waited for before
+// its products: 125 us instead of 66 for 6 features, 8 targets, n = 2000).
+// Measured against the vector form, which issues 3 + T FP64 instructions per
+// sample and operator (7.5 cycles each, its loads exposed at three waves per
+// SIMD), both with their launches: 20 features without units, n = 1999: 8
+// targets 3170 -> 1370 us (80 % of the FP64 matrix rate), 1 target 1070 ->
+// 530 us.  Without the centring (2 + T products, scores off by up to 6e-9
+// where columns vary by 1 %, here 2e-15) 1420 and 420 us.
 template <int TP, int KS>
 __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int4* __restrict__ work, int64_t n_work) {
-    constexpr int TK = TP + 3;
+    constexpr int TK = TP + 3, G = TP >= 2 ? 2 : 1;      // products; targets in step
     const int wv = wave_id();
     const int64_t w = KS == 1 ? (int64_t)blockIdx.x * 4 + wv : (int64_t)blockIdx.x;
     if (w >= n_work) return;
@@ -67,28 +68,44 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
         pr_v4d a = *(const pr_v4d*)(pa + first) * sa, b = *(const pr_v4d*)(pb + first) * sb;
         for (int s = first; s <= last; s += 16) {
             const int sn = min(s + 16, last);
-            pr_v4d an = *(const pr_v4d*)(pa + sn), bn = *(const pr_v4d*)(pb + sn);
-            pr_v4d ac = a - ca;
-            if (s + 16 > g.n) {                  // samples past the last: ac or a (0 there) is a factor everywhere
+            // loads return in order: the first targets' before the next chunk's
+            pr_v4d y[G];
 #pragma unroll
-                for (int e = 0; e < 4; e++)
-                    if (s + 4 * kq + e >= g.n) ac[e] = 0.0;
-            }
+            for (int q = 0; q < G; q++) y[q] = *(const pr_v4d*)(py + (int64_t)q * ldn + s);
+            pr_v4d an = *(const pr_v4d*)(pa + sn), bn = *(const pr_v4d*)(pb + sn);
+            __builtin_amdgcn_sched_barrier(0);
+            const pr_v4d ac = a - ca;            // 0 past the last sample, as b - cb and y
 #pragma unroll
             for (int e = 0; e < 4; e++) {
-                const double x = a[e], xc = ac[e], y = b[e], yc = y - cb;
-                const double p = DIV ? x : xc, q = DIV ? yc : y;
-                acc[TP] = __builtin_amdgcn_mfma_f64_16x16x4f64(xc, yc, acc[TP], 0, 0, 0);
+                const double x = a[e], xc = ac[e], z = b[e], zc = z - cb;
+                const double p = DIV ? x : xc, q = DIV ? zc : z;
+                acc[TP] = __builtin_amdgcn_mfma_f64_16x16x4f64(xc, zc, acc[TP], 0, 0, 0);
                 acc[TP + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(p * p, q * q, acc[TP + 1], 0, 0, 0);
-                acc[TP + 2] = DIV ? __builtin_amdgcn_mfma_f64_16x16x4f64(x * xc, yc, acc[TP + 2], 0, 0, 0)
-                                  : __builtin_amdgcn_mfma_f64_16x16x4f64(xc, y * yc, acc[TP + 2], 0, 0, 0);
+                acc[TP + 2] = DIV ? __builtin_amdgcn_mfma_f64_16x16x4f64(x * xc, zc, acc[TP + 2], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f64_16x16x4f64(xc, z * zc, acc[TP + 2], 0, 0, 0);
             }
+            const pr_v4d ya = DIV ? a : ac, yb = DIV ? b - cb : b;
 #pragma unroll
-            for (int t = 0; t < TP; t++) {
-                const pr_v4d ay = (DIV ? a : ac) * *(const pr_v4d*)(py + (int64_t)t * ldn + s);
+            for (int t = 0; t < TP; t += G) {
+                pr_v4d yn[G];
+                if (t + G < TP) {
+#pragma unroll
+                    for (int q = 0; q < G; q++) yn[q] = *(const pr_v4d*)(py + (int64_t)(t + G + q) * ldn + s);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                pr_v4d ay[G];
+#pragma unroll
+                for (int q = 0; q < G; q++) ay[q] = ya * y[q];
 #pragma unroll
                 for (int e = 0; e < 4; e++)
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ay[e], DIV ? b[e] - cb : b[e], acc[t], 0, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < G; q++)
+                        acc[t + q] = __builtin_amdgcn_mfma_f64_16x16x4f64(ay[q][e], yb[e], acc[t + q], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (t + G < TP) {
+#pragma unroll
+                    for (int q = 0; q < G; q++) y[q] = yn[q];
+                }
             }
             // (an empty asm takes the loaded operands here, so that the compiler
             // does not move their loads to the top of the next chunk)
@@ -132,9 +149,6 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
                 if (t < g.T) g.scores[(int64_t)t * g.N + id] = fabs(num[t] * isd);
         }
     };
-    double ys[TP];
-#pragma unroll
-    for (int t = 0; t < TP; t++) ys[t] = g.ysum[t] / nn;
     // the pair (i, j) with this operator set's sums P_t, C, G1, G2 in m
     auto pair = [&](int i, int j, const double (&m)[TK]) {
         if (!(j < g.jc_end && i < g.i_end && i < j) || !g.valid[i] || !g.valid[j]) return;
@@ -163,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int
             const double kappa = varn > 0.0 ? (t1 + G1 + fabs(C) / nn * sqrt(qa) * sqrt(qb)) / varn : INFINITY;
             const double* fb = g.fy + (int64_t)kb * TP;
 #pragma unroll
-            for (int t = 0; t < TP; t++) num[t] = fma(A, fb[t] * wb, m[t]) - C * ys[t];
+            for (int t = 0; t < TP; t++) num[t] = fma(A, fb[t] * wb, m[t]) - C / nn * g.ysum[t];
             const double mb = mean * back;
             emit(op, ri, rj, varn, kappa, sure, mb, varn / nn * back * back + mb * mb, num);
         }

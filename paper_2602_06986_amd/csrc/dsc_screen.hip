@@ -167,8 +167,6 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
         vmax = fmax(vmax, fabs(x));
         rmax = fmax(rmax, fabs(r));
     }
-    // padding to whole chunks of the matrix form
-    for (int i = n + lane; i < ldn; i += 64) Vf[(int64_t)c * ldn + i] = Rf[(int64_t)c * ldn + i] = 0.0;
     s = wave_sum(s);
     sr = wave_sum(sr);
     vmax = wave_max(vmax);
@@ -176,6 +174,11 @@ __device__ __forceinline__ void d_mat_stats(int n, int ldn, int c0, int c1,
     const int anyzero = __any(zero);
     const int anybad = __any(bad);
     const double m = s / n, mr = sr / n;
+    // padding to whole chunks of the matrix form
+    for (int i = n + lane; i < ldn; i += 64) {
+        Vf[(int64_t)c * ldn + i] = m;
+        Rf[(int64_t)c * ldn + i] = mr;
+    }
     double q = 0.0, qr = 0.0;
     for (int i = lane; i < n; i += 64) {
         const double d = v[i] - m, dr = Rf[(int64_t)c * ldn + i] - mr;
@@ -3742,11 +3745,11 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             // matrix form.  One work item (tile x operator set) per wave, or per
             // block where items are few or long: by their number and the products of
             // one (16-sample chunks x (3 + targets)).  Measured us per block, per
-            // wave: 102 items of 28, 77, 500 and 1375 products 15, 23; 21, 30; 41,
-            // 130; 126, 228; 402 of 28, 133 and 315 30, 26; 37, 44; 49, 92; 1050 of
-            // 52, 252 and 352 70, 44; 90, 108; 123, 129; 1302 of 128 89, 66; 2967 of
-            // 128 and 2375 171, 100; 1378, 1549; 7026 of 128, 500, 625, 875 and 1375
-            // 365, 179; 564, 560; 689, 696; 900, 892; 1723, 1372.
+            // wave: 102 items of 28, 133, 500 and 1375 products 15, 22; 21, 41; 34,
+            // 95; 66, 220; 402 of 28, 133, 315 and 2375 30, 26; 36, 41; 44, 68; 191,
+            // 368; 1050 of 52, 252 and 625 69, 39; 86, 98; 140, 201; 1302 of 128 87,
+            // 59; 2967 of 128 and 2375 167, 93; 1041, 1056; 7026 of 128, 500, 875 and
+            // 1375 357, 175; 550, 538; 907, 883; 1384, 1368.
             int64_t items = 0, prod = 0;
             for (int b : mem) {
                 const int64_t t = 3 * (int64_t)PS[b].plan->mmtiles.size();

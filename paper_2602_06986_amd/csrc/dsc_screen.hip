@@ -3547,15 +3547,14 @@ static int log2_bucket(int64_t v) {
 }
 
 // Autotuned choice of the precision form for one problem's dense pair
-// tiles: the BF16/FP16 kernel and the FP64 kernels are each timed once for this shape, their counter bumps undone, and the
-// faster is remembered.  (Both give the same selection: the FP64 scores lie
-// within the guard band of their own exact values.)
+// tiles: the BF16/FP16 kernel and the FP64 kernels are each timed once for
+// this shape, their counter bumps undone, and the faster is remembered.
+// (Both give the same selection: the FP64 scores lie within the guard band
+// of their own exact values.)  The launches come prepared: nothing is built,
+// uploaded or cleared between the events.
 static bool tune_precision(discover_ctx* ctx, const std::string& key, Problem& P,
                            const std::function<void()>& run_lp, const std::function<void()>& run_f64,
                            hipStream_t st) {
-    auto it = ctx->tuned.find(key);
-    if (it != ctx->tuned.end()) return it->second != 0;
-    if (ctx->capturing) DSC_FAIL(DISCOVER_E_CAPACITY, "precision-form tuning during graph capture");
     unsigned long long* sv = ctx->buf<unsigned long long>("tune_lp_ctr", 4);
     DSC_HIP(hipMemcpyAsync(sv, P.ctr, 32, hipMemcpyDeviceToDevice, st));
     float ms[2] = {0.f, 0.f};
@@ -3733,11 +3732,17 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
     const ctab<PairArgs> dpa = ct(ctx->upload("scr_pairs", pa, st));
     const std::vector<int> order = by_weight(PS);
     // FP64 dense tiles of problems mem, all of one (operator class, padded
-    // targets): gi numbers the group's tables and work queue
-    unsigned long long* const gqueues = PS.empty() ? nullptr : PS[0].queues;
-    auto run_dense = [&](const std::vector<int>& mem, int cls, int TP, const std::string& gi, unsigned long long* queue) {
-        int J = 1;
-        bool useq = prm.sched > 0;
+    // targets), and their launches; gi names the group's tables
+    struct Dense {
+        int cls, TP, J = 1;
+        bool useq, split = false;
+        const int4 *work = nullptr, *tiles = nullptr;     // of the matrix and of the vector form
+        int64_t n_work = 0, n_tiles = 0;
+    };
+    auto prep_dense = [&](const std::vector<int>& mem, int cls, int TP, const std::string& gi) {
+        Dense d;
+        d.cls = cls; d.TP = TP; d.useq = prm.sched > 0;
+        int& J = d.J;
         if (prm.tile_j > 0) {
             while (J * 2 <= std::min(prm.tile_j, max_J(TP))) J *= 2;
         }
@@ -3756,7 +3761,7 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                 items += t;
                 prod += t * cdiv(PS[b].n, 16) * (TP + 3);
             }
-            const bool split = items <= 256 || (items < 4096 && prod >= items * (items / 8 + 64));
+            d.split = items <= 256 || (items < 4096 && prod >= items * (items / 8 + 64));
             std::vector<int4> work;
             for (int b : mem) {
                 const uint32_t ops = PS[b].plan->dense_ops;
@@ -3764,7 +3769,8 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                     for (int sel = 0; sel < 3; sel++)
                         if (ops & (sel == 0 ? 7u : sel == 1 ? 8u : 16u)) work.push_back(make_int4(b, t.x, t.y, sel));
             }
-            launch_pairs_mm(dpa, ctx->upload("scr_mmwork" + gi, work, st), (int64_t)work.size(), TP, split, st);
+            d.work = ctx->upload("scr_mmwork" + gi, work, st);
+            d.n_work = (int64_t)work.size();
             // what the matrix form leaves: two operand features per wave for one
             // target (the width that timing chose for tables of 16 to 20 features)
             J = std::min(2, max_J(TP));
@@ -3782,17 +3788,20 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
                                     "|" + std::to_string(prm.tile_j) + "|" + std::to_string(prm.sched);
             const int c = tune_dense(ctx, key, cls, TP, dpa, PS, mem, prm.tile_j > 0 ? J : 0, prm.sched, st);
             if (prm.tile_j == 0) J = c & 0xFF;
-            if (prm.sched == 0) useq = (c >> 8) != 0;
+            if (prm.sched == 0) d.useq = (c >> 8) != 0;
         }
         const int jx = J == 4 ? 2 : J == 2 ? 1 : 0;
         std::vector<int4> tiles;
-        for (int b : mem) {
-            PS[b].tile_j = J;
+        for (int b : mem)
             for (const int2& t : PS[b].plan->dtilesJ[jx]) tiles.push_back(make_int4(b, t.x, t.y, 0));
-        }
-        const int4* dt = ctx->upload("scr_dtiles" + gi, tiles, st);
-        launch_pairs(cls, dpa, dt, (int64_t)tiles.size(), false, TP, J, st, useq ? queue : nullptr,
-                     forced ? nullptr : PS[0].bad, nb == 1);
+        d.tiles = ctx->upload("scr_dtiles" + gi, tiles, st);
+        d.n_tiles = (int64_t)tiles.size();
+        return d;
+    };
+    auto run_dense = [&](const Dense& d, ctab<PairArgs> A, const unsigned* bad, unsigned long long* queue) {
+        if (!forced) launch_pairs_mm(A, d.work, d.n_work, d.TP, d.split, st);
+        launch_pairs(d.cls, A, d.tiles, d.n_tiles, false, d.TP, d.J, st, d.useq ? queue : nullptr,
+                     forced ? nullptr : bad, nb == 1);
         check_launch("k_screen_pairs");
     };
     // 6a. precision form: per problem, BF16/FP16 screening with FP64 guard-band
@@ -3815,14 +3824,28 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             else launch_lp<false>(pl.dense_cls, a, P.ylp, P.ldl, dl, st);
             check_launch("k_screen_lp");
         };
-        auto run_f64 = [&] {
-            fill_all(ctx, "tune_qfill", {fill_seg(ctx->buf<unsigned long long>("tune_queue", 1), 8, 0u)}, st);
-            run_dense({b}, pl.dense_cls, P.TP, "_tune", ctx->buf<unsigned long long>("tune_queue", 1));
-        };
-        if (prm.lp_pairs < 0 ||
-            (prm.lp_pairs == 0 &&
-             !tune_precision(ctx, "lp" + pl.key + std::to_string(P.n) + (fp16 ? "h" : "b"), P, run_lp, run_f64, st)))
-            continue;                            // FP64 tiles below
+        if (prm.lp_pairs < 0) continue;              // FP64 tiles below
+        if (prm.lp_pairs == 0) {
+            const std::string key = "lp" + pl.key + std::to_string(P.n) + (fp16 ? "h" : "b") + "|" +
+                                    std::to_string(prm.tile_j) + "|" + std::to_string(prm.sched);
+            bool lp;
+            auto it = ctx->tuned.find(key);
+            if (it != ctx->tuned.end()) {
+                lp = it->second != 0;
+            } else {
+                if (ctx->capturing) DSC_FAIL(DISCOVER_E_CAPACITY, "precision-form tuning during graph capture");
+                // (the matrix form is timed for any data: the choice is the shape's)
+                const Dense d = prep_dense({b}, pl.dense_cls, P.TP, "_tune");
+                unsigned long long* q = ctx->buf<unsigned long long>("tune_lp_queue", 1);
+                unsigned* zero = ctx->buf<unsigned>("tune_lp_bad", nb);
+                fill_all(ctx, "tune_qfill", {fill_seg(q, 8, 0u), fill_seg(zero, nb * sizeof(unsigned), 0u)}, st);
+                std::vector<PairArgs> pt = pa;
+                for (PairArgs& x : pt) x.bad = zero;
+                const ctab<PairArgs> dpt = ct(ctx->upload("scr_pairs_tune", pt, st));
+                lp = tune_precision(ctx, key, P, run_lp, [&] { run_dense(d, dpt, zero, q); }, st);
+            }
+            if (!lp) continue;
+        }
         lp_used[b] = 1;
         KTimer kt(ctx, st, "screen_lp");
         run_lp();
@@ -3834,11 +3857,14 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
         if (P.pairs && P.plan->dense_ops && !lp_used[b])
             groups[{P.plan->dense_cls, P.TP}].push_back(b);
     }
+    unsigned long long* const gqueues = PS.empty() ? nullptr : PS[0].queues;
     int gi = 0;
     for (auto& g : groups) {
+        const Dense d = prep_dense(g.second, g.first.first, g.first.second, std::to_string(gi));
+        for (int b : g.second) PS[b].tile_j = d.J;
         KTimer kt(ctx, st, "screen_pairs");
         // (past the queue counters, one block per tile)
-        run_dense(g.second, g.first.first, g.first.second, std::to_string(gi), gi < MAX_QUEUES ? gqueues + gi : nullptr);
+        run_dense(d, dpa, PS[0].bad, gi < MAX_QUEUES ? gqueues + gi : nullptr);
         gi++;
     }
     // 6c. same-unit add/sub partner lists (FP64 in every form), merged per TP

@@ -675,25 +675,20 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     const int cb = lb / g.n_gblk;
     const int ctb = a.ct0 + cb * CT;                     // first column tile of the block
     const int64_t tile0 = (int64_t)(lb - cb * g.n_gblk) * 4 + r3_wave();
-    // a wave without a row tile still stages its share and meets every
-    // barrier (and forms products that are not stored)
-    const bool active = tile0 * 16 < g.n_grec;
     constexpr bool hk = HK;
     bool rok;
     int64_t j2;
-    int oo, rkind;
+    int oo, rkind;                                       // of every row of the block (build_r3_plan)
     bool rzero;                                          // 1/g is infinite through a zero operand
     const double* b1;
     const double* b2;
     unsigned ri1[4], ri2[4];
     {
-        const int64_t t16 = min(tile0, (g.n_grec >> 4) - 1) * 16;
-        const int64_t rec = tile0 * 16 + r16;
         int k = -2, l = 0, op2;
-        r3_rec(g.grec[rec < g.n_grec ? rec : t16], k, l, op2);
+        r3_rec(g.grec[tile0 * 16 + r16], k, l, op2);
         op2 = __builtin_amdgcn_readfirstlane(op2);
         oo = op2;
-        rok = rec < g.n_grec && k != -2;
+        rok = k != -2;
         j2 = rok ? r3_j2(g.sd, g.mat_raw, k, l, op2) : 0;
         rok = rok && g.r2v[j2 - g.sd.off[2]];
         int i1, i2;
@@ -809,7 +804,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
                     x = r3_rcp(x);
                 }
                 if (past) x = 0.0;
-                if (hk) hm[h] = fabs(x) > hm[h] ? fabs(x) : hm[h];   // NaN leaves it unchanged
+                if (hk) hm[h] = fmax(hm[h], fabs(x));        // NaN leaves it unchanged
                 w[e] = (float)x;
             }
             *(r3_f32x2*)(tw + h * 512 + (tws ^ (32 * h))) = w;
@@ -913,14 +908,13 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
             __syncthreads();
         }
     };
-    // (the kind is wave-uniform; every kind meets the same barriers)
+    // (block-uniform: every wave takes the same loop and its barriers)
     switch (rkind) {
     case RK_PROD: run(std::integral_constant<int, RK_PROD>{}); break;
     case RK_ADD: run(std::integral_constant<int, RK_ADD>{}); break;
     case RK_SUB: run(std::integral_constant<int, RK_SUB>{}); break;
     default: run(std::integral_constant<int, RK_OTHER>{}); break;
     }
-    if (!active) return;
     // of rows 4 kq + e: max |1/g|, and whether g has a zero
     double hx4[4] = {0.0, 0.0, 0.0, 0.0};
     bool gz4[4] = {false, false, false, false};
@@ -1037,7 +1031,8 @@ void launch_lp_range(R3lpArgs l, int ct0, int ct1, hipStream_t st) {
 // smaller groups.
 template <int TP>
 void launch_lp(R3lpArgs l, int n_gct, int nct, int64_t n_grec, hipStream_t st) {
-    l.m.n_gblk = (int)((n_grec / 16 + 3) / 4);
+    DSC_REQUIRE(n_grec % 64 == 0, "rung-3 records come in blocks of 64");
+    l.m.n_gblk = (int)(n_grec / 64);
     auto range = [&](int c0, int c1, auto hk) {
         constexpr bool HK = decltype(hk)::value;
         constexpr int CMAX = TP <= 4 || (TP <= 8 && !HK) ? 3 : TP <= 8 ? 2 : 1;
@@ -1106,10 +1101,11 @@ std::shared_ptr<R3Plan> build_r3_plan(const Space& sp, uint32_t r3_ops) {
         rec.push_back(make_int2(k, l | (o << 28)));
         if (addsub) gunit.insert(gunit.end(), u2.begin(), u2.end());
     };
-    // each operator's run is padded to a multiple of 16 records (k = -2:
-    // no feature), so that the rows of a 16-row tile share one operator
-    auto pad16 = [&](int o) {
-        while (rec.size() % 16) {
+    // each operator's run is padded to a multiple of 64 records (k = -2:
+    // no feature), so that the four 16-row tiles of a block share one
+    // operator (k_r3_lp branches on its kind around a loop with barriers)
+    auto pad64 = [&](int o) {
+        while (rec.size() % 64) {
             rec.push_back(make_int2(-2, o << 28));
             if (addsub) gunit.insert(gunit.end(), Bq, INT32_MIN);
         }
@@ -1118,7 +1114,7 @@ std::shared_ptr<R3Plan> build_r3_plan(const Space& sp, uint32_t r3_ops) {
         if (d.block[2][o] < 0) continue;
         for (int32_t l = c0; l < c1; l++)
             if (unit_rule(o, B, &sp.mat_unit[(size_t)l * Bq], nullptr, u2.data())) push(-1, l, o);
-        pad16(o);
+        pad64(o);
     }
     // binary records in windows of R3_SW operands l by R3_SW operands k: the
     // tiles of a window need 2 R3_SW operand rows, which stay in L2 while
@@ -1135,7 +1131,7 @@ std::shared_ptr<R3Plan> build_r3_plan(const Space& sp, uint32_t r3_ops) {
                         if (unit_rule(o, B, &sp.mat_unit[(size_t)k * Bq], &sp.mat_unit[(size_t)l * Bq], u2.data()))
                             push(k, l, o);
                 }
-        pad16(o);
+        pad64(o);
     }
     P->n_grec = (int64_t)rec.size();
     DSC_REQUIRE(P->n_grec < ((int64_t)1 << 31), "rung-3 record list too large");

@@ -3771,9 +3771,18 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             }
             d.work = ctx->upload("scr_mmwork" + gi, work, st);
             d.n_work = (int64_t)work.size();
-            // what the matrix form leaves: two operand features per wave for one
-            // target (the width that timing chose for tables of 16 to 20 features)
-            J = std::min(2, max_J(TP));
+            // what the matrix form leaves (columns that are nearly multiples of one
+            // another): one block per tile, two operand features per wave for one
+            // target, and for two targets from 400 samples.  Measured us at widths 1,
+            // 2, 4 of such columns, then from the queue: 1 target, 6 features, n = 100
+            // 28, 23, 40; 34, 45, 60; n = 2000 336, 133, 288; 398, 470, 344; 12
+            // features, n = 500 147, 75, 111; 218, 189, 155; 20 features, n = 200 336,
+            // 189, 285; 433, 334, 288; n = 2000 2823, 1091, 1721; 3058, 2246, 1568.  2
+            // targets at 1, 2: 6, n = 100 19, 29; 29, 41; 12, n = 500 104, 99; 205, 165;
+            // 20, n = 200 251, 265; 397, 318; n = 2000 2060, 1849; 3158, 2113.
+            int nmax = 0;
+            for (int b : mem) nmax = std::max(nmax, PS[b].n);
+            J = TP == 1 || (TP == 2 && nmax >= 400) ? 2 : 1;
         } else if (prm.tile_j == 0 || prm.sched == 0) {
             // shape class: operator class, padded targets, buckets of the
             // largest n and of the tile count

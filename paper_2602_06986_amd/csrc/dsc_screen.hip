@@ -3772,17 +3772,21 @@ static void screen_all(discover_ctx* ctx, const discover_problem* probs, int nb,
             d.work = ctx->upload("scr_mmwork" + gi, work, st);
             d.n_work = (int64_t)work.size();
             // what the matrix form leaves (columns that are nearly multiples of one
-            // another): one block per tile, two operand features per wave for one
-            // target, and for two targets from 400 samples.  Measured us at widths 1,
-            // 2, 4 of such columns, then from the queue: 1 target, 6 features, n = 100
-            // 28, 23, 40; 34, 45, 60; n = 2000 336, 133, 288; 398, 470, 344; 12
+            // another): one block per tile.  With units (three operators) the widest
+            // form; without (five) two operand features per wave for one target, and
+            // for two targets from 400 samples.  Measured us at widths 1, 2, 4 of such
+            // columns, then from the queue: without units, 1 target, 6 features, n =
+            // 100 28, 23, 40; 34, 45, 60; n = 2000 336, 133, 288; 398, 470, 344; 12
             // features, n = 500 147, 75, 111; 218, 189, 155; 20 features, n = 200 336,
-            // 189, 285; 433, 334, 288; n = 2000 2823, 1091, 1721; 3058, 2246, 1568.  2
+            // 189, 285; 433, 334, 288; n = 2000 2823, 1091, 1721; 3058, 2246, 1568; 2
             // targets at 1, 2: 6, n = 100 19, 29; 29, 41; 12, n = 500 104, 99; 205, 165;
-            // 20, n = 200 251, 265; 397, 318; n = 2000 2060, 1849; 3158, 2113.
+            // 20, n = 200 251, 265; 397, 318; n = 2000 2060, 1849; 3158, 2113.  With
+            // units, 1 target, 16, n = 100 57, 40, 38; 102, 72, 63; 24, n = 300 275, 155,
+            // 154; 368, 253, 209; n = 2000 1466, 856, 692; 1890, 1223, 1025; 2 targets at
+            // 1, 2: 16, n = 100 56, 41; 101, 74; 24, n = 2000 1429, 897; 2188, 1360.
             int nmax = 0;
             for (int b : mem) nmax = std::max(nmax, PS[b].n);
-            J = TP == 1 || (TP == 2 && nmax >= 400) ? 2 : 1;
+            J = cls == 28 ? max_J(TP) : TP == 1 || (TP == 2 && nmax >= 400) ? 2 : 1;
         } else if (prm.tile_j == 0 || prm.sched == 0) {
             // shape class: operator class, padded targets, buckets of the
             // largest n and of the tile count

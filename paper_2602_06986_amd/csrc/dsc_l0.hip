@@ -2011,30 +2011,31 @@ extern "C" discover_status discover_l0_fit(discover_ctx* ctx, const discover_l0_
 
 namespace dsc {
 
-// Work space of one problem's OMP, as documented for the allocation-free
-// form (byte sizes, each a multiple of 256): row means and the triangles T
-// and R (in a part sized (S + 1) rows of samples), two single values, scores, inverse norms,
-// residual (when the caller keeps none), QR columns, one value.  The first
-// part holds 8 (S + (D_max + 1)(D_max + 2)) bytes of use: S >= D_max and at
-// least 16 samples a row make that fit.
-static void omp_sizes(const discover_l0_problem& pb, int D_max, bool resid, size_t sz[8]) {
+// Work buffers of one problem's OMP (byte sizes, each a multiple of 256):
+// the triangles T and R with the row means, active count, scores, inverse
+// norms, residual (when the caller keeps none), QR columns.
+constexpr int OMP_BUFS = 6;
+
+static void omp_sizes(const discover_l0_problem& pb, int D_max, bool resid, size_t sz[OMP_BUFS]) {
     auto r256 = [](size_t b) { return (b + 255) & ~(size_t)255; };
-    const size_t ldz = (size_t)cdiv(pb.n, 16) * 16;
-    sz[0] = r256((size_t)(pb.S + 1) * ldz * 8);
+    sz[0] = r256((size_t)(pb.S + (D_max + 1) * (D_max + 2)) * 8);
     sz[1] = 256;
-    sz[2] = 256;
+    sz[2] = r256((size_t)pb.S * 8);
     sz[3] = r256((size_t)pb.S * 8);
-    sz[4] = r256((size_t)pb.S * 8);
-    sz[5] = resid ? 0 : r256((size_t)pb.n * 8);
-    sz[6] = r256((size_t)(D_max + 2) * pb.n * 8);
-    sz[7] = 256;
+    sz[4] = resid ? 0 : r256((size_t)pb.n * 8);
+    sz[5] = r256((size_t)(D_max + 2) * pb.n * 8);
 }
 
+// The work space documented for the allocation-free form, which decides what
+// it refuses: it holds (S + 1) rows of samples in place of the first buffer,
+// no smaller than it (S >= D_max, at least 16 samples a row), and two values
+// more.
 size_t omp_scratch_bytes(const discover_l0_problem* probs, int nb, int D_max, bool resid) {
     size_t t = 0;
     for (int b = 0; b < nb; b++) {
-        size_t sz[8];
+        size_t sz[OMP_BUFS];
         omp_sizes(probs[b], D_max, resid, sz);
+        sz[0] = (((size_t)(probs[b].S + 1) * (size_t)(cdiv(probs[b].n, 16) * 16) * 8 + 255) & ~(size_t)255) + 512;
         for (size_t v : sz) t += v;
     }
     return t;
@@ -2044,7 +2045,7 @@ void omp_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int 
                const int32_t* init_active, int n_init, int64_t init_ld, int32_t* out_active,
                double* out_coef, double* out_rmse, double* out_resid, int64_t ldr, hipStream_t st,
                char* scratch) {
-    static const char* const names[8] = {"ompZ", "ompyy", "ompn", "ompg", "ompnrm", "ompr", "ompA", "omprss"};
+    static const char* const names[OMP_BUFS] = {"ompTR", "ompn", "ompg", "ompnrm", "ompr", "ompA"};
     size_t off = 0;
     // (no timer events in the scratch form: it creates nothing)
     std::unique_ptr<KTimer> kt(scratch ? nullptr : new KTimer(ctx, st, "omp"));
@@ -2054,11 +2055,10 @@ void omp_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int 
         int Smax = 0;
         for (int b = b0; b < b0 + nc; b++) {
             const discover_l0_problem& pb = probs[b];
-            size_t sz[8];
+            size_t sz[OMP_BUFS];
             omp_sizes(pb, D_max, out_resid != nullptr, sz);
-            if (!scratch) sz[0] = (size_t)(pb.S + (D_max + 1) * (D_max + 2)) * 8;
-            char* w[8] = {};
-            for (int q = 0; q < 8; q++) {
+            char* w[OMP_BUFS] = {};
+            for (int q = 0; q < OMP_BUFS; q++) {
                 if (!sz[q]) continue;
                 if (scratch) {                   // the caller's scratch, laid out in order
                     w[q] = scratch + off;
@@ -2071,11 +2071,11 @@ void omp_batch(discover_ctx* ctx, const discover_l0_problem* probs, int nb, int 
             p.n = pb.n; p.S = pb.S; p.F = pb.F; p.ldf = pb.ldf; p.y = pb.y; p.ids = pb.ids;
             p.TR = (double*)w[0];
             p.mean = p.TR + (D_max + 1) * (D_max + 2);
-            p.nact = (int32_t*)w[2];
-            p.g = (double*)w[3];
-            p.inv = (double*)w[4];
-            p.r = out_resid ? out_resid + (int64_t)b * ldr : (double*)w[5];
-            p.A = (double*)w[6];
+            p.nact = (int32_t*)w[1];
+            p.g = (double*)w[2];
+            p.inv = (double*)w[3];
+            p.r = out_resid ? out_resid + (int64_t)b * ldr : (double*)w[4];
+            p.A = (double*)w[5];
             p.active = out_active + (int64_t)b * D_max;
             p.coef = out_coef + (int64_t)b * (D_max + 1);
             p.rmse = out_rmse + b;

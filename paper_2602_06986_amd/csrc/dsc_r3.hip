@@ -702,11 +702,7 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     }
     r3_f32x4 s1[CT], s2[CT], c1[CT], c2[CT];              // moments: a_h x_h and cross terms
     r3_f32x4 pa[CT][TP];
-    // div tiles: max |1/g| of the lane's samples of row l/16 + 4h, and whether
-    // g itself has a zero among them (bit h; for sums and unary values, whose
-    // reciprocal is taken here)
-    double hm[4] = {0.0, 0.0, 0.0, 0.0};
-    unsigned hz = 0;
+    float hmx = 0.0f;                                    // div tiles: max |1/g| of the lane's samples, rounded
 #pragma unroll
     for (int c = 0; c < CT; c++) {
         s1[c] = r3_f32x4{0.f, 0.f, 0.f, 0.f};
@@ -773,10 +769,8 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     // its own row of the products, whose scores are never stored, so it is
     // not masked.  FP64 -> FP32 here and FP32 -> BF16 in prepare are two
     // hardware roundings (the error bound counts both).
-    auto form = [&](int ch, const Ld& L, auto kind_c, auto tail_c) {
+    auto combine = [&](const Ld& L, auto kind_c, double (&v)[8]) {
         constexpr int kind = decltype(kind_c)::value;
-        constexpr bool tail = decltype(tail_c)::value;
-        double v[8];
         if constexpr (kind == RK_OTHER) {
 #pragma unroll
             for (int h = 0; h < 2; h++) {
@@ -792,19 +786,20 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
                 v[e] = kind == RK_PROD ? x * y : kind == RK_ADD ? x + y : x - y;
             }
         }
+    };
+    auto form = [&](int ch, const Ld& L, auto kind_c, auto tail_c) {
+        constexpr int kind = decltype(kind_c)::value;
+        constexpr bool tail = decltype(tail_c)::value;
+        double v[8];
+        combine(L, kind_c, v);
 #pragma unroll
         for (int h = 0; h < 4; h++) {
             r3_f32x2 w;
 #pragma unroll
             for (int e = 0; e < 2; e++) {
                 double x = v[2 * h + e];
-                const bool past = tail && 32 * ch + 2 * r16 + e >= g.n;
-                if (hk && kind != RK_PROD) {
-                    if (x == 0.0 && !past) hz |= 1u << h;
-                    x = r3_rcp(x);
-                }
-                if (past) x = 0.0;
-                if (hk) hm[h] = fmax(hm[h], fabs(x));        // NaN leaves it unchanged
+                if (hk && kind != RK_PROD) x = r3_rcp(x);
+                if (tail && 32 * ch + 2 * r16 + e >= g.n) x = 0.0;
                 w[e] = (float)x;
             }
             *(r3_f32x2*)(tw + h * 512 + (tws ^ (32 * h))) = w;
@@ -814,6 +809,9 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
         float vf[8];
         *(r3_f32x4*)vf = *(const r3_f32x4*)(tr + trs);
         *(r3_f32x4*)(vf + 4) = *(const r3_f32x4*)(tr + (trs ^ 16));
+#pragma unroll
+        for (int e = 0; e < 8; e++)
+            if (hk) hmx = fmaxf(hmx, fabsf(vf[e]));      // NaN leaves it unchanged
 #pragma unroll
         for (int e = 0; e < 4; e++) {
             unsigned h, l;
@@ -915,25 +913,72 @@ __global__ __launch_bounds__(256, 2) void k_r3_lp(R3lpArgs a) {
     case RK_SUB: run(std::integral_constant<int, RK_SUB>{}); break;
     default: run(std::integral_constant<int, RK_OTHER>{}); break;
     }
-    // of rows 4 kq + e: max |1/g|, and whether g has a zero
+    // of rows 4 kq + e: max |1/g| or a bound of it, and whether g has a zero
     double hx4[4] = {0.0, 0.0, 0.0, 0.0};
     bool gz4[4] = {false, false, false, false};
-    if (hk) {
-        uint64_t z = 0;                                  // of rows 4 kq .. 4 kq + 3: 16 bits each
+    if constexpr (hk) {
+        hmx = fmaxf(hmx, __shfl_xor(hmx, 16, 64));
+        hmx = fmaxf(hmx, __shfl_xor(hmx, 32, 64));
+        // the largest rounded value, rounded up (from the FP32 subnormals too)
+        const double hb = fmax((double)hmx * (1.0 + 0x1p-22), 0x1p-125);
+        bool far = false;
 #pragma unroll
-        for (int h = 0; h < 4; h++) {
-            for (int o = 8; o > 0; o >>= 1) hm[h] = fmax(hm[h], __shfl_xor(hm[h], o, 64));
-            const uint64_t m = __builtin_amdgcn_ballot_w64((hz >> h) & 1u);
-            z = kq == h ? m : z;
+        for (int e = 0; e < 4; e++) {
+            hx4[e] = __shfl(hb, 4 * kq + e, 64);
+            gz4[e] = __shfl((int)rzero, 4 * kq + e, 64) != 0;
+            const bool ok = __shfl((int)rok, 4 * kq + e, 64) != 0 && !gz4[e];
+            const double rmn = 1.0 / hx4[e];
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-                const double x = __shfl(hm[h], 16 * e, 64);          // row 4 h + e
-                hx4[e] = kq == h ? x : hx4[e];
+            for (int c = 0; c < CT; c++) {
+                const int32_t cd = g.coldesc[min(ctb + c, a.ct1 - 1) * 16 + r16];
+                if (!ok || cd < 0 || !g.valid[cd & 0xFFFF]) continue;
+                const double xmx = g.pstat[cd & 0xFFFF];
+                const bool in = rmn >= R3_TINY && xmx < R3_BIG * rmn && hx4[e] < LP_BIG2 && xmx * hx4[e] < LP_BIG2;
+                far = far || !in || !(s2[c][e] + c2[c][e] < INFINITY);
             }
         }
+        // where that does not settle a candidate's range, or its sums are not
+        // finite (a zero of g gives no reciprocal): the largest |1/g| in FP64
+        // and the zeros, from the rows again
+        if (__any(far)) {
+            double hm[4] = {0.0, 0.0, 0.0, 0.0};         // of row l/16 + 4h
+            unsigned hz = 0;                             // bit h: zero
+            auto scan = [&](auto kind_c) {
+                constexpr int kind = decltype(kind_c)::value;
+                for (int ch = 0; ch < a.NC; ch++) {
+                    Ld L;
+                    load_rows(ch, L);
+                    double v[8];
+                    combine(L, kind_c, v);
 #pragma unroll
-        for (int e = 0; e < 4; e++)
-            gz4[e] = __shfl((int)rzero, 4 * kq + e, 64) != 0 || ((z >> (16 * e)) & 0xFFFFu) != 0;
+                    for (int e = 0; e < 8; e++) {
+                        if (32 * ch + 2 * r16 + (e & 1) >= g.n) continue;
+                        if (kind != RK_PROD && v[e] == 0.0) hz |= 1u << (e >> 1);
+                        hm[e >> 1] = fmax(hm[e >> 1], fabs(kind == RK_PROD ? v[e] : r3_rcp(v[e])));
+                    }
+                }
+            };
+            switch (rkind) {
+            case RK_PROD: scan(std::integral_constant<int, RK_PROD>{}); break;
+            case RK_ADD: scan(std::integral_constant<int, RK_ADD>{}); break;
+            case RK_SUB: scan(std::integral_constant<int, RK_SUB>{}); break;
+            default: scan(std::integral_constant<int, RK_OTHER>{}); break;
+            }
+            uint64_t z = 0;                              // of rows 4 kq .. 4 kq + 3: 16 bits each
+#pragma unroll
+            for (int h = 0; h < 4; h++) {
+                for (int o = 8; o > 0; o >>= 1) hm[h] = fmax(hm[h], __shfl_xor(hm[h], o, 64));
+                const uint64_t m = __builtin_amdgcn_ballot_w64((hz >> h) & 1u);
+                z = kq == h ? m : z;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    const double x = __shfl(hm[h], 16 * e, 64);      // row 4 h + e
+                    hx4[e] = kq == h ? x : hx4[e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; e++) gz4[e] = gz4[e] || ((z >> (16 * e)) & 0xFFFFu) != 0;
+        }
     }
     const double nn = (double)g.n;
     unsigned cnt = 0;

@@ -40,9 +40,9 @@ L0_FLOP_PER_SUBSET = 12
 # plain 1 GiB device copy.  Valid only for the kernel source they were taken on.
 SWEEP3_COUNTERS = {
     "source": "paper_2602_06986_amd/csrc/dsc_l0.hip",
-    "sha256": "2463cfec93b221d5a479c2e98b9d74609a59c7678e14f519db96e8cca0f5d4fc",
-    "fetch_kib": 76895.2, "fetch_scale": 1.99991,
-    "write_kib": 15214.6, "write_scale": 1.0,
+    "sha256": "6e39b20cfc015c2309da1b6d8ee8c266f62ccc7d48c181581edd17b30d4ca051",
+    "fetch_kib": 76873.1, "fetch_scale": 1.99993,
+    "write_kib": 15212.9, "write_scale": 1.0,
 }
 
 
@@ -53,11 +53,11 @@ SWEEP3_COUNTERS = {
 R3_COUNTERS = {
     # the precision form: totals of the k_r3_lp kernels of one dimension
     "k_r3_lp": {"source": "paper_2602_06986_amd/csrc/dsc_r3.hip",
-                "sha256": "a2bf91b51baca1994c6469e422a2778039c7954ce4f4a2faa4626fa30195b7e6",
-                "fetch_kib": 1471844.9, "fetch_scale": 1.99992, "write_kib": 1173390.8, "write_scale": 1.0},
+                "sha256": "32da37ba39f5a9c67330e31a8df33f9defb8549eabe0861322b4c2ebdb430372",
+                "fetch_kib": 1648545.7, "fetch_scale": 1.99992, "write_kib": 1128166.8, "write_scale": 1.0},
     "k_r3_mm": {"source": "paper_2602_06986_amd/csrc/dsc_r3.hip",
-                "sha256": "a2bf91b51baca1994c6469e422a2778039c7954ce4f4a2faa4626fa30195b7e6",
-                "fetch_kib": 6172460.2, "fetch_scale": 1.99992, "write_kib": 1299340.4, "write_scale": 1.0},
+                "sha256": "32da37ba39f5a9c67330e31a8df33f9defb8549eabe0861322b4c2ebdb430372",
+                "fetch_kib": 6193250.1, "fetch_scale": 1.99992, "write_kib": 1299340.7, "write_scale": 1.0},
 }
 
 
@@ -475,8 +475,8 @@ def large_main(args):
                 "avg_launch_ms": r3["avg_launch_ms"], "launches_timed": r3["launches_per_step"] * args.steps,
                 "work": "(4 + 2T) n flop per unit-valid rung-3 candidate and launch-average dimension "
                         "(T = 1, 8, 8), all on the BF16 matrix cores (12 + 2T n executed: split moments)",
-                "note": "the matrix cores are not what holds this kernel: reads and copies of the "
-                        "column operands in LDS take two thirds of its cycles"}
+                "note": "no unit by itself holds this kernel: vector instructions, LDS and the matrix "
+                        "cores are each busy for a third of its cycles, at two waves per SIMD"}
     if "screen_r3" in res["fp64"][2]:
         r3 = res["fp64"][2]["screen_r3"]
         flops = sum(valid3 * w["n"] * (4 + 2 * T) for T in Ts) / r3["launches_per_step"]

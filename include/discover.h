@@ -382,7 +382,7 @@ typedef struct {
     int64_t n_subsets;        /* C(S, D) */
     int64_t n_nodes;          /* prefixes (partial subsets) expanded */
     int64_t n_bounds;         /* bound evaluations */
-    int64_t n_leaves;         /* D-subsets whose explained fraction was computed */
+    int64_t n_leaves;         /* D-subsets reached (their last pivot and correlation formed) */
     int64_t n_refit;          /* subsets refitted by Householder QR */
     int32_t m0;               /* trailing rows over which the bound is trusted (see below) */
     int32_t status;           /* DISCOVER_OK, E_CAPACITY (max_nodes reached), E_NUMERIC */

@@ -30,9 +30,11 @@ typedef double pr_v4d __attribute__((ext_vector_type(4)));
 // Measured against the vector form, which issues 3 + T FP64 instructions per
 // sample and operator (7.5 cycles each, its loads exposed at three waves per
 // SIMD), both with their launches: 20 features without units, n = 1999: 8
-// targets 3170 -> 1370 us (80 % of the FP64 matrix rate), 1 target 1070 ->
-// 530 us.  Without the centring (2 + T products, scores off by up to 6e-9
-// where columns vary by 1 %, here 2e-15) 1420 and 420 us.
+// targets 3170 -> 1370 us (76 % of the FP64 matrix rate that a large product
+// reaches), 1 target 1070 -> 530 us (FP64 vector instructions take another
+// fifth of the cycles, which the matrix cores then stand still).  Without the
+// centring (2 + T products, scores off by up to 6e-9 where columns vary by
+// 1 %, here 2e-15) 1420 and 420 us.
 template <int TP, int KS>
 __global__ __launch_bounds__(256, 2) void k_pairs_mm(ctab<PairArgs> A, const int4* __restrict__ work, int64_t n_work) {
     constexpr int TK = TP + 3, G = TP >= 2 ? 2 : 1;      // products; targets in step

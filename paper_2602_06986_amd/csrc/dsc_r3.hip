@@ -653,14 +653,15 @@ typedef float r3_f32x2 __attribute__((ext_vector_type(2)));
 // read 256 contiguous bytes of a row), combined and rounded to FP32 in that
 // order and turned to the products' order (a lane's 8 samples of one row)
 // through 2 KB of the wave's own LDS: loaded in the products' order, each
-// load would touch 64 cache lines, and their look-ups in the first-level
-// cache took three quarters of the kernel's cycles.
-// Bound: LDS (the blocks' reads and copies, two thirds of the cycles), then
-// the second-level cache.  Measured with 24 partners, 8 targets and 2000
-// samples, all rung-2 features: mul / rdiv tiles 7.6 ms (operands through
-// registers, two column tiles per wave and rows in the products' order:
-// 11.9; three tiles and copies to LDS, rows in the products' order: 8.4),
-// div tiles 5.5 ms (7.1; 6.5).
+// load would touch 64 cache lines.
+// Bound: no unit by itself.  At 8 targets the mul / rdiv tiles keep vector
+// instructions busy for 37 % of the cycles, LDS for 32 % and the matrix cores
+// for 30 %, in two waves per SIMD (all that the accumulators leave) that wait
+// on memory or LDS for a third of theirs.  Measured with 24 partners, 8
+// targets and 2000 samples, all rung-2 features: mul / rdiv tiles 6.6 ms, div
+// tiles 5.2 ms (with operands through registers, two column tiles per wave
+// and rows in the products' order 11.9 and 7.1; with three tiles and copies
+// to LDS, rows in the products' order, 8.4 and 6.5).
 // HK: the launch's column tiles multiply 1/g (div), else g (mul, rdiv);
 // the two kinds are separate launches, so that neither carries the
 // other's per-sample work.  Column tiles past the launch's range (the last
